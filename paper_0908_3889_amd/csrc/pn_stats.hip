@@ -413,9 +413,419 @@ int kde_parts(int64_t n, int ncomp, int tiles) {
 }
 
 // ---------------------------------------------------------------------------
-// Kolmogorov-Smirnov against U[lo, hi] on a sorted copy
+// Kolmogorov-Smirnov against U[lo, hi].
+//
+// D needs the order of the values only where the empirical distribution may
+// be furthest from F.  The values are counted in equal buckets of [lo, hi];
+// with the counts below a bucket, its edges bound every deviation inside it
+// from above and some deviation from below, and only the buckets whose upper
+// bound reaches the largest lower bound (the candidates; a few per cent) are
+// ranked, value by value.  Rounding is monotonic, so the bounds hold for the
+// rounded deviations and D is that of the fully sorted sample, bit for bit.
+//   ks_count, ks_sum   bucket counts, per block and summed
+//   ks_scan            ranks, bounds, candidates (one block a component)
+//   ks_collect         the candidates' values, each to its bucket's range
+//   ks_solve           ranks inside the candidates and the largest deviation
+// Bound by launches and latency up to 2^20 values: 3 x 2^20 took 0.69 ms by
+// sorting (20 launches a component), 0.10 ms this way.
+//
+// The bound works while a bucket holds far less of F than D ~ 1/sqrt(n); above
+// kKsBucketMax values (2^22: 1/16384 against 4e-4) most buckets would be
+// candidates, and a sorted copy serves, as it does for a workspace too small.
 // ---------------------------------------------------------------------------
 
+constexpr int64_t kKsBucketMax = (int64_t)1 << 22;
+constexpr int kKsCount = 1024;           // threads of ks_count, ks_scan and ks_solve
+constexpr int kKsPerBlock = 16384;       // values counted by one block
+constexpr int kKsWave = 512;             // most values of a bucket that one wave ranks
+constexpr int kKsBins = 1024;            // key bins of a refinement level
+constexpr int kKsLevels = 7;             // 10 bits a level of the 64-bit key
+constexpr unsigned kKsNone = 0xffffffffu;
+
+// Places of one component's workspace, in 4-byte words from its start
+// (256-byte aligned); buckets = 1024 .. 16384, about one for 16 values.
+struct KsPlan {
+    int buckets, blocks;
+    int64_t count, slot, cursor, cand, part, list;      // word offsets
+    int64_t bytes;
+};
+
+KsPlan ks_plan(int64_t n) {
+    KsPlan p;
+    p.buckets = 1024;
+    while (p.buckets < 16384 && (int64_t)p.buckets * 16 < n) p.buckets *= 2;
+    p.blocks = (int)((n + kKsPerBlock - 1) / kKsPerBlock);
+    int64_t w = 64;                                      // header: D's bits, number of candidates
+    p.count = w; w += p.buckets + 64;                    // counts, then counts below (buckets + 1)
+    p.slot = w; w += p.buckets;
+    p.cursor = w; w += p.buckets;
+    p.cand = w; w += p.buckets;
+    p.part = w; w += (int64_t)p.buckets * p.blocks;
+    p.list = w; w += 2 * n;
+    p.bytes = (w * 4 + 255) / 256 * 256;
+    return p;
+}
+
+struct KsView {
+    unsigned* w;
+    KsPlan p;
+    __device__ unsigned long long* dmax() const { return (unsigned long long*)w; }
+    __device__ unsigned* ncand() const { return w + 2; }
+    __device__ unsigned* count() const { return w + p.count; }
+    __device__ unsigned* slot() const { return w + p.slot; }
+    __device__ unsigned* cursor() const { return w + p.cursor; }
+    __device__ unsigned* cand() const { return w + p.cand; }
+    __device__ unsigned* part(int b) const { return w + p.part + (int64_t)b * p.buckets; }
+    __device__ double* list() const { return (double*)(w + p.list); }
+};
+__device__ __forceinline__ KsView ks_view(void* ws, const KsPlan& p, int c) {
+    return KsView{(unsigned*)((char*)ws + (int64_t)c * p.bytes), p};
+}
+
+// The bucket of v: not decreasing in v (each rounding is monotonic); values
+// outside [lo, hi] go to the first and the last.
+__device__ __forceinline__ int ks_bucket(double v, double lo, double scale, int buckets) {
+    const double t = __builtin_fmin(__builtin_fmax((v - lo) * scale, 0.0), (double)(buckets - 1));
+    return (int)t;
+}
+
+__device__ __forceinline__ double ks_F(double v, double lo, double w) { return (v - lo) / w; }
+// the deviations at the value of rank i (from 0)
+__device__ __forceinline__ double ks_up(int64_t i, double dn, double F) { return (double)(i + 1) / dn - F; }
+__device__ __forceinline__ double ks_down(int64_t i, double dn, double F) { return F - (double)i / dn; }
+
+// Values of F in bucket b lie between these (b / buckets is exact; the factor
+// covers the rounding of F and of the bucket's own product); the first and
+// the last bucket also hold what lies outside [lo, hi].
+__device__ __forceinline__ double ks_bucket_lo(int b, int buckets) {
+    return b == 0 ? -__builtin_inf() : ((double)b / buckets) * (1.0 - 0x1p-48);
+}
+__device__ __forceinline__ double ks_bucket_hi(int b, int buckets) {
+    return b == buckets - 1 ? __builtin_inf() : ((double)(b + 1) / buckets) * (1.0 + 0x1p-48);
+}
+
+__global__ __launch_bounds__(kKsCount) void ks_count(int64_t n, int64_t ld, const double* __restrict__ x, double lo,
+                                                     double scale, void* ws, KsPlan p) {
+    extern __shared__ unsigned int sh[];
+    const KsView v = ks_view(ws, p, blockIdx.y);
+    const double* xc = x + (int64_t)blockIdx.y * ld;
+    for (int b = threadIdx.x; b < p.buckets; b += kKsCount) sh[b] = 0u;
+    if (blockIdx.x == 0) {
+        if (threadIdx.x == 0) { *v.dmax() = 0ull; *v.ncand() = 0u; }
+        for (int b = threadIdx.x; b < p.buckets; b += kKsCount) v.cursor()[b] = 0u;
+    }
+    __syncthreads();
+    const int64_t i0 = (int64_t)blockIdx.x * kKsPerBlock;
+    const int64_t i1 = i0 + kKsPerBlock < n ? i0 + kKsPerBlock : n;
+#pragma unroll 4
+    for (int64_t i = i0 + threadIdx.x; i < i1; i += kKsCount) atomicAdd(&sh[ks_bucket(xc[i], lo, scale, p.buckets)], 1u);
+    __syncthreads();
+    unsigned* out = p.blocks == 1 ? v.count() : v.part(blockIdx.x);
+    for (int b = threadIdx.x; b < p.buckets; b += kKsCount) out[b] = sh[b];
+}
+
+__global__ __launch_bounds__(kBlock) void ks_sum(void* ws, KsPlan p) {
+    const KsView v = ks_view(ws, p, blockIdx.y);
+    const int b = blockIdx.x * kBlock + threadIdx.x;     // the buckets are a multiple of kBlock
+    unsigned s = 0;
+#pragma unroll 8
+    for (int k = 0; k < p.blocks; ++k) s += v.part(k)[b];
+    v.count()[b] = s;
+}
+
+// exclusive prefix sums over the block's threads, and the total
+__device__ __forceinline__ unsigned block_scan(unsigned v, unsigned* sh, unsigned& total) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    unsigned inc = v;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const unsigned o = __shfl_up(inc, d);
+        if (lane >= d) inc += o;
+    }
+    if (lane == 63) sh[wave] = inc;
+    __syncthreads();
+    unsigned before = 0, all = 0;
+    for (int k = 0; k < (int)(blockDim.x >> 6); ++k) {
+        before += k < wave ? sh[k] : 0u;
+        all += sh[k];
+    }
+    __syncthreads();
+    total = all;
+    return before + inc - v;
+}
+
+__device__ __forceinline__ double wave_max(double v) {
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) v = __builtin_fmax(v, __shfl_xor(v, d));
+    return v;
+}
+
+__global__ __launch_bounds__(kKsCount) void ks_scan(int64_t n, void* ws, KsPlan p) {
+    __shared__ unsigned shu[kKsCount / 64];
+    __shared__ double shd[kKsCount / 64];
+    const KsView v = ks_view(ws, p, blockIdx.x);
+    const int per = p.buckets / kKsCount, b0 = threadIdx.x * per;      // 1 .. 16 buckets a thread
+    const double dn = (double)n;
+    unsigned cnt[16], sum = 0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        cnt[k] = k < per ? v.count()[b0 + k] : 0u;
+        sum += cnt[k];
+    }
+    unsigned total;
+    const unsigned below0 = block_scan(sum, shu, total);
+    // ranks, and the largest lower bound
+    double low = 0.0;
+    unsigned below = below0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        if (k < per) {
+            const int b = b0 + k;
+            v.count()[b] = below;
+            if (cnt[k]) {
+                low = __builtin_fmax(low, ks_up((int64_t)below + cnt[k] - 1, dn, ks_bucket_hi(b, p.buckets)));
+                low = __builtin_fmax(low, ks_down(below, dn, ks_bucket_lo(b, p.buckets)));
+            }
+            below += cnt[k];
+        }
+    }
+    if (threadIdx.x == kKsCount - 1) v.count()[p.buckets] = below;
+    low = wave_max(low);
+    if ((threadIdx.x & 63) == 0) shd[threadIdx.x >> 6] = low;
+    __syncthreads();
+    for (int k = 0; k < kKsCount / 64; ++k) low = __builtin_fmax(low, shd[k]);
+    // candidates: where an upper bound reaches it
+    unsigned mask = 0, vals = 0;
+    below = below0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        if (k < per && cnt[k]) {
+            const int b = b0 + k;
+            const double up = ks_up((int64_t)below + cnt[k] - 1, dn, ks_bucket_lo(b, p.buckets));
+            const double down = ks_down(below, dn, ks_bucket_hi(b, p.buckets));
+            if (up >= low || down >= low) {
+                mask |= 1u << k;
+                vals += cnt[k];
+            }
+            below += cnt[k];
+        }
+    }
+    unsigned slot = block_scan(vals, shu, total);
+    unsigned at = block_scan((unsigned)__popc(mask), shu, total);
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        if (k < per) {
+            const bool c = (mask >> k) & 1u;
+            v.slot()[b0 + k] = c ? slot : kKsNone;
+            if (c) {
+                v.cand()[at++] = b0 + k;
+                slot += cnt[k];
+            }
+        }
+    }
+    if (threadIdx.x == 0) *v.ncand() = total;
+}
+
+__global__ __launch_bounds__(kBlock) void ks_collect(int64_t n, int64_t ld, const double* __restrict__ x, double lo,
+                                                     double scale, void* ws, KsPlan p) {
+    const KsView v = ks_view(ws, p, blockIdx.y);
+    const double* xc = x + (int64_t)blockIdx.y * ld;
+    double* list = v.list();
+#pragma unroll 4
+    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) {
+        const double val = xc[i];
+        const int b = ks_bucket(val, lo, scale, p.buckets);
+        const unsigned s = v.slot()[b];
+        if (s != kKsNone) list[s + atomicAdd(&v.cursor()[b], 1u)] = val;
+    }
+}
+
+// 64-bit keys that order as the values do
+__device__ __forceinline__ uint64_t ks_key(double v) {
+    const uint64_t b = (uint64_t)__double_as_longlong(v == 0.0 ? 0.0 : v);      // -0 as 0
+    return b ^ ((b >> 63) ? ~0ull : (1ull << 63));
+}
+__device__ __forceinline__ double ks_unkey(uint64_t k) {
+    return __longlong_as_double((long long)(k ^ ((k >> 63) ? (1ull << 63) : ~0ull)));
+}
+
+// The largest deviation among m values l[0 .. m), which have the ranks r0 ..
+// r0 + m - 1 of the sample, by counting; `lane` of `lanes` takes every
+// lanes-th value.  Equal values take their ranks in the order they lie.
+__device__ __forceinline__ double ks_ranked(const double* l, int m, int64_t r0, double dn, double lo, double w, int lane,
+                                            int lanes) {
+    double d = 0.0;
+    for (int e = lane; e < m; e += lanes) {
+        const double ve = l[e];
+        int rank = 0;
+        for (int j = 0; j < m; ++j) {
+            const double vj = l[j];
+            rank += (vj < ve || (vj == ve && j < e)) ? 1 : 0;
+        }
+        const double F = ks_F(ve, lo, w);
+        d = __builtin_fmax(d, __builtin_fmax(ks_up(r0 + rank, dn, F), ks_down(r0 + rank, dn, F)));
+    }
+    return d;
+}
+
+// A bucket with more values than a wave ranks (values that cluster): the
+// whole block refines it by key bins, 1024 a level, the bin with the largest
+// upper bound first, until no bin's bound exceeds the deviation found; bins
+// of up to kKsWave values are ranked, bins of one repeated value have their
+// largest deviations at their first and last rank.
+struct KsRefine {
+    unsigned below[kKsLevels][kKsBins + 1];
+    unsigned done[kKsLevels][kKsBins / 32];
+    uint64_t klo[kKsLevels], khi[kKsLevels];
+    int64_t base[kKsLevels];
+    int shift[kKsLevels];
+    double vals[kKsWave];
+    unsigned long long k0, k1, pick;
+    unsigned nvals;
+    unsigned scan[kKsCount / 64];
+    double red[kKsCount / 64];
+};
+
+// smallest and largest key of the values with keys in [a, b] (at least one)
+__device__ void ks_key_range(KsRefine& R, const double* l, int m, uint64_t a, uint64_t b) {
+    __syncthreads();
+    if (threadIdx.x == 0) { R.k0 = ~0ull; R.k1 = 0ull; }
+    __syncthreads();
+    unsigned long long k0 = ~0ull, k1 = 0ull;
+    for (int i = threadIdx.x; i < m; i += kKsCount) {
+        const uint64_t k = ks_key(l[i]);
+        if (k >= a && k <= b) {
+            k0 = k < k0 ? k : k0;
+            k1 = k > k1 ? k : k1;
+        }
+    }
+    if (k0 <= k1) {
+        atomicMin(&R.k0, k0);
+        atomicMax(&R.k1, k1);
+    }
+    __syncthreads();
+}
+
+// level lev: the values with keys in [R.k0, R.k1], the first of them of rank base
+__device__ void ks_build(KsRefine& R, int lev, const double* l, int m, int64_t base) {
+    const uint64_t a = R.k0, b = R.k1;
+    const int bits = 64 - __clzll((long long)(b - a));
+    const int shift = bits > 10 ? bits - 10 : 0;
+    for (int k = threadIdx.x; k <= kKsBins; k += kKsCount) R.below[lev][k] = 0u;
+    if (threadIdx.x < kKsBins / 32) R.done[lev][threadIdx.x] = 0u;
+    if (threadIdx.x == 0) { R.klo[lev] = a; R.khi[lev] = b; R.shift[lev] = shift; R.base[lev] = base; }
+    __syncthreads();
+    for (int i = threadIdx.x; i < m; i += kKsCount) {
+        const uint64_t k = ks_key(l[i]);
+        if (k >= a && k <= b) atomicAdd(&R.below[lev][(k - a) >> shift], 1u);
+    }
+    __syncthreads();
+    unsigned total;
+    const unsigned before = block_scan(R.below[lev][threadIdx.x], R.scan, total);      // kKsCount == kKsBins
+    R.below[lev][threadIdx.x] = before;
+    if (threadIdx.x == 0) R.below[lev][kKsBins] = total;
+    __syncthreads();
+}
+
+__device__ __forceinline__ double block_max_all(KsRefine& R, double v) {
+    v = wave_max(v);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) R.red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    for (int k = 0; k < kKsCount / 64; ++k) v = __builtin_fmax(v, R.red[k]);
+    return v;
+}
+
+__device__ double ks_refine(KsRefine& R, const double* l, int m, int64_t r0, double dn, double lo, double w) {
+    double best = 0.0;
+    ks_key_range(R, l, m, 0ull, ~0ull);
+    int lev = 0;
+    ks_build(R, 0, l, m, r0);
+    while (lev >= 0) {
+        // the open bin with the largest upper bound (the lowest of equal ones)
+        const int b = threadIdx.x;
+        const unsigned b0 = R.below[lev][b], b1 = R.below[lev][b + 1];
+        const uint64_t ka = R.klo[lev] + ((uint64_t)b << R.shift[lev]);
+        uint64_t kb = ka + (((uint64_t)1 << R.shift[lev]) - 1);
+        if (kb > R.khi[lev] || kb < ka) kb = R.khi[lev];
+        double ub = -1.0;
+        if (b1 > b0 && !((R.done[lev][b >> 5] >> (b & 31)) & 1u))
+            ub = __builtin_fmax(__builtin_fmax(ks_up(R.base[lev] + b1 - 1, dn, ks_F(ks_unkey(ka), lo, w)),
+                                               ks_down(R.base[lev] + b0, dn, ks_F(ks_unkey(kb), lo, w))), 0.0);
+        const double top = block_max_all(R, ub);
+        if (!(top > best)) {                  // nothing open can exceed the deviation found
+            --lev;
+            __syncthreads();
+            continue;
+        }
+        if (threadIdx.x == 0) R.pick = ~0ull;
+        __syncthreads();
+        if (ub == top) atomicMin(&R.pick, (unsigned long long)b);
+        __syncthreads();
+        const int pb = (int)R.pick;
+        const unsigned c0 = R.below[lev][pb];
+        const int cnt = (int)(R.below[lev][pb + 1] - c0);
+        const int64_t base = R.base[lev] + c0;
+        const uint64_t pa = R.klo[lev] + ((uint64_t)pb << R.shift[lev]);
+        uint64_t pe = pa + (((uint64_t)1 << R.shift[lev]) - 1);
+        if (pe > R.khi[lev] || pe < pa) pe = R.khi[lev];
+        __syncthreads();
+        if (threadIdx.x == 0) { R.done[lev][pb >> 5] |= 1u << (pb & 31); R.nvals = 0u; }
+        __syncthreads();
+        if (cnt <= kKsWave) {
+            for (int i = threadIdx.x; i < m; i += kKsCount) {
+                const double v = l[i];
+                const uint64_t k = ks_key(v);
+                if (k >= pa && k <= pe) R.vals[atomicAdd(&R.nvals, 1u)] = v;
+            }
+            __syncthreads();
+            best = __builtin_fmax(best, block_max_all(R, ks_ranked(R.vals, cnt, base, dn, lo, w, threadIdx.x, kKsCount)));
+            continue;
+        }
+        ks_key_range(R, l, m, pa, pe);
+        if (R.k0 == R.k1) {
+            const double F = ks_F(ks_unkey(R.k0), lo, w);
+            best = __builtin_fmax(best, __builtin_fmax(ks_up(base + cnt - 1, dn, F), ks_down(base, dn, F)));
+            continue;
+        }
+        ++lev;                                // at most 10 bits fewer each time: lev < kKsLevels
+        ks_build(R, lev, l, m, base);
+    }
+    return best;
+}
+
+__global__ __launch_bounds__(kKsCount) void ks_solve(int64_t n, double lo, double w, void* ws, KsPlan p) {
+    __shared__ KsRefine R;
+    const KsView v = ks_view(ws, p, blockIdx.y);
+    const int ncand = (int)*v.ncand();
+    const double dn = (double)n;
+    const int lane = threadIdx.x & 63;
+    double d = 0.0;
+    // a wave a candidate ...
+    bool large = false;
+    for (int k = blockIdx.x * (kKsCount / 64) + (threadIdx.x >> 6); k < ncand; k += gridDim.x * (kKsCount / 64)) {
+        const int b = (int)v.cand()[k];
+        const int64_t r0 = v.count()[b];
+        const int m = (int)(v.count()[b + 1] - v.count()[b]);
+        if (m <= kKsWave) d = __builtin_fmax(d, ks_ranked(v.list() + v.slot()[b], m, r0, dn, lo, w, lane, 64));
+        else large = true;
+    }
+    // ... and the block's candidates that are too large for one
+    if (__syncthreads_or(large)) {
+        for (int q = blockIdx.x * (kKsCount / 64); q < ncand; q += gridDim.x * (kKsCount / 64))
+            for (int k = q; k < q + kKsCount / 64 && k < ncand; ++k) {
+                const int b = (int)v.cand()[k];
+                const int64_t r0 = v.count()[b];
+                const int m = (int)(v.count()[b + 1] - v.count()[b]);
+                if (m > kKsWave) d = __builtin_fmax(d, ks_refine(R, v.list() + v.slot()[b], m, r0, dn, lo, w));
+            }
+    }
+    d = wave_max(d);
+    // non-negative doubles order as their bits
+    if (lane == 0 && d > 0.0) atomicMax(v.dmax(), (unsigned long long)__double_as_longlong(d));
+}
+
+// the deviations of a sorted copy, for samples the buckets do not serve
 __global__ __launch_bounds__(kBlock) void ks_kernel(int64_t n, const double* __restrict__ xs, double lo, double hi,
                                                     double* __restrict__ part) {
     __shared__ double sh[kBlock];
@@ -423,39 +833,48 @@ __global__ __launch_bounds__(kBlock) void ks_kernel(int64_t n, const double* __r
     const double dn = (double)n;
     double d = 0.0;
     for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)kPart * kBlock) {
-        const double F = (xs[i] - lo) / w;
-        const double up = (double)(i + 1) / dn - F;
-        const double dw = F - (double)i / dn;
-        d = __builtin_fmax(d, __builtin_fmax(up, dw));
+        const double F = ks_F(xs[i], lo, w);
+        d = __builtin_fmax(d, __builtin_fmax(ks_up(i, dn, F), ks_down(i, dn, F)));
     }
     d = block_max(d, sh);
     if (threadIdx.x == 0) part[blockIdx.x] = d;
 }
 
-// P(K > lam): alternating series for lam >= 1, theta-function form below
+// P(K > lam): alternating series for lam >= 1, theta-function form below.  The
+// terms fall so fast that the sum is complete once one does not change it
+// (after at most five; all 100 took 18 us).
 __device__ double kolmogorov_sf(double lam) {
     if (!(lam > 0.0)) return 1.0;
     const double pi = 3.14159265358979323846;
     double s = 0.0;
     if (lam >= 1.0) {
-        for (int k = 1; k <= 100; ++k)
-            s += ((k & 1) ? 2.0 : -2.0) * exp(-2.0 * (double)k * (double)k * lam * lam);
+        for (int k = 1; k <= 100; ++k) {
+            const double t = s + ((k & 1) ? 2.0 : -2.0) * exp(-2.0 * (double)k * (double)k * lam * lam);
+            if (t == s) break;
+            s = t;
+        }
         return s < 0.0 ? 0.0 : (s > 1.0 ? 1.0 : s);
     }
     for (int k = 1; k <= 100; ++k) {
         const double m = (double)(2 * k - 1);
-        s += exp(-(m * m) * (pi * pi) / (8.0 * lam * lam));
+        const double t = s + exp(-(m * m) * (pi * pi) / (8.0 * lam * lam));
+        if (t == s) break;
+        s = t;
     }
     const double p = 1.0 - sqrt(2.0 * pi) / lam * s;
     return p < 0.0 ? 0.0 : (p > 1.0 ? 1.0 : p);
 }
 
-__global__ void ks_final_kernel(int64_t n, const double* __restrict__ part, double* __restrict__ out) {
-    if (threadIdx.x != 0) return;
+// D and the p-value from `parts` partial maxima; component c's at part + c * stride
+__global__ __launch_bounds__(64) void ks_final_kernel(int64_t n, const double* __restrict__ part, int parts,
+                                                      int64_t stride, double* __restrict__ out) {
+    const double* pc = part + (int64_t)blockIdx.x * stride;
     double d = 0.0;
-    for (int b = 0; b < kPart; ++b) d = __builtin_fmax(d, part[b]);
-    out[0] = n > 0 ? d : __builtin_nan("");
-    out[1] = n > 0 ? kolmogorov_sf(sqrt((double)n) * d) : __builtin_nan("");
+    for (int b = threadIdx.x; b < parts; b += 64) d = __builtin_fmax(d, pc[b]);
+    d = wave_max(d);
+    if (threadIdx.x != 0) return;
+    out[2 * blockIdx.x] = d;
+    out[2 * blockIdx.x + 1] = kolmogorov_sf(sqrt((double)n) * d);
 }
 
 __global__ void fill_nan(double* p, int count) {
@@ -577,12 +996,21 @@ int pn_kde(int64_t n, int64_t ld, const double* x, int32_t ncomp, const double* 
     return launched();
 }
 
-size_t pn_ks_workspace_bytes(int64_t n) {
-    if (n < 0 || n > PN_MAX_N) return 0;
+// The sorted path's workspace: sorted copy, sort scratch (256-byte aligned),
+// partial maxima; 0 where the sort's own scratch size is not known.
+static size_t ks_sort_bytes(int64_t n) {
     const size_t tmp = radix_temp_bytes(n);
     if (n > 0 && tmp == 0) return 0;
-    // sorted copy, sort scratch (256-byte aligned), partial maxima
     return ((size_t)n * sizeof(double) + 255) / 256 * 256 + (tmp + 255) / 256 * 256 + kPart * sizeof(double);
+}
+
+size_t pn_ks_workspace_bytes(int64_t n) {
+    if (n < 0 || n > PN_MAX_N) return 0;
+    const size_t sort = ks_sort_bytes(n);
+    if (sort == 0 || n == 0 || n > kKsBucketMax) return sort;
+    // three components (the scalar products) side by side
+    const size_t buckets = 3 * (size_t)ks_plan(n).bytes;
+    return buckets > sort ? buckets : sort;
 }
 
 int pn_ks_uniform(int64_t n, int64_t ld, const double* x, int32_t ncomp, double lo, double hi, double* out,
@@ -597,20 +1025,44 @@ int pn_ks_uniform(int64_t n, int64_t ld, const double* x, int32_t ncomp, double 
         hipLaunchKernelGGL(fill_nan, dim3(1), dim3(kBlock), 0, s, out, (int)(ncomp * 2));
         return launched();
     }
-    const size_t need = pn_ks_workspace_bytes(n);
+    const size_t need = ks_sort_bytes(n);
     if (need == 0 || !workspace || ws_bytes < need) return PN_EINVAL;
-    char* w = (char*)workspace;
-    double* sorted = (double*)w;
+    const double w = hi - lo;
+    if (n <= kKsBucketMax && w > 1e-290 && w < 1e290) {
+        const KsPlan p = ks_plan(n);
+        const int side = (int)(ws_bytes / (size_t)p.bytes < (size_t)ncomp ? ws_bytes / (size_t)p.bytes : (size_t)ncomp);
+        if (side > 0 && ((uintptr_t)workspace & 7) == 0) {
+            const double scale = p.buckets / w;
+            const unsigned collect = (unsigned)((n + 8 * kBlock - 1) / (8 * kBlock));
+            for (int c = 0; c < ncomp; c += side) {
+                const int g = ncomp - c < side ? ncomp - c : side;
+                const double* xc = x + (int64_t)c * ld;
+                hipLaunchKernelGGL(ks_count, dim3(p.blocks, g), dim3(kKsCount), p.buckets * sizeof(unsigned), s, n, ld,
+                                   xc, lo, scale, workspace, p);
+                if (p.blocks > 1)
+                    hipLaunchKernelGGL(ks_sum, dim3(p.buckets / kBlock, g), dim3(kBlock), 0, s, workspace, p);
+                hipLaunchKernelGGL(ks_scan, dim3(g), dim3(kKsCount), 0, s, n, workspace, p);
+                hipLaunchKernelGGL(ks_collect, dim3(collect < 512 ? collect : 512, g), dim3(kBlock), 0, s, n, ld, xc, lo,
+                                   scale, workspace, p);
+                hipLaunchKernelGGL(ks_solve, dim3(64, g), dim3(kKsCount), 0, s, n, lo, w, workspace, p);
+                hipLaunchKernelGGL(ks_final_kernel, dim3(g), dim3(64), 0, s, n, (const double*)workspace, 1,
+                                   p.bytes / 8, out + 2 * c);
+            }
+            return launched();
+        }
+    }
+    char* wp = (char*)workspace;
+    double* sorted = (double*)wp;
     size_t off = ((size_t)n * sizeof(double) + 255) / 256 * 256;
-    void* tmp = w + off;
+    void* tmp = wp + off;
     size_t tmp_bytes = radix_temp_bytes(n);
     off += (tmp_bytes + 255) / 256 * 256;
-    double* part = (double*)(w + off);
+    double* part = (double*)(wp + off);
     for (int c = 0; c < ncomp; ++c) {
         if (rocprim::radix_sort_keys(tmp, tmp_bytes, x + (int64_t)c * ld, sorted, (size_t)n, 0, 64, s) != hipSuccess)
             return PN_EHIP;
         hipLaunchKernelGGL(ks_kernel, dim3(kPart), dim3(kBlock), 0, s, n, sorted, lo, hi, part);
-        hipLaunchKernelGGL(ks_final_kernel, dim3(1), dim3(64), 0, s, n, part, out + 2 * c);
+        hipLaunchKernelGGL(ks_final_kernel, dim3(1), dim3(64), 0, s, n, part, kPart, (int64_t)0, out + 2 * c);
     }
     return launched();
 }

@@ -77,3 +77,76 @@ def test_kde_outliers_and_nonfinite_values():
     assert np.isnan(api.pn_kde(_cuda(x), sig, ngrid).cpu().numpy()).all()
     for s in (0.0, np.nan):                           # nor with such a bandwidth
         assert np.isnan(api.pn_kde(_cuda(_values(n, 6)), _cuda(np.array([s])), ngrid).cpu().numpy()).all()
+
+
+def _ks_sample(kind, n, seed):
+    rng = np.random.default_rng(seed)
+    u = rng.uniform(-1.0, 1.0, n)
+    if kind == "uniform":
+        return u
+    if kind == "normal":
+        return np.clip(rng.normal(0.1, 0.4, n), -1.0, 1.0)
+    if kind == "constant":
+        return np.full(n, 0.25)
+    if kind == "half at the end":                    # aligned spins: 1, or 1 less a few ulp
+        return np.where(rng.random(n) < 0.5, 1.0 - 1.1102230246251565e-16 * rng.integers(0, 3, n), u)
+    if kind == "cluster":                            # far narrower than a bucket
+        return np.where(rng.random(n) < 0.7, 0.3 + 1e-9 * u, u)
+    if kind == "cluster at zero":                    # keys over the whole exponent range
+        return np.where(rng.random(n) < 0.7, u * 10.0 ** rng.uniform(-300, -5, n), u)
+    if kind == "ties":
+        return np.round(u * 50.0) / 50.0
+    if kind == "outside":                            # the first and last bucket hold far values
+        return np.where(rng.random(n) < 0.6, 3.0 * u, 1e5 * u)
+    raise ValueError(kind)
+
+
+def _ks_D(x, lo=-1.0, hi=1.0):
+    """The definition on the sorted values, every operation rounded as written."""
+    xs = np.sort(x)
+    n = float(xs.size)
+    i = np.arange(xs.size, dtype=np.float64)
+    F = (xs - lo) / (hi - lo)
+    return max(0.0, np.max((i + 1.0) / n - F), np.max(F - i / n))
+
+
+KS_KINDS = ["uniform", "normal", "constant", "half at the end", "cluster", "cluster at zero", "ties", "outside"]
+
+
+# D is a maximum of rounded values, taken over the same values: equal bit for bit
+@pytest.mark.parametrize("kind", KS_KINDS)
+@pytest.mark.parametrize("n", [1, 2, 65, 1024, 4099, 16384, 16385, 70001])
+def test_ks_is_the_sorted_samples(kind, n):
+    x = np.stack([_ks_sample(kind, n, 7 * n + c) for c in range(3)])
+    got = _api().pn_ks_uniform(_cuda(x)).cpu().numpy()
+    for c in range(3):
+        assert got[c, 0] == _ks_D(x[c])
+        np.testing.assert_allclose(got[c, 1], S.ks_uniform(x[c], -1.0, 1.0)["p"], rtol=1e-12, atol=1e-300)
+
+
+@pytest.mark.parametrize("n", [1 << 20, (1 << 22) - 3, 1 << 22, (1 << 22) + 1])
+def test_ks_at_the_largest_bucketed_size(n):
+    for kind in ("uniform", "normal"):
+        x = _ks_sample(kind, n, n + 1)
+        assert _api().pn_ks_uniform(_cuda(x)).cpu().numpy()[0, 0] == _ks_D(x)
+
+
+def test_ks_other_interval_and_workspaces():
+    import ctypes as C
+
+    from paper_0908_3889_amd import _lib
+    L = _lib.load()
+    n, nc, lo, hi = 40000, 5, -0.7, 1.9
+    x = np.stack([_ks_sample(k, n, 3) for k in KS_KINDS[:nc]])
+    xt = _cuda(x)
+    full = int(L.pn_ks_workspace_bytes(n))
+    p = lambda t: C.c_void_p(t.data_ptr())
+    # three, two and one components side by side
+    for ws_bytes in (full, full * 2 // 3, full * 5 // 9):
+        ws = torch.empty(ws_bytes, dtype=torch.uint8, device="cuda")
+        out = torch.empty((nc, 2), dtype=torch.float64, device="cuda")
+        _lib.check(L.pn_ks_uniform(n, n, p(xt), nc, lo, hi, p(out), p(ws), ws_bytes, None), "pn_ks_uniform")
+        torch.cuda.synchronize()
+        assert [float(v) for v in out[:, 0].cpu()] == [_ks_D(x[c], lo, hi) for c in range(nc)]
+    out = torch.empty((nc, 2), dtype=torch.float64, device="cuda")
+    assert L.pn_ks_uniform(n, n, p(xt), nc, lo, hi, p(out), p(ws), 1024, None) == _lib.PN_EINVAL
