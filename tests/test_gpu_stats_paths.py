@@ -150,3 +150,42 @@ def test_ks_other_interval_and_workspaces():
         assert [float(v) for v in out[:, 0].cpu()] == [_ks_D(x[c], lo, hi) for c in range(nc)]
     out = torch.empty((nc, 2), dtype=torch.float64, device="cuda")
     assert L.pn_ks_uniform(n, n, p(xt), nc, lo, hi, p(out), p(ws), 1024, None) == _lib.PN_EINVAL
+
+
+# one block, the first size of two, a ragged last one; bins from one copy of the
+# counters to 32; values on the edges, outside and not a number; a leading
+# dimension above n
+@pytest.mark.parametrize("n", [1, 1000, 16384, 16385, 50001])
+@pytest.mark.parametrize("nbins", [1, 20, 79, 128])
+def test_histogram_blocks(n, nbins):
+    api = _api()
+    rng = np.random.default_rng(n + nbins)
+    lo, hi = -1.0, 0.9
+    x = rng.uniform(-1.1, 1.1, (2, n))
+    edges = S.bin_edges(lo, hi, nbins)
+    k = min(n, edges.size)
+    x[0, :k] = edges[:k]
+    if n > 1:
+        x[1, -1] = np.nan
+    y = np.roll(x, 1, axis=1) * 0.9
+    wide = torch.zeros((4, n + 13), dtype=torch.float64, device="cuda")
+    wide[:2, :n], wide[2:, :n] = _cuda(x), _cuda(y)
+    one = api.pn_histogram(wide[:2, :n], nbins, lo, hi).cpu().numpy()
+    two = api.pn_histogram2d(wide[:2, :n], wide[2:, :n], nbins, lo, hi).cpu().numpy()
+    for c in range(2):
+        assert (one[c] == S.histogram(x[c], lo, hi, nbins)).all()
+        assert (two[c] == S.histogram2d(x[c], y[c], lo, hi, nbins)).all()
+
+
+def test_histogram_largest_number_of_bins():
+    x = np.random.default_rng(9).uniform(-1.0, 1.0, (1, 30000))
+    for nbins in (129, 256, 2048, 4096):
+        assert (_api().pn_histogram(_cuda(x), nbins).cpu().numpy()[0] == S.histogram(x[0], -1.0, 1.0, nbins)).all()
+
+
+# bins so narrow against the interval's ends that the rounding of an edge is a
+# good part of a bin: every value is placed by the edges
+def test_histogram_bins_near_the_rounding_of_the_edges():
+    lo, hi, nbins = 1e10, 1e10 + 1e-4, 20
+    x = np.random.default_rng(4).uniform(lo, hi, (1, 20000))
+    assert (_api().pn_histogram(_cuda(x), nbins, lo, hi).cpu().numpy()[0] == S.histogram(x[0], lo, hi, nbins)).all()
