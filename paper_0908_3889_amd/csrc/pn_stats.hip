@@ -165,21 +165,26 @@ __global__ __launch_bounds__(kHistBlock) void hist2d_kernel(int64_t n, int64_t l
 // fixed-order block reductions
 // ---------------------------------------------------------------------------
 
-template <int K>
-__device__ __forceinline__ void block_sum(double (&v)[K], double (*sh)[kBlock]) {
+// the sums over a block of THREADS, in every thread
+template <int K, int THREADS>
+__device__ __forceinline__ void block_sum(double (&v)[K], double (*sh)[THREADS / 64]) {
 #pragma unroll
-    for (int k = 0; k < K; ++k) sh[k][threadIdx.x] = v[k];
-    __syncthreads();
-    for (int s = kBlock / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) {
+    for (int k = 0; k < K; ++k) {
 #pragma unroll
-            for (int k = 0; k < K; ++k) sh[k][threadIdx.x] += sh[k][threadIdx.x + s];
-        }
-        __syncthreads();
+        for (int d = 32; d > 0; d >>= 1) v[k] += __shfl_xor(v[k], d);
     }
-#pragma unroll
-    for (int k = 0; k < K; ++k) v[k] = sh[k][0];
     __syncthreads();
+    if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) sh[k][threadIdx.x >> 6] = v[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        v[k] = 0.0;
+#pragma unroll
+        for (int w = 0; w < THREADS / 64; ++w) v[k] += sh[k][w];
+    }
 }
 
 __device__ __forceinline__ double block_max(double v, double* sh) {
@@ -195,84 +200,125 @@ __device__ __forceinline__ double block_max(double v, double* sh) {
 }
 
 // ---------------------------------------------------------------------------
-// Pearson: pass 1 sums, pass 2 centred sums (workspace: part[c][kPart][3],
-// then mean[c][2])
+// Pearson: sums, then sums of the centred products.  Samples of one block
+// (kPearOne values) are kept in its registers between the two; larger ones
+// take two passes over kPearParts blocks, each block of the second forming the
+// means from all partial sums of the first (workspace: part2[c][kPearParts][3],
+// part1[c][kPearParts][2], mean[c][2]).  Bound by launches and latency for
+// small samples (3 x 4,099: four launches 12 us, one 6 us; 3 x 16,384: 18 and
+// 9 us), by the two passes over memory for large ones (3 x 2^20: four launches
+// 30 us, three 24 us).
 // ---------------------------------------------------------------------------
 
-__global__ __launch_bounds__(kBlock) void sums_kernel(int64_t n, int64_t ld, const double* __restrict__ x,
-                                                      const double* __restrict__ y, double* __restrict__ part) {
-    __shared__ double sh[2][kBlock];
+constexpr int kPearBlock = 512;
+constexpr int kPearParts = 256;
+constexpr int kPearOneBlock = 1024;
+constexpr int kPearKeep = 16;
+constexpr int64_t kPearOne = (int64_t)kPearOneBlock * kPearKeep;
+
+__device__ __forceinline__ void pearson_out(int64_t n, double mx, double my, const double (&v)[3],
+                                            double* __restrict__ out) {
+    const double nm1 = (double)(n - 1);
+    out[0] = mx;
+    out[1] = my;
+    out[2] = sqrt(v[0] / nm1);
+    out[3] = sqrt(v[1] / nm1);
+    out[4] = v[2] / sqrt(v[0] * v[1]);
+}
+
+__global__ __launch_bounds__(kPearOneBlock) void pearson_one_kernel(int64_t n, int64_t ld, const double* __restrict__ x,
+                                                                    const double* __restrict__ y,
+                                                                    double* __restrict__ out) {
+    __shared__ double sh[3][kPearOneBlock / 64];
+    const int c = blockIdx.x;
+    const double* xc = x + (int64_t)c * ld;
+    const double* yc = y + (int64_t)c * ld;
+    double xv[kPearKeep], yv[kPearKeep];
+#pragma unroll
+    for (int k = 0; k < kPearKeep; ++k) {
+        const int i = k * kPearOneBlock + threadIdx.x;
+        xv[k] = i < n ? xc[i] : 0.0;
+        yv[k] = i < n ? yc[i] : 0.0;
+    }
+    double m[2] = {0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < kPearKeep; ++k) {
+        m[0] += xv[k];
+        m[1] += yv[k];
+    }
+    block_sum<2, kPearOneBlock>(m, sh);
+    const double mx = m[0] / (double)n, my = m[1] / (double)n;
+    double v[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < kPearKeep; ++k) {
+        if (k * kPearOneBlock + (int)threadIdx.x < n) {
+            const double dx = xv[k] - mx, dy = yv[k] - my;
+            v[0] += dx * dx;
+            v[1] += dy * dy;
+            v[2] += dx * dy;
+        }
+    }
+    block_sum<3, kPearOneBlock>(v, sh);
+    if (threadIdx.x == 0) pearson_out(n, mx, my, v, out + c * 5);
+}
+
+__global__ __launch_bounds__(kPearBlock) void sums_kernel(int64_t n, int64_t ld, const double* __restrict__ x,
+                                                          const double* __restrict__ y, double* __restrict__ part) {
+    __shared__ double sh[2][kPearBlock / 64];
     const int c = blockIdx.y;
     const double* xc = x + (int64_t)c * ld;
     const double* yc = y + (int64_t)c * ld;
     double v[2] = {0.0, 0.0};
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)kPart * kBlock) {
+#pragma unroll 4
+    for (int64_t i = (int64_t)blockIdx.x * kPearBlock + threadIdx.x; i < n; i += (int64_t)kPearParts * kPearBlock) {
         v[0] += xc[i];
         v[1] += yc[i];
     }
-    block_sum<2>(v, sh);
-    if (threadIdx.x == 0) {
-        part[((int64_t)c * kPart + blockIdx.x) * 3 + 0] = v[0];
-        part[((int64_t)c * kPart + blockIdx.x) * 3 + 1] = v[1];
-    }
+    block_sum<2, kPearBlock>(v, sh);
+    if (threadIdx.x < 2) part[((int64_t)c * kPearParts + blockIdx.x) * 2 + threadIdx.x] = v[threadIdx.x];
 }
 
-__global__ __launch_bounds__(kBlock) void means_kernel(int64_t n, const double* __restrict__ part,
-                                                       double* __restrict__ mean) {
-    __shared__ double sh[2][kBlock];
-    const int c = blockIdx.x;
-    double v[2] = {0.0, 0.0};
-    for (int b = threadIdx.x; b < kPart; b += kBlock) {
-        v[0] += part[((int64_t)c * kPart + b) * 3 + 0];
-        v[1] += part[((int64_t)c * kPart + b) * 3 + 1];
-    }
-    block_sum<2>(v, sh);
-    if (threadIdx.x == 0) {
-        mean[c * 2 + 0] = v[0] / (double)n;
-        mean[c * 2 + 1] = v[1] / (double)n;
-    }
-}
-
-__global__ __launch_bounds__(kBlock) void centred_kernel(int64_t n, int64_t ld, const double* __restrict__ x,
-                                                         const double* __restrict__ y, const double* __restrict__ mean,
-                                                         double* __restrict__ part) {
-    __shared__ double sh[3][kBlock];
+__global__ __launch_bounds__(kPearBlock) void centred_kernel(int64_t n, int64_t ld, const double* __restrict__ x,
+                                                             const double* __restrict__ y,
+                                                             const double* __restrict__ part1,
+                                                             double* __restrict__ mean, double* __restrict__ part2) {
+    __shared__ double sh[3][kPearBlock / 64];
     const int c = blockIdx.y;
     const double* xc = x + (int64_t)c * ld;
     const double* yc = y + (int64_t)c * ld;
-    const double mx = mean[c * 2], my = mean[c * 2 + 1];
+    double m[2] = {0.0, 0.0};
+    if (threadIdx.x < kPearParts) {
+        m[0] = part1[((int64_t)c * kPearParts + threadIdx.x) * 2 + 0];
+        m[1] = part1[((int64_t)c * kPearParts + threadIdx.x) * 2 + 1];
+    }
+    block_sum<2, kPearBlock>(m, sh);
+    const double mx = m[0] / (double)n, my = m[1] / (double)n;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        mean[c * 2 + 0] = mx;
+        mean[c * 2 + 1] = my;
+    }
     double v[3] = {0.0, 0.0, 0.0};
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)kPart * kBlock) {
+#pragma unroll 4
+    for (int64_t i = (int64_t)blockIdx.x * kPearBlock + threadIdx.x; i < n; i += (int64_t)kPearParts * kPearBlock) {
         const double dx = xc[i] - mx, dy = yc[i] - my;
         v[0] += dx * dx;
         v[1] += dy * dy;
         v[2] += dx * dy;
     }
-    block_sum<3>(v, sh);
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int k = 0; k < 3; ++k) part[((int64_t)c * kPart + blockIdx.x) * 3 + k] = v[k];
-    }
+    block_sum<3, kPearBlock>(v, sh);
+    if (threadIdx.x < 3) part2[((int64_t)c * kPearParts + blockIdx.x) * 3 + threadIdx.x] = v[threadIdx.x];
 }
 
-__global__ __launch_bounds__(kBlock) void pearson_final_kernel(int64_t n, const double* __restrict__ part,
-                                                               const double* __restrict__ mean, double* __restrict__ out) {
-    __shared__ double sh[3][kBlock];
+__global__ __launch_bounds__(kPearParts) void pearson_final_kernel(int64_t n, const double* __restrict__ part2,
+                                                                   const double* __restrict__ mean,
+                                                                   double* __restrict__ out) {
+    __shared__ double sh[3][kPearParts / 64];
     const int c = blockIdx.x;
-    double v[3] = {0.0, 0.0, 0.0};
-    for (int b = threadIdx.x; b < kPart; b += kBlock) {
+    double v[3];
 #pragma unroll
-        for (int k = 0; k < 3; ++k) v[k] += part[((int64_t)c * kPart + b) * 3 + k];
-    }
-    block_sum<3>(v, sh);
-    if (threadIdx.x == 0) {
-        const double nm1 = (double)(n - 1);
-        out[c * 5 + 0] = mean[c * 2];
-        out[c * 5 + 1] = mean[c * 2 + 1];
-        out[c * 5 + 2] = sqrt(v[0] / nm1);
-        out[c * 5 + 3] = sqrt(v[1] / nm1);
-        out[c * 5 + 4] = v[2] / sqrt(v[0] * v[1]);
-    }
+    for (int k = 0; k < 3; ++k) v[k] = part2[((int64_t)c * kPearParts + threadIdx.x) * 3 + k];
+    block_sum<3, kPearParts>(v, sh);
+    if (threadIdx.x == 0) pearson_out(n, mean[c * 2], mean[c * 2 + 1], v, out + c * 5);
 }
 
 // ---------------------------------------------------------------------------
@@ -1031,12 +1077,17 @@ int pn_pearson(int64_t n, int64_t ld, const double* x, const double* y, int32_t 
         hipLaunchKernelGGL(fill_nan, dim3(1), dim3(kBlock), 0, s, out, (int)(ncomp * 5));
         return launched();
     }
-    double* part = (double*)workspace;
-    double* mean = part + (size_t)ncomp * kPart * 3;
-    hipLaunchKernelGGL(sums_kernel, dim3(kPart, ncomp), dim3(kBlock), 0, s, n, ld, x, y, part);
-    hipLaunchKernelGGL(means_kernel, dim3(ncomp), dim3(kBlock), 0, s, n, part, mean);
-    hipLaunchKernelGGL(centred_kernel, dim3(kPart, ncomp), dim3(kBlock), 0, s, n, ld, x, y, mean, part);
-    hipLaunchKernelGGL(pearson_final_kernel, dim3(ncomp), dim3(kBlock), 0, s, n, part, mean, out);
+    if (n <= kPearOne) {
+        hipLaunchKernelGGL(pearson_one_kernel, dim3(ncomp), dim3(kPearOneBlock), 0, s, n, ld, x, y, out);
+        return launched();
+    }
+    static_assert(kPearParts * 5 <= kPart * 3, "the partial sums fit the workspace");
+    double* part2 = (double*)workspace;
+    double* part1 = part2 + (size_t)ncomp * kPearParts * 3;
+    double* mean = part1 + (size_t)ncomp * kPearParts * 2;
+    hipLaunchKernelGGL(sums_kernel, dim3(kPearParts, ncomp), dim3(kPearBlock), 0, s, n, ld, x, y, part1);
+    hipLaunchKernelGGL(centred_kernel, dim3(kPearParts, ncomp), dim3(kPearBlock), 0, s, n, ld, x, y, part1, mean, part2);
+    hipLaunchKernelGGL(pearson_final_kernel, dim3(ncomp), dim3(kPearParts), 0, s, n, part2, mean, out);
     return launched();
 }
 

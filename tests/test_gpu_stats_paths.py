@@ -189,3 +189,31 @@ def test_histogram_bins_near_the_rounding_of_the_edges():
     lo, hi, nbins = 1e10, 1e10 + 1e-4, 20
     x = np.random.default_rng(4).uniform(lo, hi, (1, 20000))
     assert (_api().pn_histogram(_cuda(x), nbins, lo, hi).cpu().numpy()[0] == S.histogram(x[0], lo, hi, nbins)).all()
+
+
+# one block, the first size of two passes, and sizes around the blocks of a pass;
+# a large common offset, which one pass of raw moments would lose.  Bounds: the
+# sums of n terms in trees of depth about log2 n + 16, so 64 eps of the sum of
+# magnitudes, which for the centred sums is the sum itself; the mean's error
+# enters the centred sums squared.
+@pytest.mark.parametrize("n", [2, 63, 1024, 16383, 16384, 16385, 131072, 131073, 300001])
+def test_pearson_blocks(n):
+    rng = np.random.default_rng(n)
+    x = rng.normal(0.0, 1.0, (3, n)) + np.array([[0.0], [1e3], [-7.0]])
+    y = 0.6 * x + rng.normal(0.0, 0.8, (3, n))
+    wide = torch.zeros((6, n + 5), dtype=torch.float64, device="cuda")
+    wide[:3, :n], wide[3:, :n] = _cuda(x), _cuda(y)
+    got = _api().pn_pearson(wide[:3, :n], wide[3:, :n]).cpu().numpy()
+    eps = 2.0 ** -52
+    for c in range(3):
+        xl, yl = x[c].astype(np.longdouble), y[c].astype(np.longdouble)
+        mx, my = xl.mean(), yl.mean()
+        sx, sy = ((xl - mx) ** 2).sum(), ((yl - my) ** 2).sum()
+        r = ((xl - mx) * (yl - my)).sum() / np.sqrt(sx * sy)
+        scale = np.abs(x[c]).max() + np.abs(y[c]).max()      # a centred value's rounding: eps of this
+        slack = 64 * eps + 4 * eps * scale / min(np.sqrt(sx / n), np.sqrt(sy / n))
+        assert abs(got[c, 0] - mx) <= 64 * eps * np.abs(x[c]).mean()
+        assert abs(got[c, 1] - my) <= 64 * eps * np.abs(y[c]).mean()
+        assert abs(got[c, 2] / np.sqrt(sx / (n - 1)) - 1) <= slack
+        assert abs(got[c, 3] / np.sqrt(sy / (n - 1)) - 1) <= slack
+        assert abs(got[c, 4] - r) <= slack
