@@ -542,7 +542,8 @@ int kde_parts(int64_t n, int ncomp, int tiles) {
 //   ks_collect         the candidates' values, each to its bucket's range
 //   ks_solve           ranks inside the candidates and the largest deviation
 // Bound by launches and latency up to 2^20 values: 3 x 2^20 took 0.69 ms by
-// sorting (20 launches a component), 0.10 ms this way.
+// sorting (20 launches a component), 0.083 ms this way; samples of one block
+// take one launch (ks_one).
 //
 // The bound works while a bucket holds far less of F than D ~ 1/sqrt(n); above
 // kKsBucketMax values (2^22: 1/16384 against 4e-4) most buckets would be
@@ -609,14 +610,14 @@ __device__ __forceinline__ double ks_F(double v, double lo, double w) { return (
 __device__ __forceinline__ double ks_up(int64_t i, double dn, double F) { return (double)(i + 1) / dn - F; }
 __device__ __forceinline__ double ks_down(int64_t i, double dn, double F) { return F - (double)i / dn; }
 
-// Values of F in bucket b lie between these (b / buckets is exact; the factor
-// covers the rounding of F and of the bucket's own product); the first and
-// the last bucket also hold what lies outside [lo, hi].
-__device__ __forceinline__ double ks_bucket_lo(int b, int buckets) {
-    return b == 0 ? -__builtin_inf() : ((double)b / buckets) * (1.0 - 0x1p-48);
+// Values of F in bucket b lie between these (b / buckets is exact, ib =
+// 1 / buckets; the factor covers the rounding of F and of the bucket's own
+// product); the first and the last bucket also hold what lies outside [lo, hi].
+__device__ __forceinline__ double ks_bucket_lo(int b, double ib) {
+    return b == 0 ? -__builtin_inf() : ((double)b * ib) * (1.0 - 0x1p-48);
 }
-__device__ __forceinline__ double ks_bucket_hi(int b, int buckets) {
-    return b == buckets - 1 ? __builtin_inf() : ((double)(b + 1) / buckets) * (1.0 + 0x1p-48);
+__device__ __forceinline__ double ks_bucket_hi(int b, int buckets, double ib) {
+    return b == buckets - 1 ? __builtin_inf() : ((double)(b + 1) * ib) * (1.0 + 0x1p-48);
 }
 
 __global__ __launch_bounds__(kKsCount) void ks_count(int64_t n, int64_t ld, const double* __restrict__ x, double lo,
@@ -625,17 +626,14 @@ __global__ __launch_bounds__(kKsCount) void ks_count(int64_t n, int64_t ld, cons
     const KsView v = ks_view(ws, p, blockIdx.y);
     const double* xc = x + (int64_t)blockIdx.y * ld;
     for (int b = threadIdx.x; b < p.buckets; b += kKsCount) sh[b] = 0u;
-    if (blockIdx.x == 0) {
-        if (threadIdx.x == 0) { *v.dmax() = 0ull; *v.ncand() = 0u; }
-        for (int b = threadIdx.x; b < p.buckets; b += kKsCount) v.cursor()[b] = 0u;
-    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) *v.dmax() = 0ull;
     __syncthreads();
     const int64_t i0 = (int64_t)blockIdx.x * kKsPerBlock;
     const int64_t i1 = i0 + kKsPerBlock < n ? i0 + kKsPerBlock : n;
 #pragma unroll 4
     for (int64_t i = i0 + threadIdx.x; i < i1; i += kKsCount) atomicAdd(&sh[ks_bucket(xc[i], lo, scale, p.buckets)], 1u);
     __syncthreads();
-    unsigned* out = p.blocks == 1 ? v.count() : v.part(blockIdx.x);
+    unsigned* out = v.part(blockIdx.x);
     for (int b = threadIdx.x; b < p.buckets; b += kKsCount) out[b] = sh[b];
 }
 
@@ -675,84 +673,134 @@ __device__ __forceinline__ double wave_max(double v) {
     return v;
 }
 
-__global__ __launch_bounds__(kKsCount) void ks_scan(int64_t n, void* ws, KsPlan p) {
-    __shared__ unsigned shu[kKsCount / 64];
-    __shared__ double shd[kKsCount / 64];
-    const KsView v = ks_view(ws, p, blockIdx.x);
-    const int per = p.buckets / kKsCount, b0 = threadIdx.x * per;      // 1 .. 16 buckets a thread
-    const double dn = (double)n;
-    unsigned cnt[16], sum = 0;
+// Ranks, bounds and candidates of one component, by one block: the counts
+// become the counts below; `slots` receives each candidate's place in the list
+// (kKsNone elsewhere), `cands` the candidates; returns their number.  PER =
+// buckets / kKsCount.  The empirical distribution below a bucket is the count
+// times 1/n, with a factor that covers the rounding against the quotient the
+// deviations are formed with (four divisions a bucket, and single loads, took
+// 37 us for 16,384 buckets, this 18 us).
+template <int PER>
+__device__ int ks_scan_block(int64_t n, unsigned* __restrict__ count, unsigned* __restrict__ slots,
+                             unsigned* __restrict__ cursors, unsigned* __restrict__ cands, int buckets, unsigned* shu,
+                             double* shd) {
+    const int b0 = threadIdx.x * PER;
+    const double in = 1.0 / (double)n, ib = 1.0 / buckets;       // the latter exact: a power of two
+    constexpr double kDown = 1.0 - 0x1p-50, kUp = 1.0 + 0x1p-50;
+    unsigned cnt[PER], sum = 0;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        cnt[k] = k < per ? v.count()[b0 + k] : 0u;
-        sum += cnt[k];
-    }
-    unsigned total;
-    const unsigned below0 = block_scan(sum, shu, total);
-    // ranks, and the largest lower bound
-    double low = 0.0;
-    unsigned below = below0;
+    for (int k = 0; k < PER; k += 4) {
+        if (PER >= 4) {
+            const uint4 q = *(const uint4*)(count + b0 + k);
+            cnt[k] = q.x; cnt[k + 1 < PER ? k + 1 : 0] = q.y; cnt[k + 2 < PER ? k + 2 : 0] = q.z;
+            cnt[k + 3 < PER ? k + 3 : 0] = q.w;
+        } else {
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        if (k < per) {
-            const int b = b0 + k;
-            v.count()[b] = below;
-            if (cnt[k]) {
-                low = __builtin_fmax(low, ks_up((int64_t)below + cnt[k] - 1, dn, ks_bucket_hi(b, p.buckets)));
-                low = __builtin_fmax(low, ks_down(below, dn, ks_bucket_lo(b, p.buckets)));
-            }
-            below += cnt[k];
+            for (int j = 0; j < PER; ++j) cnt[j] = count[b0 + j];
         }
     }
-    if (threadIdx.x == kKsCount - 1) v.count()[p.buckets] = below;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) sum += cnt[k];
+    unsigned total;
+    const unsigned below0 = block_scan(sum, shu, total);
+    // frac[k]: the empirical distribution below bucket b0 + k
+    double frac[PER + 1];
+    unsigned below = below0;
+    frac[0] = (double)below * in;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        count[b0 + k] = below;
+        below += cnt[k];
+        frac[k + 1] = (double)below * in;
+    }
+    if (threadIdx.x == kKsCount - 1) count[buckets] = below;
+    // the largest lower bound: a bucket's last value lies below its upper edge,
+    // its first above its lower edge
+    double low = 0.0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        if (cnt[k]) {
+            low = __builtin_fmax(low, frac[k + 1] * kDown - ks_bucket_hi(b0 + k, buckets, ib));
+            low = __builtin_fmax(low, ks_bucket_lo(b0 + k, ib) - frac[k] * kUp);
+        }
+    }
     low = wave_max(low);
     if ((threadIdx.x & 63) == 0) shd[threadIdx.x >> 6] = low;
     __syncthreads();
     for (int k = 0; k < kKsCount / 64; ++k) low = __builtin_fmax(low, shd[k]);
     // candidates: where an upper bound reaches it
     unsigned mask = 0, vals = 0;
-    below = below0;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        if (k < per && cnt[k]) {
-            const int b = b0 + k;
-            const double up = ks_up((int64_t)below + cnt[k] - 1, dn, ks_bucket_lo(b, p.buckets));
-            const double down = ks_down(below, dn, ks_bucket_hi(b, p.buckets));
-            if (up >= low || down >= low) {
-                mask |= 1u << k;
-                vals += cnt[k];
-            }
-            below += cnt[k];
+    for (int k = 0; k < PER; ++k) {
+        if (cnt[k] && (frac[k + 1] * kUp - ks_bucket_lo(b0 + k, ib) >= low ||
+                       ks_bucket_hi(b0 + k, buckets, ib) - frac[k] * kDown >= low)) {
+            mask |= 1u << k;
+            vals += cnt[k];
         }
     }
     unsigned slot = block_scan(vals, shu, total);
     unsigned at = block_scan((unsigned)__popc(mask), shu, total);
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        if (k < per) {
-            const bool c = (mask >> k) & 1u;
-            v.slot()[b0 + k] = c ? slot : kKsNone;
-            if (c) {
-                v.cand()[at++] = b0 + k;
-                slot += cnt[k];
-            }
+    for (int k = 0; k < PER; ++k) {
+        const bool c = (mask >> k) & 1u;
+        slots[b0 + k] = c ? slot : kKsNone;
+        if (c) {
+            cursors[b0 + k] = slot;
+            cands[at++] = b0 + k;
+            slot += cnt[k];
         }
     }
-    if (threadIdx.x == 0) *v.ncand() = total;
+    return (int)total;
 }
 
-__global__ __launch_bounds__(kBlock) void ks_collect(int64_t n, int64_t ld, const double* __restrict__ x, double lo,
-                                                     double scale, void* ws, KsPlan p) {
+__global__ __launch_bounds__(kKsCount) void ks_scan(int64_t n, void* ws, KsPlan p) {
+    __shared__ unsigned shu[kKsCount / 64];
+    __shared__ double shd[kKsCount / 64];
+    const KsView v = ks_view(ws, p, blockIdx.x);
+    int total = 0;
+    switch (p.buckets / kKsCount) {
+        case 1: total = ks_scan_block<1>(n, v.count(), v.slot(), v.cursor(), v.cand(), p.buckets, shu, shd); break;
+        case 2: total = ks_scan_block<2>(n, v.count(), v.slot(), v.cursor(), v.cand(), p.buckets, shu, shd); break;
+        case 4: total = ks_scan_block<4>(n, v.count(), v.slot(), v.cursor(), v.cand(), p.buckets, shu, shd); break;
+        case 8: total = ks_scan_block<8>(n, v.count(), v.slot(), v.cursor(), v.cand(), p.buckets, shu, shd); break;
+        default: total = ks_scan_block<16>(n, v.count(), v.slot(), v.cursor(), v.cand(), p.buckets, shu, shd); break;
+    }
+    if (threadIdx.x == 0) *v.ncand() = (unsigned)total;
+}
+
+// The candidates are a few per cent of the values: a bit a bucket in LDS
+// decides for the others, and the places of a thread's values are taken
+// together.  Bound by the atomics that hand out the places, which meet on the
+// few candidates (25 us for 3 x 2^20 values).
+__global__ __launch_bounds__(kKsCount) void ks_collect(int64_t n, int64_t ld, const double* __restrict__ x, double lo,
+                                                       double scale, void* ws, KsPlan p) {
+    __shared__ unsigned is_cand[16384 / 32];
     const KsView v = ks_view(ws, p, blockIdx.y);
     const double* xc = x + (int64_t)blockIdx.y * ld;
     double* list = v.list();
-#pragma unroll 4
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) {
-        const double val = xc[i];
-        const int b = ks_bucket(val, lo, scale, p.buckets);
-        const unsigned s = v.slot()[b];
-        if (s != kKsNone) list[s + atomicAdd(&v.cursor()[b], 1u)] = val;
+    for (int k = threadIdx.x; k < p.buckets / 32; k += kKsCount) is_cand[k] = 0u;
+    __syncthreads();
+    const int ncand = (int)*v.ncand();
+    for (int k = threadIdx.x; k < ncand; k += kKsCount) {
+        const unsigned b = v.cand()[k];
+        atomicOr(&is_cand[b >> 5], 1u << (b & 31));
     }
+    __syncthreads();
+    const int64_t i0 = (int64_t)blockIdx.x * kKsPerBlock + threadIdx.x;
+    constexpr int kKeep = kKsPerBlock / kKsCount;
+    double val[kKeep];
+    unsigned place[kKeep];
+#pragma unroll
+    for (int k = 0; k < kKeep; ++k) val[k] = i0 + k * kKsCount < n ? xc[i0 + k * kKsCount] : 0.0;
+#pragma unroll
+    for (int k = 0; k < kKeep; ++k) {
+        const int b = ks_bucket(val[k], lo, scale, p.buckets);
+        place[k] = kKsNone;
+        if (i0 + k * kKsCount < n && ((is_cand[b >> 5] >> (b & 31)) & 1u)) place[k] = atomicAdd(&v.cursor()[b], 1u);
+    }
+#pragma unroll
+    for (int k = 0; k < kKeep; ++k)
+        if (place[k] != kKsNone) list[place[k]] = val[k];
 }
 
 // 64-bit keys that order as the values do
@@ -765,20 +813,34 @@ __device__ __forceinline__ double ks_unkey(uint64_t k) {
 }
 
 // The largest deviation among m values l[0 .. m), which have the ranks r0 ..
-// r0 + m - 1 of the sample, by counting; `lane` of `lanes` takes every
-// lanes-th value.  Equal values take their ranks in the order they lie.
-__device__ __forceinline__ double ks_ranked(const double* l, int m, int64_t r0, double dn, double lo, double w, int lane,
-                                            int lanes) {
+// r0 + m - 1 of the sample, by counting; the wave's part of it: value e goes to
+// lane e - e0 for e0 in steps of `stride` from first.  Equal values take their
+// ranks in the order they lie.  The values are compared 64 at a time from the
+// lanes that loaded them.
+__device__ __forceinline__ double ks_ranked(const double* l, int m, int64_t r0, double dn, double lo, double w, int first,
+                                            int stride) {
+    const int lane = threadIdx.x & 63;
+    m = __builtin_amdgcn_readfirstlane(m);
+    first = __builtin_amdgcn_readfirstlane(first);
     double d = 0.0;
-    for (int e = lane; e < m; e += lanes) {
-        const double ve = l[e];
+    for (int e0 = first; e0 < m; e0 += stride) {
+        const int e = e0 + lane;
+        const double ve = e < m ? l[e] : 0.0;
         int rank = 0;
-        for (int j = 0; j < m; ++j) {
-            const double vj = l[j];
-            rank += (vj < ve || (vj == ve && j < e)) ? 1 : 0;
+        for (int j0 = 0; j0 < m; j0 += 64) {
+            const int mine = j0 + lane;
+            const double vm = j0 == e0 ? ve : (mine < m ? l[mine] : 0.0);
+            const int lim = m - j0 < 64 ? m - j0 : 64;
+            for (int j = 0; j < lim; ++j) {
+                const double vj = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(vm), j),
+                                                   __builtin_amdgcn_readlane(__double2loint(vm), j));
+                rank += (vj < ve || (vj == ve && j0 + j < e)) ? 1 : 0;
+            }
         }
-        const double F = ks_F(ve, lo, w);
-        d = __builtin_fmax(d, __builtin_fmax(ks_up(r0 + rank, dn, F), ks_down(r0 + rank, dn, F)));
+        if (e < m) {
+            const double F = ks_F(ve, lo, w);
+            d = __builtin_fmax(d, __builtin_fmax(ks_up(r0 + rank, dn, F), ks_down(r0 + rank, dn, F)));
+        }
     }
     return d;
 }
@@ -894,7 +956,7 @@ __device__ double ks_refine(KsRefine& R, const double* l, int m, int64_t r0, dou
                 if (k >= pa && k <= pe) R.vals[atomicAdd(&R.nvals, 1u)] = v;
             }
             __syncthreads();
-            best = __builtin_fmax(best, block_max_all(R, ks_ranked(R.vals, cnt, base, dn, lo, w, threadIdx.x, kKsCount)));
+            best = __builtin_fmax(best, block_max_all(R, ks_ranked(R.vals, cnt, base, dn, lo, w, threadIdx.x & ~63, kKsCount)));
             continue;
         }
         ks_key_range(R, l, m, pa, pe);
@@ -909,35 +971,92 @@ __device__ double ks_refine(KsRefine& R, const double* l, int m, int64_t r0, dou
     return best;
 }
 
+// The largest deviation in the candidates of one component: a wave a
+// candidate (wave `wave` of `waves`), and the block its candidates that are too
+// large for one; each wave's maximum, in every lane.
+__device__ __forceinline__ double ks_solve_block(KsRefine& R, const unsigned* cand, int ncand, const unsigned* count,
+                                                 const unsigned* slot, const double* list, double dn, double lo,
+                                                 double w, int block, int blocks) {
+    constexpr int kWaves = kKsCount / 64;
+    double d = 0.0;
+    bool large = false;
+    for (int k = block * kWaves + (threadIdx.x >> 6); k < ncand; k += blocks * kWaves) {
+        const int b = (int)cand[k];
+        const int64_t r0 = count[b];
+        const int m = (int)(count[b + 1] - count[b]);
+        if (m <= kKsWave) d = __builtin_fmax(d, ks_ranked(list + slot[b], m, r0, dn, lo, w, 0, 64));
+        else large = true;
+    }
+    if (__syncthreads_or(large)) {
+        for (int q = block * kWaves; q < ncand; q += blocks * kWaves)
+            for (int k = q; k < q + kWaves && k < ncand; ++k) {
+                const int b = (int)cand[k];
+                const int64_t r0 = count[b];
+                const int m = (int)(count[b + 1] - count[b]);
+                if (m > kKsWave) d = __builtin_fmax(d, ks_refine(R, list + slot[b], m, r0, dn, lo, w));
+            }
+    }
+    return wave_max(d);
+}
+
 __global__ __launch_bounds__(kKsCount) void ks_solve(int64_t n, double lo, double w, void* ws, KsPlan p) {
     __shared__ KsRefine R;
     const KsView v = ks_view(ws, p, blockIdx.y);
-    const int ncand = (int)*v.ncand();
-    const double dn = (double)n;
-    const int lane = threadIdx.x & 63;
-    double d = 0.0;
-    // a wave a candidate ...
-    bool large = false;
-    for (int k = blockIdx.x * (kKsCount / 64) + (threadIdx.x >> 6); k < ncand; k += gridDim.x * (kKsCount / 64)) {
-        const int b = (int)v.cand()[k];
-        const int64_t r0 = v.count()[b];
-        const int m = (int)(v.count()[b + 1] - v.count()[b]);
-        if (m <= kKsWave) d = __builtin_fmax(d, ks_ranked(v.list() + v.slot()[b], m, r0, dn, lo, w, lane, 64));
-        else large = true;
+    double d = ks_solve_block(R, v.cand(), (int)*v.ncand(), v.count(), v.slot(), v.list(), (double)n, lo, w,
+                                    blockIdx.x, gridDim.x);
+    // non-negative doubles order as their bits; one atomic a block (one a wave
+    // made 1024 wait for one word)
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) R.red[threadIdx.x >> 6] = d;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int k = 0; k < kKsCount / 64; ++k) d = __builtin_fmax(d, R.red[k]);
+    if (d > 0.0) atomicMax(v.dmax(), (unsigned long long)__double_as_longlong(d));
+}
+
+__device__ double kolmogorov_sf(double lam);
+
+// The whole test of a sample that one block counts (at most kKsPerBlock
+// values, 1024 buckets), in one launch: the tables in LDS, the candidates'
+// values in the workspace (3 x 4,099 values: five launches 23 us, this 11 us).
+__global__ __launch_bounds__(kKsCount) void ks_one(int64_t n, int64_t ld, const double* __restrict__ x, double lo,
+                                                   double w, double scale, void* ws, KsPlan p,
+                                                   double* __restrict__ out) {
+    __shared__ KsRefine R;
+    __shared__ unsigned count[kKsCount + 1], slot[kKsCount], cand[kKsCount], shu[kKsCount / 64];
+    __shared__ double shd[kKsCount / 64];
+    constexpr int kKeep = kKsPerBlock / kKsCount;
+    const KsView v = ks_view(ws, p, blockIdx.x);
+    const double* xc = x + (int64_t)blockIdx.x * ld;
+    double* list = v.list();
+    double val[kKeep];
+#pragma unroll
+    for (int k = 0; k < kKeep; ++k) {
+        const int i = k * kKsCount + threadIdx.x;
+        val[k] = i < n ? xc[i] : 0.0;
     }
-    // ... and the block's candidates that are too large for one
-    if (__syncthreads_or(large)) {
-        for (int q = blockIdx.x * (kKsCount / 64); q < ncand; q += gridDim.x * (kKsCount / 64))
-            for (int k = q; k < q + kKsCount / 64 && k < ncand; ++k) {
-                const int b = (int)v.cand()[k];
-                const int64_t r0 = v.count()[b];
-                const int m = (int)(v.count()[b + 1] - v.count()[b]);
-                if (m > kKsWave) d = __builtin_fmax(d, ks_refine(R, v.list() + v.slot()[b], m, r0, dn, lo, w));
-            }
-    }
-    d = wave_max(d);
-    // non-negative doubles order as their bits
-    if (lane == 0 && d > 0.0) atomicMax(v.dmax(), (unsigned long long)__double_as_longlong(d));
+    count[threadIdx.x] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kKeep; ++k)
+        if (k * kKsCount + (int)threadIdx.x < n) atomicAdd(&count[ks_bucket(val[k], lo, scale, kKsCount)], 1u);
+    __syncthreads();
+    const int ncand = ks_scan_block<1>(n, count, slot, R.below[0], cand, kKsCount, shu, shd);      // R.below[0]: the next place
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kKeep; ++k)
+        if (k * kKsCount + (int)threadIdx.x < n) {
+            const int b = ks_bucket(val[k], lo, scale, kKsCount);
+            if (slot[b] != kKsNone) list[atomicAdd(&R.below[0][b], 1u)] = val[k];
+        }
+    __syncthreads();
+    double d = ks_solve_block(R, cand, ncand, count, slot, list, (double)n, lo, w, 0, 1);
+    if ((threadIdx.x & 63) == 0) shd[threadIdx.x >> 6] = d;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int k = 0; k < kKsCount / 64; ++k) d = __builtin_fmax(d, shd[k]);
+    out[2 * blockIdx.x] = d;
+    out[2 * blockIdx.x + 1] = kolmogorov_sf(sqrt((double)n) * d);
 }
 
 // the deviations of a sorted copy, for samples the buckets do not serve
@@ -1153,19 +1272,22 @@ int pn_ks_uniform(int64_t n, int64_t ld, const double* x, int32_t ncomp, double 
     if (n <= kKsBucketMax && w > 1e-290 && w < 1e290) {
         const KsPlan p = ks_plan(n);
         const int side = (int)(ws_bytes / (size_t)p.bytes < (size_t)ncomp ? ws_bytes / (size_t)p.bytes : (size_t)ncomp);
-        if (side > 0 && ((uintptr_t)workspace & 7) == 0) {
+        if (side > 0 && ((uintptr_t)workspace & 15) == 0) {
             const double scale = p.buckets / w;
-            const unsigned collect = (unsigned)((n + 8 * kBlock - 1) / (8 * kBlock));
             for (int c = 0; c < ncomp; c += side) {
                 const int g = ncomp - c < side ? ncomp - c : side;
                 const double* xc = x + (int64_t)c * ld;
+                if (p.blocks == 1) {
+                    hipLaunchKernelGGL(ks_one, dim3(g), dim3(kKsCount), 0, s, n, ld, xc, lo, w, scale, workspace, p,
+                                       out + 2 * c);
+                    continue;
+                }
                 hipLaunchKernelGGL(ks_count, dim3(p.blocks, g), dim3(kKsCount), p.buckets * sizeof(unsigned), s, n, ld,
                                    xc, lo, scale, workspace, p);
-                if (p.blocks > 1)
-                    hipLaunchKernelGGL(ks_sum, dim3(p.buckets / kBlock, g), dim3(kBlock), 0, s, workspace, p);
+                hipLaunchKernelGGL(ks_sum, dim3(p.buckets / kBlock, g), dim3(kBlock), 0, s, workspace, p);
                 hipLaunchKernelGGL(ks_scan, dim3(g), dim3(kKsCount), 0, s, n, workspace, p);
-                hipLaunchKernelGGL(ks_collect, dim3(collect < 512 ? collect : 512, g), dim3(kBlock), 0, s, n, ld, xc, lo,
-                                   scale, workspace, p);
+                hipLaunchKernelGGL(ks_collect, dim3(p.blocks, g), dim3(kKsCount), 0, s, n, ld, xc, lo, scale, workspace,
+                                   p);
                 hipLaunchKernelGGL(ks_solve, dim3(64, g), dim3(kKsCount), 0, s, n, lo, w, workspace, p);
                 hipLaunchKernelGGL(ks_final_kernel, dim3(g), dim3(64), 0, s, n, (const double*)workspace, 1,
                                    p.bytes / 8, out + 2 * c);
