@@ -404,8 +404,10 @@ int pn_integrate_record(int64_t n, int64_t ld,
  *   m, tape, cap_steps, ckpt_every, status: the inputs and outputs of the
  *     pn_integrate_record call (same masses, same opt->terms/theta_literal);
  *   gy_final [10][ld], gt_final [ld] (may be NULL = 0);
- *   workspace: device buffer of at least pn_adjoint_workspace_bytes(n, K)
- *     bytes (the replayed states of one checkpoint segment per inspiral);
+ *   workspace: device buffer of pn_adjoint_workspace_bytes(n, K) bytes: the
+ *     replayed states of one checkpoint segment per inspiral (11 n K doubles,
+ *     which is also enough), and, for small n, of several parts of each
+ *     inspiral that are then reversed side by side;
  *   order: optional device permutation of [0, n) giving the order in which
  *     inspirals are assigned to lanes (e.g. sorted by step count, so that a
  *     wave's lanes run segments of equal length); NULL = identity.  Entries
