@@ -32,9 +32,8 @@ __device__ __forceinline__ void rhs_vjp(const Row& r, const TermConsts& tc, cons
     // ---------------- primal ----------------
     const double w = y[0];
     const double M = r[R_M];
-    const double v = M * w;
     double x, lnv;
-    stage_x_lnv(lb, v, w, x, lnv);
+    stage_x_lnv(lb, M, w, x, lnv);
     const double x2 = x * x;
     const double L0 = y[7], L1 = y[8], L2 = y[9];
     const double a0 = y[1], a1 = y[2], a2 = y[3];
@@ -52,15 +51,11 @@ __device__ __forceinline__ void rhs_vjp(const Row& r, const TermConsts& tc, cons
     const double B2 = __builtin_fma(x, B3, c3p);
     const double B1 = __builtin_fma(x, B2, r[R_C2]);
     const double B = __builtin_fma(x2, B1, 1.0);
-    const double x4 = x2 * x2;
-    const double x5 = x4 * x;
-    const double Kw2 = r[R_K] * (w * w);
-    const double f0 = Kw2 * x5 * B;
-    const double p = 0.5 * w;
-    const double sv = r[R_SIGM] * w;
-    const double A1 = __builtin_fma(r[R_G1], x2, -3.0 * sv * LS2);
-    const double A2 = __builtin_fma(r[R_G2], x2, -3.0 * sv * LS1);
-    const double al1 = p * A1, al2 = p * A2, be = p * sv;
+    const double ww = w * w, wx2 = w * x2;
+    const double Kww = r[R_K] * ww;
+    const double f0 = Kww * wx2 * B;
+    const double be = r[R_SIGM] * ww, m3be = -3.0 * be;
+    const double al1 = __builtin_fma(r[R_G1], wx2, m3be * LS2), al2 = __builtin_fma(r[R_G2], wx2, m3be * LS1);
     const double q = -r[R_LAM] * x;
 
     // ---------------- seed fbar ----------------
@@ -155,29 +150,26 @@ __device__ __forceinline__ void rhs_vjp(const Row& r, const TermConsts& tc, cons
     bb0 += __builtin_fma(wb1, L2, -wb2 * L1);
     bb1 += __builtin_fma(wb2, L0, -wb0 * L2);
     bb2 += __builtin_fma(wb0, L1, -wb1 * L0);
-    // be = p sv ; al1 = p A1 ; al2 = p A2
-    double pbar = __builtin_fma(sv, beb, __builtin_fma(A1, al1b, A2 * al2b));
-    double svbar = p * beb;
-    const double A1b = p * al1b, A2b = p * al2b;
-    // A1 = g1 x2 - 3 sv LS2 ; A2 = g2 x2 - 3 sv LS1
-    rb.v[R_G1] = __builtin_fma(x2, A1b, rb.v[R_G1]);
-    rb.v[R_G2] = __builtin_fma(x2, A2b, rb.v[R_G2]);
-    double x2bar = __builtin_fma(r[R_G1], A1b, r[R_G2] * A2b);
-    svbar = __builtin_fma(-3.0 * LS2, A1b, __builtin_fma(-3.0 * LS1, A2b, svbar));
-    double LS2bar = -3.0 * sv * A1b;
-    double LS1bar = -3.0 * sv * A2b;
-    // sv = sigM w ; p = w/2
-    rb.v[R_SIGM] = __builtin_fma(w, svbar, rb.v[R_SIGM]);
-    double wbar = __builtin_fma(r[R_SIGM], svbar, 0.5 * pbar);
-    // f0 = K w^2 x5 B
+    // al1 = g1 wx2 - 3 be LS2 ; al2 = g2 wx2 - 3 be LS1
+    rb.v[R_G1] = __builtin_fma(wx2, al1b, rb.v[R_G1]);
+    rb.v[R_G2] = __builtin_fma(wx2, al2b, rb.v[R_G2]);
+    double wx2bar = __builtin_fma(r[R_G1], al1b, r[R_G2] * al2b);
+    double LS2bar = m3be * al1b;
+    double LS1bar = m3be * al2b;
+    // be = sigM ww
+    const double bebar = __builtin_fma(-3.0, __builtin_fma(LS2, al1b, LS1 * al2b), beb);
+    rb.v[R_SIGM] = __builtin_fma(ww, bebar, rb.v[R_SIGM]);
+    // f0 = K ww wx2 B
     const double f0b = fb[0];
-    rb.v[R_K] = __builtin_fma((w * w) * x5 * B, f0b, rb.v[R_K]);
-    wbar = __builtin_fma(2.0 * r[R_K] * w * x5 * B, f0b, wbar);
-    const double x5bar = Kw2 * B * f0b;
-    const double Bbar = Kw2 * x5 * f0b;
-    // x5 = x4 x, x4 = x2^2
-    x2bar = __builtin_fma(2.0 * x2 * x, x5bar, x2bar);
-    xbar = __builtin_fma(x4, x5bar, xbar);
+    const double wB = wx2 * B;
+    rb.v[R_K] = __builtin_fma(ww * wB, f0b, rb.v[R_K]);
+    const double wwbar = __builtin_fma(r[R_K] * wB, f0b, r[R_SIGM] * bebar);
+    const double Kf = Kww * f0b;
+    wx2bar = __builtin_fma(Kf, B, wx2bar);
+    const double Bbar = Kf * wx2;
+    // wx2 = w x2, ww = w w
+    double wbar = __builtin_fma(x2, wx2bar, 2.0 * w * wwbar);
+    double x2bar = w * wx2bar;
     // B = 1 + x2 B1
     x2bar = __builtin_fma(B1, Bbar, x2bar);
     const double B1b = x2 * Bbar;
@@ -226,6 +218,7 @@ __device__ __forceinline__ void rhs_vjp(const Row& r, const TermConsts& tc, cons
     xbar = __builtin_fma(2.0 * x, x2bar, xbar);
     // d lnv/dv = 1/v, dx/dv = 1/(3 x^2) = x/(3 v): one reciprocal of v
     // (hardware seed and two Newton steps; valid for either sign)
+    const double v = M * w;
     const double rv = rcp_pos(v);
     const double vbar = rv * __builtin_fma(xbar, x * (1.0 / 3.0), lnvbar);
     rb.v[R_M] = __builtin_fma(w, vbar, rb.v[R_M]);
@@ -295,10 +288,10 @@ __device__ __forceinline__ void make_row_dual(RowDual& r, Dl m1, Dl m2, int term
     r.set(R_C6, pn * (c6c + (-273811877.0 / 1088640.0 + (451.0 / 48.0) * PN_PI * PN_PI - theta_term) * eta
                       + (541.0 / 896.0) * eta * eta - (5605.0 / 2592.0) * eta * eta * eta));
     r.set(R_C7, pn * ((-4415.0 / 4032.0 + (358675.0 / 6048.0) * eta + (91495.0 / 1512.0) * eta * eta) * PN_PI));
-    r.set(R_K, (terms & PN_TERM_RR) ? (96.0 / 5.0) * eta : Dl(0.0));
-    r.set(R_G1, (terms & PN_TERM_SO_PREC) ? eta * (4.0 + 3.0 * m2 / m1) : Dl(0.0));
-    r.set(R_G2, (terms & PN_TERM_SO_PREC) ? eta * (4.0 + 3.0 * m1 / m2) : Dl(0.0));
-    r.set(R_SIGM, (terms & PN_TERM_SS_PREC) ? iM : Dl(0.0));
+    r.set(R_K, (terms & PN_TERM_RR) ? (96.0 / 5.0) * eta * M : Dl(0.0));
+    r.set(R_G1, (terms & PN_TERM_SO_PREC) ? 0.5 * (eta * (4.0 + 3.0 * m2 / m1)) : Dl(0.0));
+    r.set(R_G2, (terms & PN_TERM_SO_PREC) ? 0.5 * (eta * (4.0 + 3.0 * m1 / m2)) : Dl(0.0));
+    r.set(R_SIGM, (terms & PN_TERM_SS_PREC) ? 0.5 * iM : Dl(0.0));
     r.set(R_LAM, 1.0 / (eta * M * M));
 }
 

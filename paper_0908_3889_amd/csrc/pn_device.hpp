@@ -169,10 +169,10 @@ enum RowIdx {
     R_C5,      // -(4159 + 15876 eta) pi / 672                        (M w)^{5/3}
     R_C6,      // 3PN constant part, -(856/105) ln 16 included        (M w)^{2}
     R_C7,      // (-4415/4032 + 358675/6048 eta + 91495/1512 eta^2) pi (M w)^{7/3}
-    R_K,       // (96/5) eta: d omega/dt = K omega^2 x^5 {...}
-    R_G1,      // eta (4 + 3 m2/m1)
-    R_G2,      // eta (4 + 3 m1/m2)
-    R_SIGM,    // 1/M: (1/M^2)(M w) = w/M in the spin-spin part of Eq. (4)
+    R_K,       // (96/5) eta M: d omega/dt = K omega^3 x^2 {...}
+    R_G1,      // eta (4 + 3 m2/m1) / 2
+    R_G2,      // eta (4 + 3 m1/m2) / 2
+    R_SIGM,    // 1/(2M): w^2 times it in the spin-spin part of Eq. (4)
     R_LAM,     // 1/(eta M^2)
     NROW
 };
@@ -228,10 +228,10 @@ __device__ __forceinline__ void make_row(RowT& r, double m1, double m2, int term
                       + (541.0 / 896.0) * eta * eta - (5605.0 / 2592.0) * eta * eta * eta
                       - (856.0 / 105.0) * PN_LN16));
     r.set(R_C7, pn * ((-4415.0 / 4032.0 + (358675.0 / 6048.0) * eta + (91495.0 / 1512.0) * eta * eta) * PN_PI));
-    r.set(R_K, (terms & PN_TERM_RR) ? (96.0 / 5.0) * eta : 0.0);
-    r.set(R_G1, (terms & PN_TERM_SO_PREC) ? eta * (4.0 + 3.0 * m2 / m1) : 0.0);
-    r.set(R_G2, (terms & PN_TERM_SO_PREC) ? eta * (4.0 + 3.0 * m1 / m2) : 0.0);
-    r.set(R_SIGM, (terms & PN_TERM_SS_PREC) ? iM : 0.0);
+    r.set(R_K, (terms & PN_TERM_RR) ? (96.0 / 5.0) * eta * M : 0.0);
+    r.set(R_G1, (terms & PN_TERM_SO_PREC) ? 0.5 * (eta * (4.0 + 3.0 * m2 / m1)) : 0.0);
+    r.set(R_G2, (terms & PN_TERM_SO_PREC) ? 0.5 * (eta * (4.0 + 3.0 * m1 / m2)) : 0.0);
+    r.set(R_SIGM, (terms & PN_TERM_SS_PREC) ? 0.5 * iM : 0.0);
     r.set(R_LAM, 1.0 / (eta * M * M));
 }
 
@@ -285,25 +285,26 @@ struct LogBase {
 };
 
 // dy/dt of Eqs. (1)-(4) at y = (w, S1, S2, L) into d (d omega/dt in d[0]),
-// given v = M w, x = v^{1/3} and ln|v|.
+// given x = (M w)^{1/3} and ln|M w|.
 //
-// With v = M w and x = v^{1/3}:
-//   d w/dt = K w^2 x^5 B (formed as K w^2 x^2 v B),
+//   d w/dt = (96/5) eta w^2 x^5 B = K w^3 x^2 B  (x^3 = M w, K = (96/5) eta M),
 //     B = 1 + x^2 (c2 + x (c3' + x (c4' + x (c5 + x (c6' + x c7)))))
 //     c3' = 4 pi - so1 L.S1 - so2 L.S2,
 //     c4' = c4 - ssd (247 S1.S2 - 721 (L.S1)(L.S2)),
 //     c6' = c6 - (1712/105) ln x;
-//   dS1/dt = Omega_1 x S1,  Omega_1 = p [ (g1 x^2 - 3 sv L.S2) L + sv S2 ],
-//   dS2/dt = Omega_2 x S2,  Omega_2 = p [ (g2 x^2 - 3 sv L.S1) L + sv S1 ],
-//     p = w/2 = (M w)/(2M),  sv = w/M  (Eq. (4) expanded; the eta (M w)^{-1/3}
-//     term times (M w)^2/(2M) is p g_i x^2);
+//   dS1/dt = Omega_1 x S1,  Omega_1 = al1 L + be S2,  al1 = g1 w x^2 - 3 be L.S2,
+//   dS2/dt = Omega_2 x S2,  Omega_2 = al2 L + be S1,  al2 = g2 w x^2 - 3 be L.S1,
+//     be = w^2/(2M),  g_i = eta (4 + 3 m_j/m_i)/2
+//     (Eq. (4) expanded: the eta (M w)^{-1/3} term times (M w)^2/(2M));
 //   dL/dt = -lam x (dS1/dt + dS2/dt)   (Eq. (3)).
+// w^2 and w x^2 serve both the chirp and the precession: five operations
+// fewer than with K w^2 x^5 and a common factor w/2 of Omega_i.
 // Off the physical region (stage points of rejected or fixed steps) omega may
 // be negative; x is then the real cube root and the log term uses
-// ln(16 x^2) = ln 16 + (2/3) ln|v|, which is what Eq. (1) gives for any real x.
+// ln(16 x^2) = ln 16 + (2/3) ln|M w|, which is what Eq. (1) gives for any real x.
 template <class RowT>
 __device__ __forceinline__ void rhs_at(const RowT& r, const TermConsts& tc, const double* __restrict__ y,
-                                       double v, double x, double lnv, double* __restrict__ d) {
+                                       double x, double lnv, double* __restrict__ d) {
     const double w = y[0];
     const double x2 = x * x;
     const double L0 = y[7], L1 = y[8], L2 = y[9];
@@ -323,14 +324,13 @@ __device__ __forceinline__ void rhs_at(const RowT& r, const TermConsts& tc, cons
     B = __builtin_fma(x, B, c3p);
     B = __builtin_fma(x, B, r[R_C2]);
     B = __builtin_fma(x2, B, 1.0);
-    // x^5 = x^2 v (x^3 = v)
-    d[0] = (r[R_K] * (w * w)) * (x2 * v) * B;
+    const double ww = w * w, wx2 = w * x2;
+    d[0] = (r[R_K] * ww) * wx2 * B;
 
-    const double p = 0.5 * w;
-    const double sv = r[R_SIGM] * w;
-    const double al1 = p * __builtin_fma(r[R_G1], x2, -3.0 * sv * LS2);
-    const double al2 = p * __builtin_fma(r[R_G2], x2, -3.0 * sv * LS1);
-    const double be = p * sv;
+    const double be = r[R_SIGM] * ww;
+    const double m3be = -3.0 * be;
+    const double al1 = __builtin_fma(r[R_G1], wx2, m3be * LS2);
+    const double al2 = __builtin_fma(r[R_G2], wx2, m3be * LS1);
     // Omega_1 = al1 L + be S2, Omega_2 = al2 L + be S1
     const double o0 = __builtin_fma(al1, L0, be * b0), o1 = __builtin_fma(al1, L1, be * b1),
                  o2 = __builtin_fma(al1, L2, be * b2);
@@ -348,10 +348,10 @@ __device__ __forceinline__ void rhs_at(const RowT& r, const TermConsts& tc, cons
     d[9] = q * (d[3] + d[6]);
 }
 
-// x = v^{1/3} and ln|v| at a stage point (v = M w) from the step's base
-// point: the polynomials in u = (w - w_n)/w_n, or in full on the rare lanes
-// with |u| > 1/16 (a block the wave skips unless one of its lanes needs it).
-__device__ __forceinline__ void stage_x_lnv(const LogBase& lb, double v, double w, double& x, double& lnv) {
+// x = (M w)^{1/3} and ln|M w| at a stage point from the step's base point:
+// the polynomials in u = (w - w_n)/w_n, or in full on the rare lanes with
+// |u| > 1/16 (a block the wave skips unless one of its lanes needs it).
+__device__ __forceinline__ void stage_x_lnv(const LogBase& lb, double M, double w, double& x, double& lnv) {
     const double u = (w - lb.w) * lb.iw;
     const double c = cbrt1p_small_m1(u);
     x = __builtin_fma(lb.x, c, lb.x);
@@ -359,6 +359,7 @@ __device__ __forceinline__ void stage_x_lnv(const LogBase& lb, double v, double 
     const bool far = !(__builtin_fabs(u) <= kSmallU);
     if (__builtin_expect(__ballot(far) != 0, 0)) {
         if (far) {
+            const double v = M * w;
             x = cbrt_real(v);
             lnv = log_pos(__builtin_fabs(v));
         }
@@ -371,16 +372,15 @@ template <class RowT, bool FAST_LOG>
 __device__ __forceinline__ double rhs_x(const RowT& r, const TermConsts& tc, const LogBase& lb,
                                         const double* __restrict__ y, double* __restrict__ d, double& xo) {
     const double w = y[0];
-    const double v = r[R_M] * w;
     double x, lnv;
     if (FAST_LOG) {
-        stage_x_lnv(lb, v, w, x, lnv);
-        rhs_at(r, tc, y, v, x, lnv, d);
+        stage_x_lnv(lb, r[R_M], w, x, lnv);
     } else {
+        const double v = r[R_M] * w;
         x = cbrt_real(v);
         lnv = log_pos(__builtin_fabs(v));
-        rhs_at(r, tc, y, v, x, lnv, d);
     }
+    rhs_at(r, tc, y, x, lnv, d);
     xo = x;
     return lnv;
 }
@@ -411,10 +411,18 @@ struct RowF {
     __device__ __forceinline__ float operator[](int i) const { return v[i]; }
 };
 
-__device__ __forceinline__ RowF to_f32(const Row& r) {
+// The FP32 right-hand side keeps the factors of Eqs. (1) and (4) apart: K =
+// (96/5) eta, g_i = eta (4 + 3 m_j/m_i), 1/M.
+__device__ __forceinline__ RowF to_f32(const Row& r, double m1, double m2, int terms) {
     RowF f;
 #pragma unroll
     for (int i = 0; i < NROW; ++i) f.v[i] = (float)r.v[i];
+    const double iM = 1.0 / (m1 + m2);
+    const double eta = m1 * m2 * iM * iM;
+    f.v[R_K] = (float)((terms & PN_TERM_RR) ? (96.0 / 5.0) * eta : 0.0);
+    f.v[R_G1] = (float)(2.0 * r.v[R_G1]);
+    f.v[R_G2] = (float)(2.0 * r.v[R_G2]);
+    f.v[R_SIGM] = (float)(2.0 * r.v[R_SIGM]);
     return f;
 }
 
@@ -433,7 +441,8 @@ struct TermConstsF {
     float c6lnv;   // -1712/315 (or 0)
 };
 
-// Eqs. (1)-(4) in FP32, same expansion as rhs() above.
+// Eqs. (1)-(4) in FP32: d w/dt = K w^2 x^5 B with x^5 = x^2 v (v = M w), and
+// Omega_1 = p [(g1 x^2 - 3 sv L.S2) L + sv S2] with p = w/2, sv = w/M.
 __device__ __forceinline__ void rhs_f32(const RowF& r, const TermConstsF& tc, const float* __restrict__ y,
                                         float* __restrict__ d) {
     const float w = y[0];

@@ -590,7 +590,7 @@ struct F32Split {
         L.phase = 0.0;
         Row r;
         make_row(r, m1, m2, u.terms, u.theta_literal);
-        L.row = to_f32(r);
+        L.row = to_f32(r, m1, m2, u.terms);
         float yf[10];
 #pragma unroll
         for (int c = 0; c < 10; ++c) yf[c] = (float)L.y[c];
@@ -771,7 +771,7 @@ struct F32State {
         L.phlo = 0.0f;
         Row r;
         make_row(r, m1, m2, u.terms, u.theta_literal);
-        L.row = to_f32(r);
+        L.row = to_f32(r, m1, m2, u.terms);
         rhs_f32(L.row, u.tcf, L.y, L.k1);
         L.dt1 = 1.0f;
         L.nrhs = 1;

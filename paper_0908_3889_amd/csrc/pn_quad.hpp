@@ -82,7 +82,6 @@ __device__ __forceinline__ double rhs_quad(const RowQ& r, const PolyQ& pc, const
                                            const double (&Y)[3], double (&d)[3], double& ws, double& kws, double& xo,
                                            bool lane3, bool& far) {
     const double w = quad_perm<kQ3>(Y[0]);
-    const double v = r.M * w;
     const double u = (w - lb.w) * lb.iw;
     double q = pc.cb[0];
 #pragma unroll
@@ -97,6 +96,7 @@ __device__ __forceinline__ double rhs_quad(const RowQ& r, const PolyQ& pc, const
     if (FAST) far = far || f;
     else if (__ballot(f) != 0) {
         if (f) {
+            const double v = r.M * w;
             x = cbrt_real(v);
             lnv = log_pos(__builtin_fabs(v));
         }
@@ -123,12 +123,11 @@ __device__ __forceinline__ double rhs_quad(const RowQ& r, const PolyQ& pc, const
     B = __builtin_fma(x, B, c3p);
     B = __builtin_fma(x, B, r.C2);
     B = __builtin_fma(x2, B, 1.0);
-    const double dw = (r.K * (w * w)) * (x2 * v) * B;
+    const double ww = w * w, wx2 = w * x2;
+    const double dw = (r.K * ww) * wx2 * B;
     // Omega x (own vector) on lanes 0 and 1
-    const double p = 0.5 * w;
-    const double sv = r.SIGM * w;
-    const double al = p * __builtin_fma(r.G, x2, -3.0 * sv * dot);
-    const double be = p * sv;
+    const double be = r.SIGM * ww;
+    const double al = __builtin_fma(r.G, wx2, -3.0 * be * dot);
     const double o0 = __builtin_fma(al, P[0], be * Q[0]), o1 = __builtin_fma(al, P[1], be * Q[1]),
                  o2 = __builtin_fma(al, P[2], be * Q[2]);
     d[0] = __builtin_fma(o1, Y[2], -o2 * Y[1]);
