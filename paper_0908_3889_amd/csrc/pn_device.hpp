@@ -142,6 +142,13 @@ __device__ __forceinline__ double fmin_k(double a, double k) {
     return d;
 }
 
+// min(a, b) likewise
+__device__ __forceinline__ double fmin_v(double a, double b) {
+    double d;
+    asm("v_min_f64 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+    return d;
+}
+
 // c z^(-1/10) for z in [2^-30, 2^30] (callers clamp): FP32 seed (relative
 // error below 1e-7 over that range), then one Newton step of
 // y <- y (11 - z y^10) / 10, which leaves 5.5 times its square (< 1e-13).

@@ -244,7 +244,13 @@ __device__ __forceinline__ void rcp3(double s0, double s1, double s2, double& i0
 // reciprocal per component by a few ulp.  Lanes with a group product outside
 // the normal range (tolerances or states far beyond double precision) take one
 // reciprocal per component instead.
-__device__ __forceinline__ double error_norm(const Uni& u, const double* y, const double* ynew, const double* e) {
+//
+// fin is cleared where the candidate state or the norm is not finite.  The
+// state needs no test of its own on the other lanes: an infinite component
+// makes its group's product infinite, and a NaN one makes d omega/dt at the
+// candidate, hence e and the norm, NaN.
+__device__ __forceinline__ double error_norm(const Uni& u, const double* y, const double* ynew, const double* e,
+                                             bool& fin) {
     double sc[10], iv[10];
 #pragma unroll
     for (int c = 0; c < 10; ++c) sc[c] = __builtin_fma(u.tol, fmax_abs(y[c], ynew[c]), u.tol);
@@ -258,6 +264,7 @@ __device__ __forceinline__ double error_norm(const Uni& u, const double* y, cons
         const double q = e[c] * iv[c];
         z = __builtin_fma(q, q, z);
     }
+    fin = true;
     if (__builtin_expect(__ballot(bad) != 0, 0)) {
         if (bad) {
             z = 0.0;
@@ -265,9 +272,11 @@ __device__ __forceinline__ double error_norm(const Uni& u, const double* y, cons
             for (int c = 0; c < 10; ++c) {
                 const double q = e[c] * rcp_1step(sc[c]);
                 z = __builtin_fma(q, q, z);
+                fin = fin && finite(ynew[c]);
             }
         }
     }
+    fin = fin && !__builtin_isnan(z);
     return z * 0.1;
 }
 
@@ -294,6 +303,20 @@ __device__ __forceinline__ void tape_checkpoint(const Uni& u, int64_t idx, int j
     for (int c = 0; c < 10; ++c) ck[c] = y[c];
 }
 
+// max_steps as the lanes count
+__device__ __forceinline__ int step_limit(const Uni& u) {
+    return u.max_steps < INT32_MAX ? (int)u.max_steps : INT32_MAX;
+}
+
+// Right-hand-side evaluations of a finished inspiral: one at the start and six
+// an attempted step.  Attempted are the accepted and rejected steps, the
+// candidate past omega_f that is discarded on entering omega mode, and the one
+// that ends an inspiral as PN_ST_NONFINITE.
+template <class LaneT>
+__device__ __forceinline__ int rhs_count(const LaneT& L, int st) {
+    return 1 + 6 * (L.acc + L.rej + (L.omega_mode ? 1 : 0) + (st == PN_ST_NONFINITE ? 1 : 0));
+}
+
 // Outcome known before a step (in this order of precedence): the step limit,
 // a full tape, d omega/dt <= 0.
 template <bool RECORD, class LaneT>
@@ -301,7 +324,7 @@ __device__ __forceinline__ int pre_status(const Uni& u, const LaneT& L) {
     int st = 0;
     if (L.omega_mode ? L.dt1 <= 0 : (u.rr_on && L.k1[0] <= 0)) st = PN_ST_OMEGADOT_NONPOSITIVE;
     if (RECORD && L.acc >= u.tape_cap) st = PN_ST_TAPE_FULL;
-    if (L.acc + L.rej >= u.max_steps) st = PN_ST_MAX_STEPS;
+    if (L.acc + L.rej >= step_limit(u)) st = PN_ST_MAX_STEPS;
     return st;
 }
 
@@ -319,12 +342,16 @@ __device__ __forceinline__ double clip_step(const Uni& u, const LaneT& L, bool& 
 // Acceptance test and state update of an attempted step of size h, applied
 // on lanes with go = (active, no status before the step); other lanes keep
 // their state.  Y: candidate state, k7/dt7: its derivative, dts = sum_j b_j
-// dt_j (omega mode).  Returns 0 (continue), 1 (finished OK) or a status.
+// dt_j (omega mode); any_w: some lane of the wave is in omega mode.  What only
+// such lanes, rejections or the end of an inspiral need is branched around: of
+// the instructions a step issues, the control takes about 75 (120 with every
+// case computed and selected on every lane).  Returns 0 (continue), 1
+// (finished OK) or a status.
 template <bool RECORD, bool GEN, class LaneT, class KT>
 __device__ __forceinline__ int control(const Uni& u, LaneT& L, bool go, int st, bool fin, double z, double h,
-                                       bool last, const double* Y, const KT* k7, KT dt7, KT dts) {
+                                       bool last, const double* Y, const KT* k7, KT dt7, KT dts, bool any_w) {
     const bool fixed = GEN && u.fixed, tend = GEN && u.tend;
-    if (go && !fin) st = PN_ST_NONFINITE;
+    if (__builtin_expect(__ballot(go && !fin) != 0, 0)) st = go && !fin ? PN_ST_NONFINITE : st;
     const bool ok = go && fin;
     const bool acc = ok && (fixed || z <= Z_ACCEPT);
     // a candidate past omega_f is discarded: the stretch is finished with
@@ -334,14 +361,12 @@ __device__ __forceinline__ int control(const Uni& u, LaneT& L, bool go, int st, 
     const bool rej = ok && !acc;
     // step factor (safety 0.9, exponent 1/5, clamped to [0.2, 5], no growth
     // right after a rejection); one z^(-1/10) serves accepts and rejects
-    double fac = 1.0;
-    if (!fixed) {
-        const double p = pow_m_tenth_scaled(fmin_k(fmax_k(z, 9.313225746154785e-10), 1.073741824e9), 0.9);
-        const double lo = fmax_k(p, 0.2);
-        fac = rej ? lo : fmin_k(lo, L.last_rej ? 1.0 : 5.0);
-    }
-    // The state is updated with selects rather than a divergent branch, so
-    // that y and k1 keep their registers across the loop.
+    double lo = 1.0;
+    if (!fixed)
+        lo = fmax_k(pow_m_tenth_scaled(fmin_k(fmax_k(z, 9.313225746154785e-10), 1.073741824e9), 0.9), 0.2);
+    bool done = take && !L.omega_mode && !tend && Y[0] == u.omega_f;
+    if (tend) done = take && last;
+    if (__builtin_expect(any_w, 0)) done = done || (take && L.omega_mode && last);
     if (__builtin_expect(__ballot(to_w) != 0, 0)) {
         const KT s = to_w ? KT(1) / L.k1[0] : KT(1);
 #pragma unroll
@@ -357,19 +382,32 @@ __device__ __forceinline__ int control(const Uni& u, LaneT& L, bool go, int st, 
         tape_of(u, L.idx)[2 + L.acc] = h;
         if ((L.acc + 1) % u.ckpt_every == 0) tape_checkpoint(u, L.idx, (L.acc + 1) / u.ckpt_every, Y);
     }
-    const double tn = L.omega_mode ? __builtin_fma(h, (double)dts, L.t) : L.t + h;
-    const bool done = take && (last || (!L.omega_mode && !tend && Y[0] == u.omega_f));
-    if (take) L.take(Y, k7);
-    if (done && L.omega_mode) L.set_omega(u.omega_f);
-    L.t = take ? tn : L.t;
-    L.dt1 = take ? dt7 : L.dt1;
-    L.acc += take ? 1 : 0;
-    L.rej += rej ? 1 : 0;
-    const bool resize = rej || (take && !done && !fixed);
-    L.h = resize ? h * fac : L.h;
-    L.last_rej = resize ? rej : L.last_rej;
-    const double scale = L.omega_mode ? __builtin_fabs(L.omega()) : __builtin_fmax(1.0, __builtin_fabs(L.t));
-    if (rej && L.h < 1e-14 * scale) st = PN_ST_H_UNDERFLOW;
+    double tn = L.t + h;
+    if (__builtin_expect(any_w, 0)) {
+        tn = L.omega_mode ? __builtin_fma(h, (double)dts, L.t) : tn;
+        L.dt1 = take ? dt7 : L.dt1;
+    }
+    if (take) {
+        L.take(Y, k7);
+        L.t = tn;
+        L.acc += 1;
+        if (!fixed) {
+            L.h = h * fmin_v(lo, L.last_rej ? 1.0 : 5.0);
+            L.last_rej = false;
+        }
+    }
+    if (__builtin_expect(any_w, 0)) {
+        if (done && L.omega_mode) L.set_omega(u.omega_f);
+    }
+    if (__ballot(rej) != 0) {
+        if (rej) {
+            L.rej += 1;
+            L.h = h * lo;
+            L.last_rej = true;
+            const double scale = L.omega_mode ? __builtin_fabs(L.omega()) : __builtin_fmax(1.0, __builtin_fabs(L.t));
+            if (L.h < 1e-14 * scale) st = PN_ST_H_UNDERFLOW;
+        }
+    }
     return st != 0 ? st : (done ? 1 : 0);
 }
 
@@ -386,7 +424,7 @@ struct LaneF64 {
     double phase;     // integral of omega dt (phase kernels only)
     Row row;
     int64_t idx;
-    int acc, rej, nrhs;
+    int acc, rej;
     int nt;           // accepted time steps (recording only)
     bool omega_mode, last_rej;
     __device__ __forceinline__ double omega() const { return y[0]; }
@@ -422,14 +460,13 @@ struct F64 {
         LogBase lb;
         L.lnv = rhs_x<Row, false>(L.row, u.tc, lb, L.y, L.k1, L.x);
         L.dt1 = 1.0;
-        L.nrhs = 1;
         L.nt = 0;
         if (RECORD) tape_checkpoint(u, idx, 0, L.y);
         return 0;
     }
 
     static __device__ void finish(const Io& io, const Uni& u, const LaneT& L, int st) {
-        write_out<PHASE>(io, u, L.idx, L.y, L.t, L.acc, L.rej, L.nrhs, st, L.phase);
+        write_out<PHASE>(io, u, L.idx, L.y, L.t, L.acc, L.rej, rhs_count(L, st), st, L.phase);
         if (RECORD) {
             double* tp = tape_of(u, L.idx);
             const int nt = L.omega_mode ? L.nt : L.acc;
@@ -522,7 +559,6 @@ struct F64 {
         double k7[10], dt7 = 1.0, x7;
         const double lnv7 = rhs_x<Row, true>(R, u.tc, lb, Y, k7, x7);
         if (__builtin_expect(any_w, 0)) to_omega_variable(k7, dt7, L.omega_mode);
-        L.nrhs += go ? 6 : 0;
 
         // the error norm is formed in fixed-step mode too (and ignored there),
         // which keeps it in the same block as its operands
@@ -530,12 +566,15 @@ struct F64 {
         double e[10];
 #pragma unroll
         for (int c = 0; c < 10; ++c) e[c] = __builtin_fma(E7, k7[c], Ep[c]);
-        const double z = error_norm(u, y, Y, e) * (h * h);
-        bool fin = (GEN && u.fixed) || !__builtin_isnan(z);
+        bool fin;
+        const double z = error_norm(u, y, Y, e, fin) * (h * h);
+        if (GEN) {                   // a fixed step asks for the state alone
+            fin = u.fixed || !__builtin_isnan(z);
 #pragma unroll
-        for (int c = 0; c < 10; ++c) fin = fin && finite(Y[c]);
+            for (int c = 0; c < 10; ++c) fin = fin && finite(Y[c]);
+        }
         const int acc0 = L.acc;
-        const int r = control<RECORD, GEN>(u, L, go, st0, fin, z, h, last, Y, k7, dt7, dts);
+        const int r = control<RECORD, GEN>(u, L, go, st0, fin, z, h, last, Y, k7, dt7, dts, any_w);
         L.lnv = L.acc != acc0 ? lnv7 : L.lnv;
         L.x = L.acc != acc0 ? x7 : L.x;
         if (PHASE) L.phase = L.acc != acc0 ? __builtin_fma(h, ps, L.phase) : L.phase;
@@ -560,7 +599,7 @@ struct LaneF32 {
     double phase;     // integral of omega dt, FP64 sum of FP32 increments (phase kernels only)
     RowF row;
     int64_t idx;
-    int acc, rej, nrhs;
+    int acc, rej;
     int nt;           // accepted time steps (unused: no tape in this mode)
     bool omega_mode, last_rej;
     __device__ __forceinline__ double omega() const { return y[0]; }
@@ -596,12 +635,11 @@ struct F32Split {
         for (int c = 0; c < 10; ++c) yf[c] = (float)L.y[c];
         rhs_f32(L.row, u.tcf, yf, L.k1);
         L.dt1 = 1.0f;
-        L.nrhs = 1;
         return 0;
     }
 
     static __device__ void finish(const Io& io, const Uni& u, const LaneT& L, int st) {
-        write_out<PHASE>(io, u, L.idx, L.y, L.t, L.acc, L.rej, L.nrhs, st, L.phase);
+        write_out<PHASE>(io, u, L.idx, L.y, L.t, L.acc, L.rej, rhs_count(L, st), st, L.phase);
     }
 
     // One attempted step, run by every lane as in the FP64 lane.
@@ -681,7 +719,6 @@ struct F32Split {
         float k7[10], dt7 = 1.0f;
         rhs_f32(R, u.tcf, Y, k7);
         if (__builtin_expect(any_w, 0)) to_omega_variable(k7, dt7, L.omega_mode);
-        L.nrhs += go ? 6 : 0;
 
         // candidate state in FP64
         double ynew[10];
@@ -695,7 +732,7 @@ struct F32Split {
 #pragma unroll
         for (int c = 0; c < 10; ++c) fin = fin && finite(ynew[c]) && __builtin_isfinite(k7[c]);
         const int acc0 = L.acc;
-        const int r = control<false, GEN>(u, L, go, st0, fin, z, h, last, ynew, k7, dt7, dts);
+        const int r = control<false, GEN>(u, L, go, st0, fin, z, h, last, ynew, k7, dt7, dts, any_w);
         // the FP32 increment is summed in FP64, as the state is
         if (PHASE) L.phase = L.acc != acc0 ? __builtin_fma(h, (double)ps, L.phase) : L.phase;
         return r;
@@ -721,7 +758,7 @@ struct LaneF32S {
     float ph, phlo;   // orbital phase as ph + phlo (phase kernels only)
     RowF row;
     int64_t idx;
-    int acc, rej, nrhs;
+    int acc, rej;
     int nt;           // accepted time steps (unused: no tape in this mode)
     bool omega_mode, last_rej;
     __device__ __forceinline__ double omega() const { return (double)y[0] + (double)wlo; }
@@ -774,7 +811,6 @@ struct F32State {
         L.row = to_f32(r, m1, m2, u.terms);
         rhs_f32(L.row, u.tcf, L.y, L.k1);
         L.dt1 = 1.0f;
-        L.nrhs = 1;
         return 0;
     }
 
@@ -784,7 +820,7 @@ struct F32State {
         // an integration that reached omega_f ends on it exactly (the float
         // pair holds 48 bits of it)
         if (st == PN_ST_OK && !u.tend) yd[0] = u.omega_f;
-        write_out<PHASE>(io, u, L.idx, yd, L.t, L.acc, L.rej, L.nrhs, st, (double)L.ph + (double)L.phlo);
+        write_out<PHASE>(io, u, L.idx, yd, L.t, L.acc, L.rej, rhs_count(L, st), st, (double)L.ph + (double)L.phlo);
     }
 
     // One attempted step, run by every lane as in the FP64 lane.
@@ -863,7 +899,6 @@ struct F32State {
         float k7[10], dt7 = 1.0f;
         rhs_f32(R, u.tcf, Y, k7);
         if (__builtin_expect(any_w, 0)) to_omega_variable(k7, dt7, L.omega_mode);
-        L.nrhs += go ? 6 : 0;
 
         // the state and the candidate, viewed in FP64 for the norm and the
         // control: omega's increment joins the compensated sum, the other
@@ -883,7 +918,7 @@ struct F32State {
 #pragma unroll
         for (int c = 0; c < 10; ++c) fin = fin && finite(ynew[c]) && __builtin_isfinite(k7[c]);
         const int acc0 = L.acc;
-        const int r = control<false, GEN>(u, L, go, st0, fin, z, h, last, ynew, k7, dt7, dts);
+        const int r = control<false, GEN>(u, L, go, st0, fin, z, h, last, ynew, k7, dt7, dts, any_w);
         if (PHASE && L.acc != acc0) {
             // the phase increment joins its compensated sum
             float s, err;
@@ -981,9 +1016,11 @@ __device__ __forceinline__ void persistent_loop(const Uni& u, unsigned long long
                                           __popcll(wmask) + (64 - __popcll(amask)) >= u.refill_min);
         const bool act = active && (run_w || !L.omega_mode);
         const int r = P::step(u, L, act, run_w);
-        if (act && r != 0) {
-            L.h = -(double)(r + kPend);
-            active = false;
+        if (__builtin_expect(wave_ballot(act && r != 0) != 0, 0)) {
+            if (act && r != 0) {
+                L.h = -(double)(r + kPend);
+                active = false;
+            }
         }
     }
 }

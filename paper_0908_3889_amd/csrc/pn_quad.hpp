@@ -68,7 +68,7 @@ struct LaneQ {
     double phase;
     RowQ r;
     int64_t idx;
-    int acc, rej, nrhs, nt;
+    int acc, rej, nt;
     bool omega_mode, last_rej;
 };
 
@@ -200,7 +200,7 @@ struct QuadF64 {
         L.w = y[0];
         L.kw = k1[0];
         L.t = 0.0;
-        L.acc = 0; L.rej = 0; L.nrhs = 1; L.nt = 0;
+        L.acc = 0; L.rej = 0; L.nt = 0;
         L.omega_mode = false; L.last_rej = false;
         L.h = u.h0;
         L.dt1 = 1.0;
@@ -218,7 +218,7 @@ struct QuadF64 {
         double y[10];
         gather(L.v, y);
         if (q != 0) return;
-        write_out<PHASE>(io, u, L.idx, y, L.t, L.acc, L.rej, L.nrhs, st, L.phase);
+        write_out<PHASE>(io, u, L.idx, y, L.t, L.acc, L.rej, rhs_count(L, st), st, L.phase);
         if (RECORD) {
             double* tp = tape_of(u, L.idx);
             const int nt = L.omega_mode ? L.nt : L.acc;
@@ -362,7 +362,8 @@ struct QuadF64 {
 #pragma unroll
         for (int i = 0; i < 3; ++i) e[i] = __builtin_fma(E7, T.k7[i], e[i]);
         T.z = norm<FAST>(u, L, T.Y, e, q, far) * (h * h);
-        T.fin = finite(T.Y[0]) && finite(T.Y[1]) && finite(T.Y[2]);
+        // (a state that is not finite leaves the fast path in the norm: error_norm)
+        T.fin = FAST || (finite(T.Y[0]) && finite(T.Y[1]) && finite(T.Y[2]));
         T.dts = dts;
         T.ps = ps;
         T.far = far;
@@ -374,7 +375,7 @@ struct QuadF64 {
         int st = 0;
         if (L.omega_mode ? L.dt1 <= 0 : (u.rr_on && L.kw <= 0)) st = PN_ST_OMEGADOT_NONPOSITIVE;
         if (RECORD && L.acc >= u.tape_cap) st = PN_ST_TAPE_FULL;
-        if (L.acc + L.rej >= u.max_steps) st = PN_ST_MAX_STEPS;
+        if (L.acc + L.rej >= step_limit(u)) st = PN_ST_MAX_STEPS;
         const bool go = active && st == 0;
         bool last = false;
         double h = active ? L.h : 0.0;
@@ -393,9 +394,8 @@ struct QuadF64 {
             slow = __ballot(T.far) != 0;
         }
         if (__builtin_expect(slow, 0)) attempt<false>(u, pc, L, h, q, T);
-        L.nrhs += go ? 6 : 0;
         bool fin = T.fin;
-        if (__builtin_expect(__ballot(!fin) != 0, 0)) {
+        if (__builtin_expect(slow, 0)) {
             int f = fin ? 1 : 0;
             f = quad_perm<kQ0>(f) & quad_perm<kQ1>(f) & quad_perm<kQ2>(f) & quad_perm<kQ3>(f);
             fin = f != 0;
@@ -412,7 +412,6 @@ struct QuadF64 {
         const bool rej = ok && !acc;
         const double p = pow_m_tenth_scaled(fmin_k(fmax_k(z, 9.313225746154785e-10), 1.073741824e9), 0.9);
         const double lo = fmax_k(p, 0.2);
-        const double fac = rej ? lo : fmin_k(lo, L.last_rej ? 1.0 : 5.0);
         if (__builtin_expect(__ballot(to_w) != 0, 0)) {
             const double s = to_w ? 1.0 / L.kw : 1.0;
 #pragma unroll
@@ -429,7 +428,7 @@ struct QuadF64 {
             if (lane3) tape_of(u, L.idx)[2 + L.acc] = h;
             if ((L.acc + 1) % u.ckpt_every == 0) checkpoint(u, L.idx, (L.acc + 1) / u.ckpt_every, q, T.Y);
         }
-        const double tn = L.omega_mode ? __builtin_fma(h, T.dts, L.t) : L.t + h;
+        const double tn = any_w && L.omega_mode ? __builtin_fma(h, T.dts, L.t) : L.t + h;
         const bool done = take && (last || (!L.omega_mode && ws == u.omega_f));
         if (take) {
 #pragma unroll
@@ -442,21 +441,26 @@ struct QuadF64 {
             L.lnv = T.lnv;
             L.x = T.x;
             L.t = tn;
-            L.dt1 = T.dt7;
+            L.dt1 = any_w ? T.dt7 : L.dt1;
             L.acc += 1;
+            L.h = h * fmin_v(lo, L.last_rej ? 1.0 : 5.0);
+            L.last_rej = false;
             if (PHASE) L.phase = __builtin_fma(h, T.ps, L.phase);
         }
-        if (done && L.omega_mode) {
-            L.w = u.omega_f;
-            L.v[0] = lane3 ? u.omega_f : L.v[0];
+        if (__builtin_expect(any_w, 0)) {
+            if (done && L.omega_mode) {
+                L.w = u.omega_f;
+                L.v[0] = lane3 ? u.omega_f : L.v[0];
+            }
         }
-        L.rej += rej ? 1 : 0;
-        const bool resize = rej || (take && !done);
-        L.h = resize ? h * fac : L.h;
-        L.last_rej = resize ? rej : L.last_rej;
         if (__builtin_expect(__ballot(rej) != 0, 0)) {
-            const double scale = L.omega_mode ? __builtin_fabs(L.w) : __builtin_fmax(1.0, __builtin_fabs(L.t));
-            if (rej && L.h < 1e-14 * scale) st = PN_ST_H_UNDERFLOW;
+            if (rej) {
+                L.rej += 1;
+                L.h = h * lo;
+                L.last_rej = true;
+                const double scale = L.omega_mode ? __builtin_fabs(L.w) : __builtin_fmax(1.0, __builtin_fabs(L.t));
+                if (L.h < 1e-14 * scale) st = PN_ST_H_UNDERFLOW;
+            }
         }
         return st != 0 ? st : (done ? 1 : 0);
     }
