@@ -280,6 +280,23 @@ __device__ __forceinline__ double error_norm(const Uni& u, const double* y, cons
     return z * 0.1;
 }
 
+// Whether an FP32 step is finite: its candidate state, the derivative there
+// and the norm.  A component of either that is not makes the norm infinite or
+// NaN (an infinite state through the reciprocal of its scale, a NaN one through
+// d omega/dt, the derivative through the estimate), so the twenty tests are
+// made only where the norm is not finite, or where a fixed step ignores it.
+template <bool GEN>
+__device__ __forceinline__ bool fp32_finite(const Uni& u, double z, const double* ynew, const float* k7) {
+    bool fin = true;
+    const bool look = (GEN && u.fixed) || !finite(z);
+    if (__builtin_expect(__ballot(look) != 0, 0)) {
+        fin = (GEN && u.fixed) || !__builtin_isnan(z);
+#pragma unroll
+        for (int c = 0; c < 10; ++c) fin = fin && finite(ynew[c]) && __builtin_isfinite(k7[c]);
+    }
+    return fin;
+}
+
 // omega-mode: divide the RHS by omega-dot and put 1 in the omega slot.  One
 // Newton step (about 11 ulp) suffices: the scaled derivatives only enter
 // the state through increments far smaller than the state itself.
@@ -728,9 +745,7 @@ struct F32Split {
 #pragma unroll
         for (int c = 0; c < 10; ++c) e[c] = (double)(hf * __builtin_fmaf((float)E7, k7[c], Ep[c]));
         const double z = error_norm_pairs(u, L.y, ynew, e);
-        bool fin = (GEN && u.fixed) || !__builtin_isnan(z);
-#pragma unroll
-        for (int c = 0; c < 10; ++c) fin = fin && finite(ynew[c]) && __builtin_isfinite(k7[c]);
+        const bool fin = fp32_finite<GEN>(u, z, ynew, k7);
         const int acc0 = L.acc;
         const int r = control<false, GEN>(u, L, go, st0, fin, z, h, last, ynew, k7, dt7, dts, any_w);
         // the FP32 increment is summed in FP64, as the state is
@@ -914,9 +929,7 @@ struct F32State {
 #pragma unroll
         for (int c = 0; c < 10; ++c) e[c] = (double)(hf * __builtin_fmaf((float)E7, k7[c], Ep[c]));
         const double z = error_norm_each(u, yd, ynew, e);
-        bool fin = (GEN && u.fixed) || !__builtin_isnan(z);
-#pragma unroll
-        for (int c = 0; c < 10; ++c) fin = fin && finite(ynew[c]) && __builtin_isfinite(k7[c]);
+        const bool fin = fp32_finite<GEN>(u, z, ynew, k7);
         const int acc0 = L.acc;
         const int r = control<false, GEN>(u, L, go, st0, fin, z, h, last, ynew, k7, dt7, dts, any_w);
         if (PHASE && L.acc != acc0) {
