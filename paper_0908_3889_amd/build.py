@@ -52,7 +52,7 @@ def build(verbose: bool = False) -> str:
 
 
 # the sources the integration and adjoint kernels are compiled from
-KERNEL_SOURCES = ["pn_lib.hip", "pn_device.hpp", "pn_quad.hpp", "pn_adjoint.hpp"]
+KERNEL_SOURCES = ["pn_lib.hip", "pn_cost.hpp", "pn_device.hpp", "pn_quad.hpp", "pn_adjoint.hpp"]
 
 
 def source_digest() -> str:

@@ -22,6 +22,7 @@
 
 #include "pn.h"
 #include "pn_adjoint.hpp"
+#include "pn_cost.hpp"
 #include "pn_device.hpp"
 #include "pn_slots.hpp"
 
@@ -134,13 +135,9 @@ __device__ void write_out(const Io& io, const Uni& u, int64_t i, const double* y
     }
 }
 
-// Read inspiral idx into y and the masses; returns 0, or the status of an
-// inspiral that is finished at once (bad input, or omega0 >= omega_f), whose
-// outputs are then already written.  From the packed record when there is
-// one (six 16-byte loads from one cache line), else from the SoA inputs.
-template <bool PHASE = false>
-__device__ int read_input(const Io& io, const Uni& u, int64_t idx, double* y, double& m1, double& m2) {
-    const int64_t ld = u.ld;
+// The inputs of inspiral idx: from the packed record when there is one (six
+// 16-byte loads from one cache line), else from the SoA inputs.
+__device__ __forceinline__ void fetch(const Io& io, int64_t ld, int64_t idx, double* y, double& m1, double& m2) {
     if (io.packed) {
         const double2* r = (const double2*)(io.packed + idx * 16);
         const double2 a = r[0], b = r[1], c = r[2], d = r[3], e = r[4], f = r[5];
@@ -156,6 +153,14 @@ __device__ int read_input(const Io& io, const Uni& u, int64_t idx, double* y, do
 #pragma unroll
         for (int c = 0; c < 3; ++c) y[7 + c] = io.L0[c * ld + idx];
     }
+}
+
+// Read inspiral idx into y and the masses; returns 0, or the status of an
+// inspiral that is finished at once (bad input, or omega0 >= omega_f), whose
+// outputs are then already written.
+template <bool PHASE = false>
+__device__ int read_input(const Io& io, const Uni& u, int64_t idx, double* y, double& m1, double& m2) {
+    fetch(io, u.ld, idx, y, m1, m2);
     bool bad = !(m1 > 0.0) || !(m2 > 0.0) || !(y[0] > 0.0) || !finite(m1) || !finite(m2);
 #pragma unroll
     for (int c = 0; c < 10; ++c) bad = bad || !finite(y[c]);
@@ -950,17 +955,75 @@ __device__ __forceinline__ int lane_id() { return __builtin_amdgcn_mbcnt_hi(~0u,
 
 __device__ __forceinline__ uint64_t wave_ballot(bool p) { return __ballot(p); }
 
-// Persistent loop: each wave hands new inspirals to idle lanes from a global
-// counter, until the counter passes n and its lanes are done.  A lane that
-// finishes keeps its final state and status until the wave's next refill
-// pass, which first writes the outputs of all such lanes at once (the output
-// code then runs once per pass rather than once per finishing step); once
-// the counter is exhausted, every iteration with an idle lane is such a
-// pass, so the last outputs are written before the wave exits.
-template <class P>
-__device__ __forceinline__ void persistent_loop(const Uni& u, unsigned long long* slot) {
+// What a persistent loop hands to idle lanes: positions 0 .. total - 1, each of
+// which index() turns into an inspiral.
+
+// All inspirals of the call, from the global counter at the start of its slot,
+// in the caller's order if there is one.
+struct HandAll {
+    unsigned long long* counter;
+    __device__ __forceinline__ unsigned long long take(int cnt, int lane, int leader) {
+        unsigned long long base = 0;
+        if (lane == leader) base = atomicAdd(counter, (unsigned long long)cnt);
+        const unsigned lo = __builtin_amdgcn_readlane((unsigned)(base & 0xffffffffu), leader);
+        const unsigned hi = __builtin_amdgcn_readlane((unsigned)(base >> 32), leader);
+        return ((unsigned long long)hi << 32) | lo;
+    }
+    __device__ __forceinline__ unsigned long long total(const Uni& u) const { return (unsigned long long)u.n; }
+    __device__ __forceinline__ int64_t index(const Io& io, unsigned long long pos) const {
+        return io.order ? (int64_t)io.order[pos] : (int64_t)pos;
+    }
+};
+
+// The block's own share of a call, longest first by the estimate of
+// pn_cost.hpp (the list kernels below).  Its slots j = 8 r + k are the
+// positions k of line (r G + (b + hash(r)) mod G) of the call's n, eight
+// positions (64 bytes of an input) a line and G the number of blocks: shares of
+// one size, and of one mixture whatever pattern the caller's inputs follow.
+constexpr int kListMax = 16384;      // slots a block: 64 of a CU's 160 KB of LDS
+constexpr int kListBits = 15;        // of slot + 1
+struct BlockList {
+    uint32_t entry[kListMax];        // key << kListBits | slot + 1, descending; 0: no inspiral
+    unsigned next, total;
+};
+__device__ __forceinline__ int64_t list_element(unsigned slot) {
+    const unsigned r = slot >> 3, G = gridDim.x;
+    return ((int64_t)(r * G + (blockIdx.x + ((r * 2654435769u) >> 16)) % G) << 3) + (slot & 7);
+}
+struct HandList {
+    BlockList* l;
+    int first;       // the wave's first position, then -1
+    __device__ __forceinline__ unsigned long long take(int cnt, int lane, int leader) {
+        unsigned base = 0;
+        if (first >= 0) {
+            base = (unsigned)first;
+            first = -1;
+        } else {
+            if (lane == leader) base = atomicAdd(&l->next, (unsigned)cnt);
+            base = __builtin_amdgcn_readlane(base, leader);
+        }
+        return base;
+    }
+    __device__ __forceinline__ unsigned long long total(const Uni&) const {
+        return __builtin_amdgcn_readfirstlane(l->total);
+    }
+    __device__ __forceinline__ int64_t index(const Io& io, unsigned long long pos) const {
+        const int64_t i = list_element((l->entry[pos] & ((1u << kListBits) - 1)) - 1);
+        return io.order ? (int64_t)io.order[i] : i;
+    }
+};
+
+// Persistent loop: each wave hands new inspirals to idle lanes, until none is
+// left to hand out and its lanes are done.  A lane that finishes keeps its
+// final state and status until the wave's next refill pass, which first writes
+// the outputs of all such lanes at once (the output code then runs once per
+// pass rather than once per finishing step).  Once none is left, the wave's
+// last pass, with all its lanes idle, writes the rest: a pass and a step of
+// omega-mode for each lane that ends in the drain cost 0.2-0.3 ms of 9 (1M
+// inspirals in FP64).
+template <class P, class Hand>
+__device__ __forceinline__ void persistent_loop(const Uni& u, unsigned long long* slot, Hand hand) {
     const int lane = lane_id();
-    unsigned long long* counter = slot;
     typename P::LaneT L{};      // idle lanes step on this state and discard the result
     L.y[0] = 1.0;               // a positive omega keeps their arithmetic finite
     bool active = false;
@@ -972,7 +1035,7 @@ __device__ __forceinline__ void persistent_loop(const Uni& u, unsigned long long
     for (;;) {
         uint64_t need = wave_ballot(!active);
         const int nidle = __popcll(need);
-        if (need != 0 && (exhausted || nidle >= u.refill_min || nidle == 64)) {
+        if (nidle == 64 || (!exhausted && nidle >= u.refill_min)) {
             // The inputs, outputs and the arguments only a refill needs are read
             // from the launch descriptor in the call's slot here, rather than
             // kept in scalar registers across the step loop, which needs them all.
@@ -990,18 +1053,14 @@ __device__ __forceinline__ void persistent_loop(const Uni& u, unsigned long long
             while (need != 0 && !exhausted) {
                 const int cnt = __popcll(need);
                 const int leader = __ffsll((unsigned long long)need) - 1;
-                unsigned long long base = 0;
-                if (lane == leader) base = atomicAdd(counter, (unsigned long long)cnt);
-                const unsigned lo = __builtin_amdgcn_readlane((unsigned)(base & 0xffffffffu), leader);
-                const unsigned hi = __builtin_amdgcn_readlane((unsigned)(base >> 32), leader);
-                base = ((unsigned long long)hi << 32) | lo;
+                const unsigned long long base = hand.take(cnt, lane, leader);
                 bool still = false;
                 if (!active) {
                     const unsigned rank = __builtin_amdgcn_mbcnt_hi((unsigned)(need >> 32),
                                           __builtin_amdgcn_mbcnt_lo((unsigned)need, 0u));
                     const unsigned long long pos = base + rank;
-                    if (pos < (unsigned long long)u.n) {
-                        const int64_t idx = io.order ? (int64_t)io.order[pos] : (int64_t)pos;
+                    if (pos < hand.total(u)) {
+                        const int64_t idx = hand.index(io, pos);
                         if (idx >= 0 && idx < u.n) {
                             const int st = P::load(io, uc, L, idx);
                             if (st == 0) active = true; else still = true;
@@ -1010,7 +1069,7 @@ __device__ __forceinline__ void persistent_loop(const Uni& u, unsigned long long
                         }
                     }
                 }
-                if (base + cnt >= (unsigned long long)u.n) exhausted = true;
+                if (base + cnt >= hand.total(u)) exhausted = true;
                 need = wave_ballot(still);
             }
         }
@@ -1025,8 +1084,8 @@ __device__ __forceinline__ void persistent_loop(const Uni& u, unsigned long long
         // arithmetic runs in fewer wave-steps.
         const uint64_t wmask = wave_ballot(active && L.omega_mode);
         const uint64_t amask = wave_ballot(active);
-        const bool run_w = wmask != 0 && (exhausted || wmask == amask ||
-                                          __popcll(wmask) + (64 - __popcll(amask)) >= u.refill_min);
+        const bool run_w = wmask != 0 && (wmask == amask ||
+                                          (!exhausted && __popcll(wmask) + (64 - __popcll(amask)) >= u.refill_min));
         const bool act = active && (run_w || !L.omega_mode);
         const int r = P::step(u, L, act, run_w);
         if (__builtin_expect(wave_ballot(act && r != 0) != 0, 0)) {
@@ -1059,59 +1118,136 @@ __device__ __forceinline__ void static_loop(const Io& io, const Uni& u, int64_t 
     }
 }
 
+// One block a CU, each with a share of the inspirals that it sorts by their
+// estimated length, for calls that put more than one wave on a SIMD.  Taken as
+// they come, every wave holds a long inspiral and runs about as long as the
+// longest, with its neighbour on the SIMD.  Sorted, the lanes of a wave end
+// together, with fewer refill passes and fewer steps at which some lane is near
+// its end and slows the wave; the block's waves differ in length, and the
+// neighbours of the first ones are the last ones (a block's waves go to the
+// four SIMDs in turn); the drain is made of short inspirals.  Against the
+// global counter, FP64 (FP32-split): 100,003 of the 1M workload's inspirals
+// 1.58 -> 1.19 ms (1.20 -> 0.93), 2^20 of them 9.3 -> 8.7 (6.5 -> 5.8); lengths
+// that differ by 20, 131,072 inspirals 6.6 -> 4.1 (4.9 -> 3.5); equal masses,
+// 200,000 inspirals 1.69 -> 1.29 (1.02 -> 0.90).  The sort takes 5 us for 100,003
+// and 20 us for 2^20.
+template <class P, int BLOCK>
+__device__ __forceinline__ void list_loop(const Uni& u, unsigned long long* slot) {
+    __shared__ BlockList l;
+    const int t = threadIdx.x;
+    {
+        const LaunchDesc* d = reinterpret_cast<const LaunchDesc*>(slot + kDescOffset);
+        const Io& io = d->io;
+        const int64_t ld = d->u.ld, n = d->u.n;
+        const unsigned slots = 8 * (unsigned)((n + 8 * (int64_t)gridDim.x - 1) / (8 * (int64_t)gridDim.x));
+        unsigned size = 8;
+        while (size < slots) size *= 2;
+        if (t == 0) { l.next = BLOCK; l.total = 0; }
+        __syncthreads();
+        unsigned mine = 0;
+        for (unsigned j = t; j < size; j += BLOCK) {
+            uint32_t e = 0;
+            int64_t i = list_element(j);
+            if (j < slots && i < n && io.order) i = io.order[i];
+            if (j < slots && i >= 0 && i < n) {
+                double m1, m2, y[10];
+                fetch(io, ld, i, y, m1, m2);
+                e = cost_key(m1, m2, y, d->u.omega_f) << kListBits | (j + 1);
+                ++mine;
+            }
+            l.entry[j] = e;
+        }
+        if (mine) atomicAdd(&l.total, mine);
+        for (unsigned k = 2; k <= size; k *= 2)
+            for (unsigned j = k / 2; j > 0; j /= 2) {
+                __syncthreads();
+                for (unsigned i = t; i < size / 2; i += BLOCK) {
+                    const unsigned a = 2 * i - (i & (j - 1));
+                    const uint32_t x = l.entry[a], y = l.entry[a + j];
+                    if ((x < y) == ((a & k) == 0)) {
+                        l.entry[a] = y;
+                        l.entry[a + j] = x;
+                    }
+                }
+            }
+        __syncthreads();
+    }
+    // a wave's first run of 64: its number, the second four back to front
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+    persistent_loop<P>(u, slot, HandList{&l, 64 * ((w & ~3) == 4 ? 11 - w : w)});
+}
+
+template <int BLOCK, bool PHASE>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(kWpeF64)))
+void integrate_list_f64(Uni u, unsigned long long* slot) {
+    list_loop<F64<false, PHASE, false>, BLOCK>(u, slot);
+}
+
+template <int BLOCK, bool PHASE>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(kWpeF32)))
+void integrate_list_f32s(Uni u, unsigned long long* slot) {
+    list_loop<F32Split<PHASE, false>, BLOCK>(u, slot);
+}
+
+template <int BLOCK, bool PHASE>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(kWpeF32S)))
+void integrate_list_f32x(Uni u, unsigned long long* slot) {
+    list_loop<F32State<PHASE, false>, BLOCK>(u, slot);
+}
+
 template <int BLOCK, bool RECORD>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(kWpeF64)))
 void integrate_persistent_f64(Uni u, unsigned long long* slot) {
-    persistent_loop<F64<RECORD, false, false>>(u, slot);      // adaptive, to omega_f
+    persistent_loop<F64<RECORD, false, false>>(u, slot, HandAll{slot});      // adaptive, to omega_f
 }
 
 template <int BLOCK, bool RECORD>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(kWpeF64)))
 void integrate_persistent_f64_modes(Uni u, unsigned long long* slot) {
-    persistent_loop<F64<RECORD, false, true>>(u, slot);       // also fixed step and t_end
+    persistent_loop<F64<RECORD, false, true>>(u, slot, HandAll{slot});       // also fixed step and t_end
 }
 
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(kWpeF32)))
 void integrate_persistent_f32s(Uni u, unsigned long long* slot) {
-    persistent_loop<F32Split<false, false>>(u, slot);
+    persistent_loop<F32Split<false, false>>(u, slot, HandAll{slot});
 }
 
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(kWpeF32)))
 void integrate_persistent_f32s_modes(Uni u, unsigned long long* slot) {
-    persistent_loop<F32Split<false, true>>(u, slot);
+    persistent_loop<F32Split<false, true>>(u, slot, HandAll{slot});
 }
 
 // the same loops with the orbital phase integrated alongside
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(kWpeF64)))
 void integrate_persistent_f64_phase(Uni u, unsigned long long* slot) {
-    persistent_loop<F64<false, true>>(u, slot);
+    persistent_loop<F64<false, true>>(u, slot, HandAll{slot});
 }
 
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(kWpeF32)))
 void integrate_persistent_f32s_phase(Uni u, unsigned long long* slot) {
-    persistent_loop<F32Split<true>>(u, slot);
+    persistent_loop<F32Split<true>>(u, slot, HandAll{slot});
 }
 
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(kWpeF32S)))
 void integrate_persistent_f32x(Uni u, unsigned long long* slot) {
-    persistent_loop<F32State<false, false>>(u, slot);
+    persistent_loop<F32State<false, false>>(u, slot, HandAll{slot});
 }
 
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(kWpeF32S)))
 void integrate_persistent_f32x_modes(Uni u, unsigned long long* slot) {
-    persistent_loop<F32State<false, true>>(u, slot);
+    persistent_loop<F32State<false, true>>(u, slot, HandAll{slot});
 }
 
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(kWpeF32S)))
 void integrate_persistent_f32x_phase(Uni u, unsigned long long* slot) {
-    persistent_loop<F32State<true>>(u, slot);
+    persistent_loop<F32State<true>>(u, slot, HandAll{slot});
 }
 
 template <int BLOCK>
@@ -1964,6 +2100,43 @@ hipError_t launch_persistent(const Io& io, const Uni& u, int precision, int wave
     return hipGetLastError();
 }
 
+// The list launch: one block of waves_per_simd waves on each SIMD of a CU.
+hipError_t launch_list(const Io& io, const Uni& u, int precision, int cus, unsigned long long* counter,
+                       hipStream_t s) {
+    LaunchDesc desc;
+    desc.io = io;
+    desc.u = u;
+    hipLaunchKernelGGL(prepare_launch, dim3(1), dim3(64), 0, s, counter, desc);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    constexpr int B64 = 256 * kWpeF64, B32 = 256 * kWpeF32, B32S = 256 * kWpeF32S;
+    const bool ph = io.phase != nullptr;
+    const dim3 g((unsigned)cus);
+    if (precision == PN_PREC_FP32_STATE) {
+        if (ph) hipLaunchKernelGGL((integrate_list_f32x<B32S, true>), g, dim3(B32S), 0, s, u, counter);
+        else hipLaunchKernelGGL((integrate_list_f32x<B32S, false>), g, dim3(B32S), 0, s, u, counter);
+    } else if (precision == PN_PREC_FP32_SPLIT) {
+        if (ph) hipLaunchKernelGGL((integrate_list_f32s<B32, true>), g, dim3(B32), 0, s, u, counter);
+        else hipLaunchKernelGGL((integrate_list_f32s<B32, false>), g, dim3(B32), 0, s, u, counter);
+    } else {
+        if (ph) hipLaunchKernelGGL((integrate_list_f64<B64, true>), g, dim3(B64), 0, s, u, counter);
+        else hipLaunchKernelGGL((integrate_list_f64<B64, false>), g, dim3(B64), 0, s, u, counter);
+    }
+    return hipGetLastError();
+}
+
+// Whether a persistent call takes the list kernels: adaptive, to omega_f (what
+// the estimate is of), more inspirals than one wave on each SIMD holds (with
+// one, the longest inspiral is the time in any order) and no more than the
+// lists do.  Their estimate ranks better than pn_cost_order's (1M workload with
+// that order: 9.0 ms from the global counter, 8.65 from the lists), whose order
+// comes with packed records; an order by itself is taken as it is (by the true
+// numbers of steps it is the better one: 8.1 ms).
+bool use_list(const Io& io, const Uni& u, int cus) {
+    return !u.fixed && !u.tend && !u.tape && (!io.order || io.packed) && u.n > (int64_t)cus * 256 &&
+           u.n <= (int64_t)cus * kListMax;
+}
+
 // FP64 batches of up to this many inspirals, integrated adaptively to omega_f,
 // run four lanes on each (pn_quad.hpp): as many as fill the SIMDs with one wave
 // of 16 each.  There the chain of the longest inspiral is the time, and a
@@ -2099,8 +2272,13 @@ static int integrate_impl(int64_t n, int64_t ld, const double* m, const double* 
         return e == hipSuccess ? PN_OK : PN_EHIP;
     }
     const int cus = noalloc ? sd->cus : ctx->cus;
+    const bool list = !o.waves_per_simd && use_list(io, u, cus);
     auto launch = [&](unsigned long long* counter) {
         hipError_t e;
+        if (list) {
+            e = launch_list(io, u, o.precision, cus, counter, s);
+            return e == hipSuccess ? PN_OK : PN_EHIP;
+        }
         switch (block) {
             case 64: e = launch_persistent<64>(io, u, o.precision, wps, cus, counter, s); break;
             case 128: e = launch_persistent<128>(io, u, o.precision, wps, cus, counter, s); break;
