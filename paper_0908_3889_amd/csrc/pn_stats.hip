@@ -542,7 +542,7 @@ int kde_parts(int64_t n, int ncomp, int tiles) {
 //   ks_collect         the candidates' values, each to its bucket's range
 //   ks_solve           ranks inside the candidates and the largest deviation
 // Bound by launches and latency up to 2^20 values: 3 x 2^20 took 0.69 ms by
-// sorting (20 launches a component), 0.083 ms this way; samples of one block
+// sorting (20 launches a component), 0.056 ms this way; samples of one block
 // take one launch (ks_one).
 //
 // The bound works while a bucket holds far less of F than D ~ 1/sqrt(n); above
@@ -562,7 +562,7 @@ constexpr unsigned kKsNone = 0xffffffffu;
 // (256-byte aligned); buckets = 1024 .. 16384, about one for 16 values.
 struct KsPlan {
     int buckets, blocks;
-    int64_t count, slot, cursor, cand, part, list;      // word offsets
+    int64_t count, slot, cand, part, list;              // word offsets
     int64_t bytes;
 };
 
@@ -574,7 +574,6 @@ KsPlan ks_plan(int64_t n) {
     int64_t w = 64;                                      // header: D's bits, number of candidates
     p.count = w; w += p.buckets + 64;                    // counts, then counts below (buckets + 1)
     p.slot = w; w += p.buckets;
-    p.cursor = w; w += p.buckets;
     p.cand = w; w += p.buckets;
     p.part = w; w += (int64_t)p.buckets * p.blocks;
     p.list = w; w += 2 * n;
@@ -589,7 +588,6 @@ struct KsView {
     __device__ unsigned* ncand() const { return w + 2; }
     __device__ unsigned* count() const { return w + p.count; }
     __device__ unsigned* slot() const { return w + p.slot; }
-    __device__ unsigned* cursor() const { return w + p.cursor; }
     __device__ unsigned* cand() const { return w + p.cand; }
     __device__ unsigned* part(int b) const { return w + p.part + (int64_t)b * p.buckets; }
     __device__ double* list() const { return (double*)(w + p.list); }
@@ -637,12 +635,24 @@ __global__ __launch_bounds__(kKsCount) void ks_count(int64_t n, int64_t ld, cons
     for (int b = threadIdx.x; b < p.buckets; b += kKsCount) out[b] = sh[b];
 }
 
+// The counts of a bucket over the blocks, and for each block the sum of those
+// before it: the place of its values among the bucket's.
 __global__ __launch_bounds__(kBlock) void ks_sum(void* ws, KsPlan p) {
     const KsView v = ks_view(ws, p, blockIdx.y);
     const int b = blockIdx.x * kBlock + threadIdx.x;     // the buckets are a multiple of kBlock
+    constexpr int kAhead = 16;                           // loads in flight
     unsigned s = 0;
-#pragma unroll 8
-    for (int k = 0; k < p.blocks; ++k) s += v.part(k)[b];
+    for (int k0 = 0; k0 < p.blocks; k0 += kAhead) {
+        unsigned c[kAhead];
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) c[k] = k0 + k < p.blocks ? v.part(k0 + k)[b] : 0u;
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k)
+            if (k0 + k < p.blocks) {
+                v.part(k0 + k)[b] = s;
+                s += c[k];
+            }
+    }
     v.count()[b] = s;
 }
 
@@ -673,13 +683,26 @@ __device__ __forceinline__ double wave_max(double v) {
     return v;
 }
 
+template <int PER>
+__device__ __forceinline__ void store_words(unsigned* __restrict__ to, const unsigned* w) {
+#pragma unroll
+    for (int k = 0; k < PER; k += 4) {
+        if (PER >= 4) {
+            *(uint4*)(to + k) = make_uint4(w[k], w[k + 1 < PER ? k + 1 : 0], w[k + 2 < PER ? k + 2 : 0], w[k + 3 < PER ? k + 3 : 0]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < PER; ++j) to[j] = w[j];
+        }
+    }
+}
+
 // Ranks, bounds and candidates of one component, by one block: the counts
 // become the counts below; `slots` receives each candidate's place in the list
 // (kKsNone elsewhere), `cands` the candidates; returns their number.  PER =
 // buckets / kKsCount.  The empirical distribution below a bucket is the count
 // times 1/n, with a factor that covers the rounding against the quotient the
 // deviations are formed with (four divisions a bucket, and single loads, took
-// 37 us for 16,384 buckets, this 18 us).
+// 37 us for 16,384 buckets, this 14 us).
 template <int PER>
 __device__ int ks_scan_block(int64_t n, unsigned* __restrict__ count, unsigned* __restrict__ slots,
                              unsigned* __restrict__ cursors, unsigned* __restrict__ cands, int buckets, unsigned* shu,
@@ -707,12 +730,14 @@ __device__ int ks_scan_block(int64_t n, unsigned* __restrict__ count, unsigned* 
     double frac[PER + 1];
     unsigned below = below0;
     frac[0] = (double)below * in;
+    unsigned word[PER];
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-        count[b0 + k] = below;
+        word[k] = below;
         below += cnt[k];
         frac[k + 1] = (double)below * in;
     }
+    store_words<PER>(count + b0, word);
     if (threadIdx.x == kKsCount - 1) count[buckets] = below;
     // the largest lower bound: a bucket's last value lies below its upper edge,
     // its first above its lower edge
@@ -743,13 +768,14 @@ __device__ int ks_scan_block(int64_t n, unsigned* __restrict__ count, unsigned* 
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const bool c = (mask >> k) & 1u;
-        slots[b0 + k] = c ? slot : kKsNone;
+        word[k] = c ? slot : kKsNone;
         if (c) {
-            cursors[b0 + k] = slot;
+            if (cursors) cursors[b0 + k] = slot;
             cands[at++] = b0 + k;
             slot += cnt[k];
         }
     }
+    store_words<PER>(slots + b0, word);
     return (int)total;
 }
 
@@ -759,48 +785,44 @@ __global__ __launch_bounds__(kKsCount) void ks_scan(int64_t n, void* ws, KsPlan 
     const KsView v = ks_view(ws, p, blockIdx.x);
     int total = 0;
     switch (p.buckets / kKsCount) {
-        case 1: total = ks_scan_block<1>(n, v.count(), v.slot(), v.cursor(), v.cand(), p.buckets, shu, shd); break;
-        case 2: total = ks_scan_block<2>(n, v.count(), v.slot(), v.cursor(), v.cand(), p.buckets, shu, shd); break;
-        case 4: total = ks_scan_block<4>(n, v.count(), v.slot(), v.cursor(), v.cand(), p.buckets, shu, shd); break;
-        case 8: total = ks_scan_block<8>(n, v.count(), v.slot(), v.cursor(), v.cand(), p.buckets, shu, shd); break;
-        default: total = ks_scan_block<16>(n, v.count(), v.slot(), v.cursor(), v.cand(), p.buckets, shu, shd); break;
+        case 1: total = ks_scan_block<1>(n, v.count(), v.slot(), nullptr, v.cand(), p.buckets, shu, shd); break;
+        case 2: total = ks_scan_block<2>(n, v.count(), v.slot(), nullptr, v.cand(), p.buckets, shu, shd); break;
+        case 4: total = ks_scan_block<4>(n, v.count(), v.slot(), nullptr, v.cand(), p.buckets, shu, shd); break;
+        case 8: total = ks_scan_block<8>(n, v.count(), v.slot(), nullptr, v.cand(), p.buckets, shu, shd); break;
+        default: total = ks_scan_block<16>(n, v.count(), v.slot(), nullptr, v.cand(), p.buckets, shu, shd); break;
     }
     if (threadIdx.x == 0) *v.ncand() = (unsigned)total;
 }
 
-// The candidates are a few per cent of the values: a bit a bucket in LDS
-// decides for the others, and the places of a thread's values are taken
-// together.  Bound by the atomics that hand out the places, which meet on the
-// few candidates (25 us for 3 x 2^20 values).
+// The candidates are a few per cent of the values: a word a bucket in LDS has
+// the next place of the block's values of a candidate, and kKsNone for the
+// others.  (Places handed out by global atomics met on the few candidates: 27 us
+// for 3 x 2^20 values, this 8.)
 __global__ __launch_bounds__(kKsCount) void ks_collect(int64_t n, int64_t ld, const double* __restrict__ x, double lo,
                                                        double scale, void* ws, KsPlan p) {
-    __shared__ unsigned is_cand[16384 / 32];
+    extern __shared__ unsigned int sh[];
     const KsView v = ks_view(ws, p, blockIdx.y);
     const double* xc = x + (int64_t)blockIdx.y * ld;
     double* list = v.list();
-    for (int k = threadIdx.x; k < p.buckets / 32; k += kKsCount) is_cand[k] = 0u;
-    __syncthreads();
-    const int ncand = (int)*v.ncand();
-    for (int k = threadIdx.x; k < ncand; k += kKsCount) {
-        const unsigned b = v.cand()[k];
-        atomicOr(&is_cand[b >> 5], 1u << (b & 31));
-    }
-    __syncthreads();
     const int64_t i0 = (int64_t)blockIdx.x * kKsPerBlock + threadIdx.x;
     constexpr int kKeep = kKsPerBlock / kKsCount;
     double val[kKeep];
-    unsigned place[kKeep];
 #pragma unroll
     for (int k = 0; k < kKeep; ++k) val[k] = i0 + k * kKsCount < n ? xc[i0 + k * kKsCount] : 0.0;
+    for (int k = threadIdx.x; k < p.buckets; k += kKsCount) sh[k] = kKsNone;
+    __syncthreads();
+    const int ncand = (int)*v.ncand();
+    const unsigned* before = v.part(blockIdx.x);
+    for (int k = threadIdx.x; k < ncand; k += kKsCount) {
+        const unsigned b = v.cand()[k];
+        sh[b] = v.slot()[b] + before[b];
+    }
+    __syncthreads();
 #pragma unroll
     for (int k = 0; k < kKeep; ++k) {
         const int b = ks_bucket(val[k], lo, scale, p.buckets);
-        place[k] = kKsNone;
-        if (i0 + k * kKsCount < n && ((is_cand[b >> 5] >> (b & 31)) & 1u)) place[k] = atomicAdd(&v.cursor()[b], 1u);
+        if (i0 + k * kKsCount < n && sh[b] != kKsNone) list[atomicAdd(&sh[b], 1u)] = val[k];
     }
-#pragma unroll
-    for (int k = 0; k < kKeep; ++k)
-        if (place[k] != kKsNone) list[place[k]] = val[k];
 }
 
 // 64-bit keys that order as the values do
@@ -810,6 +832,11 @@ __device__ __forceinline__ uint64_t ks_key(double v) {
 }
 __device__ __forceinline__ double ks_unkey(uint64_t k) {
     return __longlong_as_double((long long)(k ^ ((k >> 63) ? (1ull << 63) : ~0ull)));
+}
+
+__device__ __forceinline__ double lane_value(double v, int lane) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                            __builtin_amdgcn_readlane(__double2loint(v), lane));
 }
 
 // The largest deviation among m values l[0 .. m), which have the ranks r0 ..
@@ -831,11 +858,16 @@ __device__ __forceinline__ double ks_ranked(const double* l, int m, int64_t r0, 
             const int mine = j0 + lane;
             const double vm = j0 == e0 ? ve : (mine < m ? l[mine] : 0.0);
             const int lim = m - j0 < 64 ? m - j0 : 64;
-            for (int j = 0; j < lim; ++j) {
-                const double vj = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(vm), j),
-                                                   __builtin_amdgcn_readlane(__double2loint(vm), j));
-                rank += (vj < ve || (vj == ve && j0 + j < e)) ? 1 : 0;
-            }
+            // equal values of the 64 before come before, of the 64 after, after
+            if (j0 < e0)
+                for (int j = 0; j < lim; ++j) rank += lane_value(vm, j) <= ve ? 1 : 0;
+            else if (j0 > e0)
+                for (int j = 0; j < lim; ++j) rank += lane_value(vm, j) < ve ? 1 : 0;
+            else
+                for (int j = 0; j < lim; ++j) {
+                    const double vj = lane_value(vm, j);
+                    rank += (vj < ve || (vj == ve && j < lane)) ? 1 : 0;
+                }
         }
         if (e < m) {
             const double F = ks_F(ve, lo, w);
@@ -972,15 +1004,16 @@ __device__ double ks_refine(KsRefine& R, const double* l, int m, int64_t r0, dou
 }
 
 // The largest deviation in the candidates of one component: a wave a
-// candidate (wave `wave` of `waves`), and the block its candidates that are too
-// large for one; each wave's maximum, in every lane.
+// candidate, dealt to the blocks in turn (a block of 16 waves on 16 candidates
+// left half the CUs idle: 20 us against 12 for 3 x 2^20 values), and the block
+// its candidates that are too large for one; each wave's maximum, in every lane.
 __device__ __forceinline__ double ks_solve_block(KsRefine& R, const unsigned* cand, int ncand, const unsigned* count,
                                                  const unsigned* slot, const double* list, double dn, double lo,
                                                  double w, int block, int blocks) {
     constexpr int kWaves = kKsCount / 64;
     double d = 0.0;
     bool large = false;
-    for (int k = block * kWaves + (threadIdx.x >> 6); k < ncand; k += blocks * kWaves) {
+    for (int k = (threadIdx.x >> 6) * blocks + block; k < ncand; k += blocks * kWaves) {
         const int b = (int)cand[k];
         const int64_t r0 = count[b];
         const int m = (int)(count[b + 1] - count[b]);
@@ -988,13 +1021,12 @@ __device__ __forceinline__ double ks_solve_block(KsRefine& R, const unsigned* ca
         else large = true;
     }
     if (__syncthreads_or(large)) {
-        for (int q = block * kWaves; q < ncand; q += blocks * kWaves)
-            for (int k = q; k < q + kWaves && k < ncand; ++k) {
-                const int b = (int)cand[k];
-                const int64_t r0 = count[b];
-                const int m = (int)(count[b + 1] - count[b]);
-                if (m > kKsWave) d = __builtin_fmax(d, ks_refine(R, list + slot[b], m, r0, dn, lo, w));
-            }
+        for (int k = block; k < ncand; k += blocks) {
+            const int b = (int)cand[k];
+            const int64_t r0 = count[b];
+            const int m = (int)(count[b + 1] - count[b]);
+            if (m > kKsWave) d = __builtin_fmax(d, ks_refine(R, list + slot[b], m, r0, dn, lo, w));
+        }
     }
     return wave_max(d);
 }
@@ -1286,8 +1318,8 @@ int pn_ks_uniform(int64_t n, int64_t ld, const double* x, int32_t ncomp, double 
                                    xc, lo, scale, workspace, p);
                 hipLaunchKernelGGL(ks_sum, dim3(p.buckets / kBlock, g), dim3(kBlock), 0, s, workspace, p);
                 hipLaunchKernelGGL(ks_scan, dim3(g), dim3(kKsCount), 0, s, n, workspace, p);
-                hipLaunchKernelGGL(ks_collect, dim3(p.blocks, g), dim3(kKsCount), 0, s, n, ld, xc, lo, scale, workspace,
-                                   p);
+                hipLaunchKernelGGL(ks_collect, dim3(p.blocks, g), dim3(kKsCount), p.buckets * sizeof(unsigned), s, n,
+                                   ld, xc, lo, scale, workspace, p);
                 hipLaunchKernelGGL(ks_solve, dim3(64, g), dim3(kKsCount), 0, s, n, lo, w, workspace, p);
                 hipLaunchKernelGGL(ks_final_kernel, dim3(g), dim3(64), 0, s, n, (const double*)workspace, 1,
                                    p.bytes / 8, out + 2 * c);
