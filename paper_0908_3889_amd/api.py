@@ -590,7 +590,7 @@ def statistics(dots_initial, dots_final, nbins=20, nbins2d=79, ngrid=201, stream
     return {"hist": pn_histogram(dots_final, nbins, stream=stream),
             "hist2d": pn_histogram2d(dots_initial, dots_final, nbins2d, stream=stream),
             "pearson": p,
-            "kde": pn_kde(dots_final, p[:, 3].contiguous(), ngrid, stream=stream),
+            "kde": pn_kde(dots_final, p[:, 3], ngrid, stream=stream),
             "ks": pn_ks_uniform(dots_final, stream=stream)}
 
 
