@@ -1326,14 +1326,20 @@ struct AdjIo {
 // the stage derivative: f (time mode) or g (omega mode); the cube root and
 // log of the stage from the step's base point lb
 __device__ __forceinline__ void stage_deriv(const Row& R, const TermConsts& tc, const LogBase& lb, const double* Y,
-                                            double* k, bool om) {
-    rhs<Row, true>(R, tc, lb, Y, k);
+                                            double* k, bool om, double& x, double& lnv) {
+    lnv = rhs_x<Row, true>(R, tc, lb, Y, k, x);
     if (om) {
         const double s = 1.0 / k[0];
 #pragma unroll
         for (int c = 1; c < 10; ++c) k[c] *= s;
         k[0] = 1.0;
     }
+}
+
+__device__ __forceinline__ void stage_deriv(const Row& R, const TermConsts& tc, const LogBase& lb, const double* Y,
+                                            double* k, bool om) {
+    double x, lnv;
+    stage_deriv(R, tc, lb, Y, k, om, x, lnv);
 }
 
 // one replayed step (no error control): y <- y + h sum b_i k_i
@@ -1380,7 +1386,7 @@ __device__ __forceinline__ void replay_step(const Row& R, const TermConsts& tc, 
 //   ys: this lane's LDS rows, entry (s, c) at ys[(s * 10 + c) * 64]: the state
 //       before the step (slot 0, filled by the caller), the stage points
 //       Y_2..Y_6 (slots 1..5; each replaced by its stage adjoint mu_j once
-//       stage j is reversed), and the step's log base (slot 6, entries 0..3);
+//       stage j is reversed);
 //   pf: the state and step size of the step reversed next (workspace column,
 //       entry c at pf[c * pfstride]), parked in nx (LDS, entry c at nx[c * 64]).
 // What stays in registers across the stages is the row, its adjoint, lambda
@@ -1399,6 +1405,7 @@ __device__ __forceinline__ void reverse_step(const Row& R, const TermConsts& tc,
     lds_double* ml = (lds_double*)ys;
 #define MS(J, C) ml[(((J) + 1) * 10 + (C)) * 64]
     const LogBase lb{};
+    double xs[6], ls[6];         // (M omega)^{1/3} and ln|M omega| of the stages
     {
         double y[10];
 #pragma unroll
@@ -1411,26 +1418,25 @@ __device__ __forceinline__ void reverse_step(const Row& R, const TermConsts& tc,
         for (int c = 0; c < 11; ++c) nxt[c] = pf[c * pfstride];
         double k1[10], k2[10], k3[10], k4[10], k5[10], Y[10];
         const LogBase lbs = log_base(R, y);
-        YS(6, 0) = lbs.lnv; YS(6, 1) = lbs.x; YS(6, 2) = lbs.w; YS(6, 3) = lbs.iw;
-        stage_deriv(R, tc, lbs, y, k1, om);
+        stage_deriv(R, tc, lbs, y, k1, om, xs[0], ls[0]);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int c = 0; c < 10; ++c) { Y[c] = __builtin_fma(h * A21, k1[c], y[c]); YS(1, c) = Y[c]; }
-        stage_deriv(R, tc, lbs, Y, k2, om);
+        stage_deriv(R, tc, lbs, Y, k2, om, xs[1], ls[1]);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int c = 0; c < 10; ++c) {
             Y[c] = __builtin_fma(h * A32, k2[c], __builtin_fma(h * A31, k1[c], y[c]));
             YS(2, c) = Y[c];
         }
-        stage_deriv(R, tc, lbs, Y, k3, om);
+        stage_deriv(R, tc, lbs, Y, k3, om, xs[2], ls[2]);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int c = 0; c < 10; ++c) {
             Y[c] = __builtin_fma(h * A43, k3[c], __builtin_fma(h * A42, k2[c], __builtin_fma(h * A41, k1[c], y[c])));
             YS(3, c) = Y[c];
         }
-        stage_deriv(R, tc, lbs, Y, k4, om);
+        stage_deriv(R, tc, lbs, Y, k4, om, xs[3], ls[3]);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int c = 0; c < 10; ++c) {
@@ -1438,13 +1444,14 @@ __device__ __forceinline__ void reverse_step(const Row& R, const TermConsts& tc,
                    __builtin_fma(h * A52, k2[c], __builtin_fma(h * A51, k1[c], y[c]))));
             YS(4, c) = Y[c];
         }
-        stage_deriv(R, tc, lbs, Y, k5, om);
+        stage_deriv(R, tc, lbs, Y, k5, om, xs[4], ls[4]);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int c = 0; c < 10; ++c)
             YS(5, c) = __builtin_fma(h * A65, k5[c], __builtin_fma(h * A64, k4[c],
                        __builtin_fma(h * A63, k3[c], __builtin_fma(h * A62, k2[c],
                        __builtin_fma(h * A61, k1[c], y[c])))));
+        stage_x_lnv(lbs, R[R_M], YS(5, 0), xs[5], ls[5]);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int c = 0; c < 11; ++c) nx[c * 64] = nxt[c];
@@ -1462,8 +1469,7 @@ __device__ __forceinline__ void reverse_step(const Row& R, const TermConsts& tc,
             Yi[c] = YS(SLOT, c);                                                                 \
             Lh[c] = (LAMEXPR);                                                                   \
         }                                                                                        \
-        const LogBase lbv{ml[(60) * 64], ml[(61) * 64], ml[(62) * 64], ml[(63) * 64]};              \
-        rhs_vjp(R, tc, lbv, Yi, Lh, h, lt * h * (BI), om, mu, rb);                                       \
+        rhs_vjp(R, tc, xs[SLOT], ls[SLOT], Yi, Lh, h, lt * h * (BI), om, mu, rb);                     \
         /* the row adjoint's updates are completed here: left to itself the */                 \
         /* compiler defers them to the end of the step and keeps every */                         \
         /* stage's operands alive until then (~700 AGPR moves and scratch */                      \
@@ -1643,7 +1649,7 @@ __device__ void adjoint_one(const AdjIo& io, const AdjUni& u, int64_t idx, doubl
 
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) void adjoint_kernel(AdjIo io, AdjUni u) {
-    __shared__ double s_ys[BLOCK / 64][64][64];     // y, the stage points and the step's log base
+    __shared__ double s_ys[BLOCK / 64][60][64];     // y and the stage points
     double* ys = &s_ys[threadIdx.x / 64][0][lane_id()];
     __shared__ double s_nx[BLOCK / 64][11][64];     // state and step size of the step reversed next
     double* nx = &s_nx[threadIdx.x / 64][0][lane_id()];
@@ -1662,7 +1668,7 @@ __global__ __launch_bounds__(BLOCK) void adjoint_kernel(AdjIo io, AdjUni u) {
 // gradient; adjoint_join then multiplies the parts' matrices onto it.  That is
 // 11 times the work on lanes that were idle: the time is the chain of steps of
 // one part instead of the whole run (1,000 inspirals, K = 16: one part 1.47
-// ms, five 0.49 ms).
+// ms, five 0.46 ms).
 // ---------------------------------------------------------------------------
 constexpr int kSeeds = 11;                 // lambda's 10 components and dL/dt
 constexpr int kSeedOut = 10 + NROW;        // lambda at the part's start, and the row adjoint
@@ -1681,7 +1687,7 @@ struct AdjParts {
 __device__ __forceinline__ int part_start(int N, int c, int parts) { return (int)((int64_t)N * c / parts); }
 
 __global__ __launch_bounds__(64) void adjoint_parts_kernel(AdjIo io, AdjUni u, AdjParts p) {
-    __shared__ double s_ys[64][64];
+    __shared__ double s_ys[60][64];
     __shared__ double s_nx[11][64];
     const int lane = threadIdx.x;
     double* ys = &s_ys[0][lane];
