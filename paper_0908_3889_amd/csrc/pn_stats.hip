@@ -201,17 +201,22 @@ __device__ __forceinline__ double block_max(double v, double* sh) {
 
 // ---------------------------------------------------------------------------
 // Pearson: sums, then sums of the centred products.  Samples of one block
-// (kPearOne values) are kept in its registers between the two; larger ones
-// take two passes over kPearParts blocks, each block of the second forming the
-// means from all partial sums of the first (workspace: part2[c][kPearParts][3],
-// part1[c][kPearParts][2], mean[c][2]).  Bound by launches and latency for
-// small samples (3 x 4,099: four launches 12 us, one 6 us; 3 x 16,384: 18 and
-// 9 us), by the two passes over memory for large ones (3 x 2^20: four launches
-// 30 us, three 24 us).
+// (kPearOne values) take one launch; of larger ones, up to kPearParts blocks
+// take chunks of kPearChunk values.  A chunk's values are kept in registers
+// between its sums and its centred sums, and the centred sums of two sets a, b
+// about their own means combine to those about the mean of both with
+// n_a n_b / (n_a + n_b) times the product of the differences of the means
+// (Chan, Golub & LeVeque 1983), which loses no more than a second pass over
+// memory would.  Workspace: part[c][kPearParts][5].  Bound by launches and
+// latency for small samples (3 x 4,099: four launches 12 us, one 6 us; 3 x
+// 16,384: 18 and 9 us), by reading them for large ones (3 x 2^20: two passes 24
+// us, one 16 us).
 // ---------------------------------------------------------------------------
 
 constexpr int kPearBlock = 512;
 constexpr int kPearParts = 256;
+constexpr int kPearHold = 8;
+constexpr int64_t kPearChunk = (int64_t)kPearBlock * kPearHold;
 constexpr int kPearOneBlock = 1024;
 constexpr int kPearKeep = 16;
 constexpr int64_t kPearOne = (int64_t)kPearOneBlock * kPearKeep;
@@ -262,63 +267,87 @@ __global__ __launch_bounds__(kPearOneBlock) void pearson_one_kernel(int64_t n, i
     if (threadIdx.x == 0) pearson_out(n, mx, my, v, out + c * 5);
 }
 
-__global__ __launch_bounds__(kPearBlock) void sums_kernel(int64_t n, int64_t ld, const double* __restrict__ x,
-                                                          const double* __restrict__ y, double* __restrict__ part) {
-    __shared__ double sh[2][kPearBlock / 64];
-    const int c = blockIdx.y;
-    const double* xc = x + (int64_t)c * ld;
-    const double* yc = y + (int64_t)c * ld;
-    double v[2] = {0.0, 0.0};
-#pragma unroll 4
-    for (int64_t i = (int64_t)blockIdx.x * kPearBlock + threadIdx.x; i < n; i += (int64_t)kPearParts * kPearBlock) {
-        v[0] += xc[i];
-        v[1] += yc[i];
-    }
-    block_sum<2, kPearBlock>(v, sh);
-    if (threadIdx.x < 2) part[((int64_t)c * kPearParts + blockIdx.x) * 2 + threadIdx.x] = v[threadIdx.x];
+// the number of values in the chunks k, k + parts, .. of a block
+__device__ __forceinline__ double pearson_count(int64_t n, int k, int parts) {
+    const int64_t chunks = (n + kPearChunk - 1) / kPearChunk;
+    const int64_t mine = (chunks - k + parts - 1) / parts;
+    return (double)(mine * kPearChunk - ((chunks - 1) % parts == k ? chunks * kPearChunk - n : 0));
 }
 
-__global__ __launch_bounds__(kPearBlock) void centred_kernel(int64_t n, int64_t ld, const double* __restrict__ x,
-                                                             const double* __restrict__ y,
-                                                             const double* __restrict__ part1,
-                                                             double* __restrict__ mean, double* __restrict__ part2) {
+__global__ __launch_bounds__(kPearBlock) void pearson_part_kernel(int64_t n, int64_t ld, const double* __restrict__ x,
+                                                                  const double* __restrict__ y,
+                                                                  double* __restrict__ part) {
     __shared__ double sh[3][kPearBlock / 64];
     const int c = blockIdx.y;
     const double* xc = x + (int64_t)c * ld;
     const double* yc = y + (int64_t)c * ld;
-    double m[2] = {0.0, 0.0};
-    if (threadIdx.x < kPearParts) {
-        m[0] = part1[((int64_t)c * kPearParts + threadIdx.x) * 2 + 0];
-        m[1] = part1[((int64_t)c * kPearParts + threadIdx.x) * 2 + 1];
+    double sum[2] = {0.0, 0.0}, cen[3] = {0.0, 0.0, 0.0}, na = 0.0;
+    for (int64_t i0 = blockIdx.x * kPearChunk; i0 < n; i0 += gridDim.x * kPearChunk) {
+        const int cnt = n - i0 < kPearChunk ? (int)(n - i0) : (int)kPearChunk;
+        double xv[kPearHold], yv[kPearHold], m[2] = {0.0, 0.0}, v[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < kPearHold; ++k) {
+            const int i = k * kPearBlock + threadIdx.x;
+            xv[k] = i < cnt ? xc[i0 + i] : 0.0;
+            yv[k] = i < cnt ? yc[i0 + i] : 0.0;
+        }
+#pragma unroll
+        for (int k = 0; k < kPearHold; ++k) {
+            m[0] += xv[k];
+            m[1] += yv[k];
+        }
+        block_sum<2, kPearBlock>(m, sh);
+        const double nb = (double)cnt, mx = m[0] / nb, my = m[1] / nb;
+#pragma unroll
+        for (int k = 0; k < kPearHold; ++k) {
+            if (k * kPearBlock + (int)threadIdx.x < cnt) {
+                const double dx = xv[k] - mx, dy = yv[k] - my;
+                v[0] += dx * dx;
+                v[1] += dy * dy;
+                v[2] += dx * dy;
+            }
+        }
+        block_sum<3, kPearBlock>(v, sh);
+        if (na > 0.0) {
+            const double dx = mx - sum[0] / na, dy = my - sum[1] / na, f = na * nb / (na + nb);
+            v[0] += f * dx * dx;
+            v[1] += f * dy * dy;
+            v[2] += f * dx * dy;
+        }
+        na += nb;
+        sum[0] += m[0];
+        sum[1] += m[1];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) cen[k] += v[k];
     }
-    block_sum<2, kPearBlock>(m, sh);
-    const double mx = m[0] / (double)n, my = m[1] / (double)n;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        mean[c * 2 + 0] = mx;
-        mean[c * 2 + 1] = my;
+    if (threadIdx.x == 0) {
+        double* o = part + ((int64_t)c * kPearParts + blockIdx.x) * 5;
+        o[0] = sum[0]; o[1] = sum[1]; o[2] = cen[0]; o[3] = cen[1]; o[4] = cen[2];
     }
-    double v[3] = {0.0, 0.0, 0.0};
-#pragma unroll 4
-    for (int64_t i = (int64_t)blockIdx.x * kPearBlock + threadIdx.x; i < n; i += (int64_t)kPearParts * kPearBlock) {
-        const double dx = xc[i] - mx, dy = yc[i] - my;
-        v[0] += dx * dx;
-        v[1] += dy * dy;
-        v[2] += dx * dy;
-    }
-    block_sum<3, kPearBlock>(v, sh);
-    if (threadIdx.x < 3) part2[((int64_t)c * kPearParts + blockIdx.x) * 3 + threadIdx.x] = v[threadIdx.x];
 }
 
-__global__ __launch_bounds__(kPearParts) void pearson_final_kernel(int64_t n, const double* __restrict__ part2,
-                                                                   const double* __restrict__ mean,
+__global__ __launch_bounds__(kPearParts) void pearson_final_kernel(int64_t n, int parts, const double* __restrict__ part,
                                                                    double* __restrict__ out) {
     __shared__ double sh[3][kPearParts / 64];
     const int c = blockIdx.x;
-    double v[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) v[k] = part2[((int64_t)c * kPearParts + threadIdx.x) * 3 + k];
+    const bool mine = (int)threadIdx.x < parts;
+    double m[2] = {0.0, 0.0}, v[3] = {0.0, 0.0, 0.0};
+    if (mine) {
+        const double* o = part + ((int64_t)c * kPearParts + threadIdx.x) * 5;
+        m[0] = o[0]; m[1] = o[1];
+        v[0] = o[2]; v[1] = o[3]; v[2] = o[4];
+    }
+    const double sx = m[0], sy = m[1];
+    block_sum<2, kPearParts>(m, sh);
+    const double mx = m[0] / (double)n, my = m[1] / (double)n;
+    if (mine) {
+        const double nb = pearson_count(n, threadIdx.x, parts), dx = sx / nb - mx, dy = sy / nb - my;
+        v[0] += nb * dx * dx;
+        v[1] += nb * dy * dy;
+        v[2] += nb * dx * dy;
+    }
     block_sum<3, kPearParts>(v, sh);
-    if (threadIdx.x == 0) pearson_out(n, mean[c * 2], mean[c * 2 + 1], v, out + c * 5);
+    if (threadIdx.x == 0) pearson_out(n, mx, my, v, out + c * 5);
 }
 
 // ---------------------------------------------------------------------------
@@ -1233,12 +1262,11 @@ int pn_pearson(int64_t n, int64_t ld, const double* x, const double* y, int32_t 
         return launched();
     }
     static_assert(kPearParts * 5 <= kPart * 3, "the partial sums fit the workspace");
-    double* part2 = (double*)workspace;
-    double* part1 = part2 + (size_t)ncomp * kPearParts * 3;
-    double* mean = part1 + (size_t)ncomp * kPearParts * 2;
-    hipLaunchKernelGGL(sums_kernel, dim3(kPearParts, ncomp), dim3(kPearBlock), 0, s, n, ld, x, y, part1);
-    hipLaunchKernelGGL(centred_kernel, dim3(kPearParts, ncomp), dim3(kPearBlock), 0, s, n, ld, x, y, part1, mean, part2);
-    hipLaunchKernelGGL(pearson_final_kernel, dim3(ncomp), dim3(kPearParts), 0, s, n, part2, mean, out);
+    const int64_t chunks = (n + kPearChunk - 1) / kPearChunk;
+    const int parts = chunks < kPearParts ? (int)chunks : kPearParts;
+    double* part = (double*)workspace;
+    hipLaunchKernelGGL(pearson_part_kernel, dim3(parts, ncomp), dim3(kPearBlock), 0, s, n, ld, x, y, part);
+    hipLaunchKernelGGL(pearson_final_kernel, dim3(ncomp), dim3(kPearParts), 0, s, n, parts, part, out);
     return launched();
 }
 

@@ -217,3 +217,10 @@ def test_pearson_blocks(n):
         assert abs(got[c, 2] / np.sqrt(sx / (n - 1)) - 1) <= slack
         assert abs(got[c, 3] / np.sqrt(sy / (n - 1)) - 1) <= slack
         assert abs(got[c, 4] - r) <= slack
+
+
+# more chunks of 4,096 values than blocks: the same bounds (the combined sums
+# add one more level)
+@pytest.mark.parametrize("n", [1048576, 1048577, 1052673, 2100003])
+def test_pearson_chunks(n):
+    test_pearson_blocks(n)
