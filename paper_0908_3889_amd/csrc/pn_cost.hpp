@@ -5,15 +5,18 @@
 //   needs about the integral of |y^(p)|^(1/p) dt of them.  The L_hat part of
 //   Eq. (4) turns spin i at the rate K_i = 4 + 3 m_j/m_i (in units of
 //   eta omega^(5/3) M^(2/3) / 2) about L = l L_hat, l = eta M^(5/3) omega^(-1/3),
-//   and the reaction on L turns both about L + S_i: the rate is K_i |L + S_i| / l,
-//   K_i (1 + S_i.L_hat / l) to first order.  With S_i' the part of S_i normal to
-//   L_hat, |y^(5)|^2 is the sum of |K_i^5 S_i'|^2 and, for L_hat, of
-//   |sum K_i^5 S_i'|^2 / l^2 (the latter taken twice: the better ranking where
-//   the masses are equal).  Integrated over the Newtonian chirp (1/omega0 -
-//   1/omega_f) / M is common to both rates.
-//   Rank correlation with the steps taken: 0.99 for masses up to 4:1, 0.998
-//   where the lengths differ by 20, 0.92 for equal masses and spins (0.93,
-//   0.99 and 0.05 for the larger spin's part normal to J).
+//   and the reaction on L turns both about L + S_i, at the rate K_i |L + S_i| / l.
+//   With V_i = rate^5 times the part of S_i normal to L_hat, |y^(5)|^2 is
+//   |V_1|^2 + |V_2|^2 for the spins and |V_1 + V_2|^2 / l^2 for L_hat, where the
+//   product V_1.V_2 averages out unless the spins keep step: it is weighted by
+//   1 / (1 + phi^2), phi = (5/192) (K_1 - K_2) (1/omega0 - 1/omega_f) / M the
+//   angle by which one outruns the other (and twice: the better ranking where
+//   the masses are equal).  The time is that of the chirp, (1/omega0 -
+//   1/omega_f) / M over the factor of Eq. (1) to order x^3 at omega0.
+//   Scatter of the steps taken about a smooth function of the estimate: 2.3 %
+//   for masses up to 4:1, 3.1 % where the lengths differ by 20, 2.6 % for equal
+//   masses and spins (the larger spin's part normal to J, as pn_cost_order
+//   takes it: 7, 14 and 8 %).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -30,16 +33,19 @@ __device__ __forceinline__ uint32_t cost_key(double m1, double m2, const double*
     const float n0 = (float)y[7], n1 = (float)y[8], n2 = (float)y[9];
     float a0 = (float)(y[1] * iS), a1 = (float)(y[2] * iS), a2 = (float)(y[3] * iS);
     float b0 = (float)(y[4] * iS), b1 = (float)(y[5] * iS), b2 = (float)(y[6] * iS);
-    const float il = (1.0f + q) * (1.0f + q) / q * exp2f(log2f((float)(M * w)) * (1.0f / 3.0f));
+    const float x = exp2f(log2f((float)(M * w)) * (1.0f / 3.0f));
+    const float ieta = (1.0f + q) * (1.0f + q) / q, il = ieta * x, k1 = 4.0f + 3.0f * q, k2 = 4.0f + 3.0f / q;
     const float az = a0 * n0 + a1 * n1 + a2 * n2, bz = b0 * n0 + b1 * n1 + b2 * n2;
-    float ka = (4.0f + 3.0f * q) * (1.0f + az * il), kb = (4.0f + 3.0f / q) * (1.0f + bz * il);
-    ka *= ka * ka * ka * ka;
-    kb *= kb * kb * kb * kb;
-    a0 = ka * (a0 - az * n0); a1 = ka * (a1 - az * n1); a2 = ka * (a2 - az * n2);
-    b0 = kb * (b0 - bz * n0); b1 = kb * (b1 - bz * n1); b2 = kb * (b2 - bz * n2);
-    const float ls = a0 * a0 + a1 * a1 + a2 * a2 + (b0 * b0 + b1 * b1 + b2 * b2);
-    a0 += b0; a1 += b1; a2 += b2;
-    const float k = span * exp2f(0.1f * log2f(ls + 2.0f * il * il * (a0 * a0 + a1 * a1 + a2 * a2)));
+    const float aa = a0 * a0 + a1 * a1 + a2 * a2, bb = b0 * b0 + b1 * b1 + b2 * b2;
+    const float beta = (1.0f / 12.0f) * ((113.0f + 75.0f * q) * az + (113.0f + 75.0f / q) * bz);
+    const float chirp = 1.0f + x * x * (x * (12.566371f - beta) - (743.0f / 336.0f) - 2.75f / ieta);
+    // squares of the rates, and the squares and the product of the normal parts
+    const float ra = k1 * k1 * (1.0f + il * (2.0f * az + il * aa)), rb = k2 * k2 * (1.0f + il * (2.0f * bz + il * bb));
+    const float va = ra * ra * ra * ra * ra * (aa - az * az), vb = rb * rb * rb * rb * rb * (bb - bz * bz);
+    const float rr = ra * rb, ab = rr * rr * sqrtf(fmaxf(rr, 0.0f)) * (a0 * b0 + a1 * b1 + a2 * b2 - az * bz);
+    const float phi = (5.0f / 192.0f) * (k1 - k2) * span;
+    const float y5 = (va + vb) * (1.0f + il * il) + 4.0f * il * il / (1.0f + phi * phi) * ab;
+    const float k = span / fmaxf(chirp, 0.25f) * exp2f(0.1f * log2f(fmaxf(y5, 1e-30f)));
     // positive floats order as their bit patterns do
     return k > 0.0f ? __float_as_uint(k) >> 14 : 0u;
 }
