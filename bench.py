@@ -184,6 +184,9 @@ def kernel_resources(kernel: str, block: int):
             "integrate_static_f32x": f"integrate_static_f32xILi{block}E"}.get(kernel)
     if kernel.endswith("_phase"):
         want = f"{kernel}ILi{block}E"
+    if kernel.startswith("integrate_list_"):
+        base = kernel.removesuffix("_phase")
+        want = f"{base}ILi{512 if base.endswith('f64') else 768}ELb{int(base != kernel)}E"
     for name, fields in build.resource_usage().items():
         if want and want in name:
             keep = ("VGPRs", "AGPRs", "ScratchSize [bytes/lane]", "Occupancy [waves/SIMD]", "VGPRs Spill",
@@ -705,6 +708,12 @@ def main() -> int:
     value = n * args.steps / wall
     kernel = (f"integrate_{args.schedule}_{ {'fp64': 'f64', 'fp32split': 'f32s', 'fp32': 'f32x'}[precision] }"
               + ("_phase" if args.phase else ""))
+    # the sizes at which each CU takes a share of the inspirals, longest first
+    # (a share holds 8,192; up to one wave on each SIMD the lists are not used)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    lists = (args.schedule == "persistent" and not opts.waves_per_simd and 256 * cus < n <= 8192 * cus)
+    if lists:
+        kernel = kernel.replace("persistent", "list")
     traffic = measured_traffic(kernel, w.name)
     counter_flop = measured_counter_flop(kernel, w.name)
     resources = kernel_resources(kernel, opts.block or 256)

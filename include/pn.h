@@ -10,8 +10,8 @@
  *   Eq. (4) Omega_1 (and Omega_2 by 1 <-> 2),
  * from omega0 to omega_f with the adaptive Dormand-Prince method at error
  * tolerance tol and initial step h = 10 (Sec. II).  One GPU lane integrates
- * one inspiral at a time; a persistent kernel hands new inspirals to lanes
- * as theirs finish.
+ * one inspiral at a time (four lanes in small FP64 batches); a persistent
+ * kernel hands new inspirals to lanes as theirs finish.
  *
  * Conventions for every entry point:
  *  - Arrays are structure-of-arrays of float64 (int32 where stated): component
@@ -119,18 +119,29 @@ typedef struct pn_opts {
     int32_t schedule;      /* PN_SCHED_* */
     int32_t block;         /* threads per block: 64, 128, 256 or 512; 0 -> 256 */
     int32_t waves_per_simd;/* persistent grid: waves per SIMD (1..8); 0 -> the
-                              occupancy the kernel is compiled for (2 FP64, 3 FP32-split) */
+                              occupancy the kernel is compiled for (2 FP64, 3 FP32-split).
+                              At 0, adaptive integrations to omega_f may take kernels
+                              of a shape of their own, and block is not used: up to
+                              16,384 inspirals in FP64, four lanes on each; above one
+                              wave on each SIMD and up to 8,192 inspirals on each CU,
+                              without order or with packed, one block
+                              on each CU with a share of the inspirals, the longest of
+                              it (by the library's own estimate) first.  The results
+                              are the same bit for bit. */
     int32_t refill_min;    /* persistent: a wave refills once this many of its lanes
-                              are idle (1..64), or all are; 0 -> 4 (each refill pass
-                              costs the whole wave, so refilling in small batches
-                              beats refilling every lane at once) */
+                              are idle (1..64) while inspirals are left, or all are;
+                              0 -> 4 (each refill pass costs the whole wave, so
+                              refilling in small batches beats refilling every lane
+                              at once) */
     int32_t precision;     /* PN_PREC_*; 0 -> FP64 */
     const int32_t* order;  /* NULL, or device int32 [n]: the inspiral indices in the
                               order in which the schedule hands them to lanes (a
                               permutation of 0 .. n-1, e.g. from pn_cost_order).
                               Every output is written at the inspiral's own index,
                               so the results do not depend on the order, only the
-                              speed does.  Entries outside [0, n) are skipped (that
+                              speed does.  Together with packed the order is refined
+                              (waves_per_simd above); by itself it is kept.
+                              Entries outside [0, n) are skipped (that
                               slot integrates nothing); an index missing from the
                               array leaves its outputs unwritten.  Requires
                               n <= 2^31 - 1. */
@@ -307,7 +318,8 @@ int pn_integrate_phase(int64_t n, int64_t ld,
  * pn_autotune -- choose the launch shape of pn_integrate for a population:
  * times pn_integrate on its first `sample` inspirals (all n when sample <= 0
  * or sample > n) for every candidate refill threshold {2, 3, 4, 6} and block
- * size {128, 256} (waves per SIMD as compiled), `reps` times each (<= 0 ->
+ * size {128, 256} (waves per SIMD as compiled; calls that take a kernel of a
+ * shape of its own differ by the threshold at most), `reps` times each (<= 0 ->
  * 2) after one warm-up run, and writes the fastest to *best: a copy of *opt
  * (or of the defaults when opt is NULL) with `block` and `refill_min` set.
  * The outcome of an integration does not depend on the launch shape, so the
@@ -511,7 +523,9 @@ int pn_kde(int64_t n, int64_t ld, const double* x, int32_t ncomp, const double* 
  * F(x_(i)), F(x_(i)) - (i-1)/n) over the sorted values, F(x) = (x - lo)/(hi - lo);
  * out[c][1] = the asymptotic p-value P(K > sqrt(n) D) of the Kolmogorov
  * distribution.  The values must not be NaN.  workspace:
- * pn_ks_workspace_bytes(n) bytes (a sorted copy and the sort's scratch).
+ * pn_ks_workspace_bytes(n) bytes: the larger of a sorted copy with the sort's
+ * scratch and, up to 2^22 values, three components' bucket counts and
+ * candidates (less than that but enough for the sort is accepted, and sorts).
  */
 size_t pn_ks_workspace_bytes(int64_t n);
 int pn_ks_uniform(int64_t n, int64_t ld, const double* x, int32_t ncomp, double lo, double hi, double* out,

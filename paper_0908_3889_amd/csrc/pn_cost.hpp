@@ -23,7 +23,7 @@
 
 namespace pn {
 
-// The estimate for the initial state y as 17 bits (exponent and 9 bits of the
+// The estimate for the initial state y as 18 bits (exponent and 10 bits of the
 // mantissa); 0 for inputs the integrator refuses, or that finish at once: last.
 __device__ __forceinline__ uint32_t cost_key(double m1, double m2, const double* y, double omega_f) {
     const double w = y[0];
@@ -47,7 +47,7 @@ __device__ __forceinline__ uint32_t cost_key(double m1, double m2, const double*
     const float y5 = (va + vb) * (1.0f + il * il) + 4.0f * il * il / (1.0f + phi * phi) * ab;
     const float k = span / fmaxf(chirp, 0.25f) * exp2f(0.1f * log2f(fmaxf(y5, 1e-30f)));
     // positive floats order as their bit patterns do
-    return k > 0.0f ? __float_as_uint(k) >> 14 : 0u;
+    return k > 0.0f ? __float_as_uint(k) >> 13 : 0u;
 }
 
 }  // namespace pn

@@ -980,8 +980,8 @@ struct HandAll {
 // positions k of line (r G + (b + hash(r)) mod G) of the call's n, eight
 // positions (64 bytes of an input) a line and G the number of blocks: shares of
 // one size, and of one mixture whatever pattern the caller's inputs follow.
-constexpr int kListMax = 16384;      // slots a block: 64 of a CU's 160 KB of LDS
-constexpr int kListBits = 15;        // of slot + 1
+constexpr int kListMax = 8192;       // slots a block
+constexpr int kListBits = 14;        // of slot + 1
 struct BlockList {
     uint32_t entry[kListMax];        // key << kListBits | slot + 1, descending; 0: no inspiral
     unsigned next, total;
@@ -1131,9 +1131,9 @@ __device__ __forceinline__ void static_loop(const Io& io, const Uni& u, int64_t 
 // neighbours of the first ones are the last ones (a block's waves go to the
 // four SIMDs in turn); the drain is made of short inspirals.  Against the
 // global counter, FP64 (FP32-split): 100,003 of the 1M workload's inspirals
-// 1.58 -> 1.19 ms (1.20 -> 0.93), 2^20 of them 9.3 -> 8.7 (6.5 -> 5.8); lengths
+// 1.58 -> 1.24 ms (1.20 -> 0.89), 2^20 of them 9.3 -> 8.7 (6.5 -> 5.7); lengths
 // that differ by 20, 131,072 inspirals 6.6 -> 4.1 (4.9 -> 3.5); equal masses,
-// 200,000 inspirals 1.69 -> 1.29 (1.02 -> 0.90).  The sort takes 5 us for 100,003
+// 200,000 inspirals 1.69 -> 1.28 (1.02 -> 0.89).  The sort takes 5 us for 100,003
 // and 20 us for 2^20.
 template <class P, int BLOCK>
 __device__ __forceinline__ void list_loop(const Uni& u, unsigned long long* slot) {
@@ -2138,7 +2138,9 @@ hipError_t launch_list(const Io& io, const Uni& u, int precision, int cus, unsig
 // Whether a persistent call takes the list kernels: adaptive, to omega_f (what
 // the estimate is of), more inspirals than one wave on each SIMD holds (with
 // one, the longest inspiral is the time in any order) and no more than the
-// lists do.  Their estimate ranks better than pn_cost_order's (1M workload with
+// lists do: at 2,000,003 they are still the faster way for all populations
+// measured (1M workload's 17.5 -> 16.8 ms), at 4,194,304 no longer (34.7 -> 37.2
+// with lists of 16,384).  Their estimate ranks better than pn_cost_order's (1M workload with
 // that order: 9.0 ms from the global counter, 8.65 from the lists), whose order
 // comes with packed records; an order by itself is taken as it is (by the true
 // numbers of steps it is the better one: 8.1 ms).
@@ -2150,9 +2152,9 @@ bool use_list(const Io& io, const Uni& u, int cus) {
 // FP64 batches of up to this many inspirals, integrated adaptively to omega_f,
 // run four lanes on each (pn_quad.hpp): as many as fill the SIMDs with one wave
 // of 16 each.  There the chain of the longest inspiral is the time, and a
-// quad's step takes 2.0 us against 2.8 us for one lane's (1,024 inspirals at
-// tol 1e-10: 0.64 against 0.92 ms; 16,384 of the 1M workload: 0.81 against
-// 1.06 ms).  Beyond, two waves of quads would share a SIMD at twice the
+// quad's step takes 1.9 us against 2.8 us for one lane's (1,024 inspirals at
+// tol 1e-10: 0.62 against 0.85 ms; 16,384 of the 1M workload: 0.78 against
+// 0.95 ms).  Beyond, two waves of quads would share a SIMD at twice the
 // instructions per inspiral.  Results do not depend on the choice.
 constexpr int64_t kQuadMax = 16384;
 

@@ -469,7 +469,7 @@ struct QuadF64 {
 // A quad per inspiral, no refill: a wave runs until its longest inspiral ends.
 // Bound by the instructions one wave issues for a step of its 16 inspirals
 // (about 800 straight-line vector instructions, 190 of them permutations, and
-// 130 for the step control; 4.8 cycles each for a wave alone on its SIMD).
+// the step control; 4.8 cycles each for a wave alone on its SIMD).
 // One wave a SIMD: blocks of four waves, the register count padded so that a
 // CU takes one block (two blocks on one CU while others idle cost 690 instead
 // of 450 us for 16,384 inspirals).

@@ -23,9 +23,9 @@ def _gpu():
 WAVES = {"fp64": 2, "fp32split": 3, "fp32": 3}
 
 
-# the edges of the range on 256 CUs (65,536 < n <= 4,194,304), of a list's full
+# the edges of the range on 256 CUs (65,536 < n <= 2,097,152), of a list's full
 # waves (131,072 and 196,608), odd sizes, and rows of more columns than n
-SIZES = (65536, 65537, 67583, 100003, 131072, 131073, 196609, 500009, 1048577, 4194304, 4194305)
+SIZES = (65536, 65537, 67583, 100003, 131072, 131073, 196609, 500009, 1048577, 2097152, 2097153)
 
 
 @pytest.mark.parametrize("n,phase", [(n, False) for n in SIZES] + [(67583, True), (131073, True)])
