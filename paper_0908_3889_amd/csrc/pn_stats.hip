@@ -363,10 +363,13 @@ __global__ __launch_bounds__(kPearParts) void pearson_final_kernel(int64_t n, in
 // where the first factor depends on (i, x), the second on (j, x) and the
 // third on (i, j) only: the sum over the points is the 16 x 16 product of the
 // first two, taken by the FP64 matrix instruction four points at a time, and
-// the third multiplies the finished sums.  That leaves one exponential per
-// (point, segment) instead of one per (point, grid point).  Bound by the FP64
-// units: about 26 vector instructions (104 cycles) per 64 of those factors and
-// 64 cycles for their matrix instruction, which share them.
+// the third multiplies the finished sums.  The first factor, in turn, is formed
+// by an exponential at one end of each group of four segments, the end nearer to
+// the point, and a ratio from there outward:
+//   exp(-(u + 16 s d)^2/2) = exp(-u^2/2) . exp(-16 s d u - 128 d^2),  s = +-1,
+// the ratio shrinking by exp(-256 d^2) a segment.  That leaves two exponentials
+// per (point, 64 grid points).  Bound by the FP64 units, which vector and
+// matrix instructions share.
 //
 // The first factor is carried as 2^320 times its value: an anchor up to 45 h
 // from a point still has a normal number there, so that a grid point 8 d
@@ -377,7 +380,8 @@ __global__ __launch_bounds__(kPearParts) void pearson_final_kernel(int64_t n, in
 // everywhere exceed.  Other grids (a step coarse against the bandwidth, or a
 // bandwidth that is 0 or not a number) take one exponential per (point, grid
 // point).  On 2^20 x 3 points and 201
-// grid points that path takes 0.76 ms, the products 0.074 ms.
+// grid points that path takes 0.76 ms, the products with an
+// exponential per (point, segment) 0.080 ms, these 0.073 ms.
 // ---------------------------------------------------------------------------
 
 __device__ __forceinline__ double kde_h(const double* sigma, int64_t stride, int c, double nfac) {
@@ -385,22 +389,17 @@ __device__ __forceinline__ double kde_h(const double* sigma, int64_t stride, int
 }
 
 constexpr int kKdeTile = 256;       // grid points of a block
-constexpr int kKdeRow = 18;         // LDS row of a point: 16 powers, v, padding (16-byte multiples)
+constexpr int kKdeRow = 18;         // LDS row of a point: 16 factors and padding
+constexpr int kKdePoints = 32;      // points a wave takes at a time
 
 __device__ __forceinline__ bool kde_products(double ih, double gstep, double span) {
     const double d = gstep * ih;
     return d <= 0.625 && (span * ih) * d <= 37.0;
 }
 
-// 2^(t + kKdeScale) for t <= 0 (0 below t = -1395, NaN for NaN): the polynomial
-// interpolates 2^f on [-1/2, 1/2] at its Chebyshev nodes, formed in 50-digit
-// arithmetic (largest error 3.2e-18).
-constexpr int kKdeScale = 320;
-
-__device__ __forceinline__ double exp2_scaled(double t) {
-    t = t < -1500.0 ? -1500.0 : t;
-    const double k = __builtin_rint(t);
-    const double f = t - k;
+// 2^(k + f): the polynomial interpolates 2^f on [-1/2, 1/2] at its Chebyshev
+// nodes, formed in 50-digit arithmetic (largest error 3.2e-18).
+__device__ __forceinline__ double exp2_parts(int k, double f) {
     double p = 4.455817908336064492979619e-10;
     p = __builtin_fma(p, f, 7.07419429728852100555915e-9);
     p = __builtin_fma(p, f, 1.017805708773394110461712e-7);
@@ -413,49 +412,82 @@ __device__ __forceinline__ double exp2_scaled(double t) {
     p = __builtin_fma(p, f, 0.2402265069591015956717015);
     p = __builtin_fma(p, f, 0.6931471805599453092537366);
     p = __builtin_fma(p, f, 1.0);
-    return __builtin_amdgcn_ldexp(p, (int)k + kKdeScale);
+    return __builtin_amdgcn_ldexp(p, k);
+}
+
+// 2^(t + kKdeScale) for t <= 0 (0 below t = -1395, NaN for NaN)
+constexpr int kKdeScale = 320;
+
+__device__ __forceinline__ double exp2_scaled(double t) {
+    t = t < -1500.0 ? -1500.0 : t;
+    const double k = __builtin_rint(t);
+    return exp2_parts((int)k + kKdeScale, t - k);
 }
 
 typedef double double4_t __attribute__((ext_vector_type(4)));
 
-// Chunks of 64 points are dealt to the waves of all blocks in turn.
+// Chunks of 32 points are dealt to the waves of all blocks in turn; two lanes
+// form a point's factors, lane p those of the segments and powers below the
+// middle, lane 32 + p those above.
 __device__ __forceinline__ void kde_block_products(int64_t n, const double* __restrict__ xc, double ih, double d,
                                                    double gmid, double* sh, int ngrid, int g0,
                                                    double* __restrict__ out) {
+    constexpr double kLog2e = 1.44269504088896340736;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    double (*row)[kKdeRow] = (double (*)[kKdeRow])sh + wave * 64;
-    const double m = 16.0 * (double)((lane & 15) - 8);
-    const int64_t chunks = (n + 63) / 64;
+    double (*first)[kKdeRow] = (double (*)[kKdeRow])sh + wave * 2 * kKdePoints;      // exp(-u_i^2/2)
+    double (*power)[kKdeRow] = first + kKdePoints;                                    // exp(-v d)^j
+    const int pt = lane & (kKdePoints - 1), half = lane / kKdePoints;
+    // the ratio's exponent step u + step2 with both coefficients to twice the
+    // precision, step2's integer apart: rounded alike for all points, they
+    // would not average out
+    const double step = -16.0 * d * kLog2e;
+    const double steplo = __builtin_fma(-16.0 * d, kLog2e, -step) + (-16.0 * d) * 2.0355273740931033e-17;
+    const double step2 = (8.0 * d) * step, step2i = __builtin_rint(step2), step2f = step2 - step2i;
+    const double step2lo = __builtin_fma(8.0 * d, step, -step2) + (8.0 * d) * steplo;
+    const double shrink = exp(-256.0 * d * d), far = 65.0 / d;
+    const int64_t chunks = (n + kKdePoints - 1) / kKdePoints;
     double4_t acc = {0.0, 0.0, 0.0, 0.0};
     for (int64_t ch = (int64_t)blockIdx.x * (kBlock / 64) + wave; ch < chunks;
          ch += (int64_t)gridDim.x * (kBlock / 64)) {
-        const int64_t i = ch * 64 + lane;
+        const int64_t i = ch * kKdePoints + pt;
         // beyond the end: a point at infinity, whose first factor is 0
         const double x = i < n ? xc[i] : __builtin_inf();
         const double v = (gmid - x) * ih;
         double a = v * d;
         a = __builtin_fmin(__builtin_fmax(a, -75.0), 75.0);
-        const double p1 = exp(-a), q1 = exp(a);
-        const double p2 = p1 * p1, p3 = p2 * p1, p4 = p2 * p2, q2 = q1 * q1, q3 = q2 * q1, q4 = q2 * q2;
-        double2* r = (double2*)row[lane];
-        r[0] = make_double2(q4 * q4, q4 * q3);
-        r[1] = make_double2(q3 * q3, q4 * q1);
-        r[2] = make_double2(q4, q3);
-        r[3] = make_double2(q2, q1);
-        r[4] = make_double2(1.0, p1);
-        r[5] = make_double2(p2, p3);
-        r[6] = make_double2(p4, p4 * p1);
-        r[7] = make_double2(p3 * p3, p4 * p3);
-        row[lane][16] = v;
+        // the powers -8 .. -1 or 0 .. 7
+        const double b1 = exp(half ? -a : a);
+        const double b2 = b1 * b1, b3 = b2 * b1, b4 = b2 * b2;
+        double* r = &power[pt][8];
+        const int s = half ? 1 : -1;
+        r[s] = b1; r[2 * s] = b2; r[3 * s] = b3; r[4 * s] = b4;
+        r[5 * s] = b4 * b1; r[6 * s] = b3 * b3; r[7 * s] = b4 * b3;
+        r[half ? 0 : -8] = half ? 1.0 : b4 * b4;
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            const int i0 = 8 * half + 4 * g;
+            const double m0 = 16.0 * (double)(i0 - 8);
+            const bool up = __builtin_fma(m0 + 24.0, d, v) >= 0.0;       // the group's middle is right of the point
+            const double u = __builtin_fma(up ? m0 : m0 + 48.0, d, v);
+            const double e0 = exp2_scaled((u * u) * (-0.5 * kLog2e));
+            const double su = __builtin_fmin(up ? u : -u, far);          // beyond, e0 is 0
+            const double k = __builtin_rint(__builtin_fma(su, step, step2f));
+            double q = exp2_parts((int)k + (int)step2i, __builtin_fma(su, step, -k) + (step2f + __builtin_fma(su, steplo, step2lo)));
+            const double e1 = e0 * q;
+            q *= shrink;
+            const double e2 = e1 * q;
+            q *= shrink;
+            double* f = &first[pt][up ? i0 : i0 + 3];
+            const int t = up ? 1 : -1;
+            f[0] = e0; f[t] = e1; f[2 * t] = e2; f[3 * t] = e2 * q;
+        }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll 4
-        for (int q = 0; q < 16; ++q) {
-            const double* rq = row[4 * q + (lane >> 4)];
-            const double u = __builtin_fma(m, d, rq[16]);
-            const double e = exp2_scaled((u * u) * -0.72134752044448170368);     // -(log2 e)/2
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(e, rq[lane & 15], acc, 0, 0, 0);
+#pragma unroll
+        for (int k = 0; k < kKdePoints / 4; ++k) {
+            const int p = 4 * k + (lane >> 4);
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(first[p][lane & 15], power[p][lane & 15], acc, 0, 0, 0);
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
