@@ -377,8 +377,10 @@ __global__ __launch_bounds__(kPearParts) void pearson_final_kernel(int64_t n, in
 // stay in range for d <= 5/8 (the third factor is then at least exp(-413))
 // and (hi - lo)/h . d <= 37 (the second is at most exp(296) inside [lo, hi]);
 // v d is clamped to +-75, which only points whose first factor is 0
-// everywhere exceed.  Other grids (a step coarse against the bandwidth, or a
-// bandwidth that is 0 or not a number) take one exponential per (point, grid
+// everywhere exceed.  Other grids (a step coarse against the bandwidth, a
+// bandwidth that is 0, negative or not a number, or one so large that the step
+// is below 1e-290 of it, infinite ones among them: 65/d and the lanes beyond the
+// end, with x at infinity, need a normal d) take one exponential per (point, grid
 // point).  On 2^20 x 3 points and 201
 // grid points that path takes 0.76 ms, the products with an
 // exponential per (point, segment) 0.080 ms, these 0.073 ms.
@@ -394,7 +396,7 @@ constexpr int kKdePoints = 32;      // points a wave takes at a time
 
 __device__ __forceinline__ bool kde_products(double ih, double gstep, double span) {
     const double d = gstep * ih;
-    return d <= 0.625 && (span * ih) * d <= 37.0;
+    return d >= 1e-290 && d <= 0.625 && (span * ih) * d <= 37.0;
 }
 
 // 2^(k + f): the polynomial interpolates 2^f on [-1/2, 1/2] at its Chebyshev
