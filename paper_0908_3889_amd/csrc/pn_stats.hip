@@ -371,17 +371,18 @@ __global__ __launch_bounds__(kPearParts) void pearson_final_kernel(int64_t n, in
 // per (point, 64 grid points).  Bound by the FP64 units, which vector and
 // matrix instructions share.
 //
-// The first factor is carried as 2^320 times its value: an anchor up to 45 h
-// from a point still has a normal number there, so that a grid point 8 d
-// closer is exact down to the smallest density a double holds.  The products
-// stay in range for d <= 5/8 (the third factor is then at least exp(-413))
-// and (hi - lo)/h . d <= 37 (the second is at most exp(296) inside [lo, hi]);
-// v d is clamped to +-75, which only points whose first factor is 0
-// everywhere exceed.  Other grids (a step coarse against the bandwidth, a
-// bandwidth that is 0, negative or not a number, or one so large that the step
-// is below 1e-290 of it, infinite ones among them: 65/d and the lanes beyond the
-// end, with x at infinity, need a normal d) take one exponential per (point, grid
-// point).  On 2^20 x 3 points and 201
+// The first factor is carried as 2^448 times its value.  Of a term that is a
+// normal number, exp(-708) at least, the product of the first two is then at
+// least exp(310 - 708 - 871 d^2) (j = 7, m_i = -128), which is normal too for
+// d <= 0.59, and at most exp(310 + 1056 d^2) (j = -8), which leaves exp(30) for
+// the sum over the points.  It is 0 beyond 46 h from the anchor, and the
+// outermost anchors lie 128 d from the middle one: a point with |v d| > 46 d +
+// 128 d^2, at most 72, has none, and v d is clamped to +-75.  With (hi - lo)/h .
+// d <= 37 the second factor is at most exp(296) inside [lo, hi].  Other grids (a
+// step coarse against the bandwidth, a bandwidth that is 0, negative or not a
+// number, or one so large that the step is below 1e-290 of it, infinite ones
+// among them: 65/d and the lanes beyond the end, with x at infinity, need a
+// normal d) take one exponential per (point, grid point).  On 2^20 x 3 points and 201
 // grid points that path takes 0.76 ms, the products with an
 // exponential per (point, segment) 0.080 ms, these 0.073 ms.
 // ---------------------------------------------------------------------------
@@ -396,7 +397,7 @@ constexpr int kKdePoints = 32;      // points a wave takes at a time
 
 __device__ __forceinline__ bool kde_products(double ih, double gstep, double span) {
     const double d = gstep * ih;
-    return d >= 1e-290 && d <= 0.625 && (span * ih) * d <= 37.0;
+    return d >= 1e-290 && d <= 0.59 && (span * ih) * d <= 37.0;
 }
 
 // 2^(k + f): the polynomial interpolates 2^f on [-1/2, 1/2] at its Chebyshev
@@ -417,11 +418,11 @@ __device__ __forceinline__ double exp2_parts(int k, double f) {
     return __builtin_amdgcn_ldexp(p, k);
 }
 
-// 2^(t + kKdeScale) for t <= 0 (0 below t = -1395, NaN for NaN)
-constexpr int kKdeScale = 320;
+// 2^(t + kKdeScale) for t <= 0 (0 below t = -1523, NaN for NaN)
+constexpr int kKdeScale = 448;
 
 __device__ __forceinline__ double exp2_scaled(double t) {
-    t = t < -1500.0 ? -1500.0 : t;
+    t = t < -1600.0 ? -1600.0 : t;
     const double k = __builtin_rint(t);
     return exp2_parts((int)k + kKdeScale, t - k);
 }

@@ -1,5 +1,6 @@
 """The density estimate where its products of exponentials end: bandwidths far
-larger than the grid, infinite or negative, against the numpy definition of
+larger than the grid, infinite or negative, and points at the distance where
+their last contribution to the grid vanishes, against the numpy definition of
 oracle/stats.py."""
 import numpy as np
 import pytest
@@ -40,3 +41,17 @@ def test_kde_extreme_bandwidths(n, sigma):
         got = _kde(x, sigma, ngrid)
         assert np.isfinite(ref).all()
         np.testing.assert_allclose(got, ref, rtol=RTOL, atol=0.0 if sigma < 1e306 else 1e-307)
+
+
+# a grid step of d bandwidths, the points `away` bandwidths outside [lo, hi]
+@pytest.mark.parametrize("d", [0.1, 0.3, 0.5, 0.58, 0.589999, 0.59, 0.590001, 0.6, 0.62, 0.7])
+@pytest.mark.parametrize("away", [0.0, 20.0, 30.0, 34.0, 36.0, 37.0])
+@pytest.mark.parametrize("ngrid", [9, 17, 25, 60, 95, 257, 300])
+def test_kde_points_outside_the_grid(d, away, ngrid):
+    sigma = (2.0 / (ngrid - 1)) / d / (1.06 * 3 ** -0.2)
+    h = 1.06 * sigma * 3 ** -0.2
+    for side in (-1.0, 1.0):
+        x = side * (1.0 + h * (away + np.array([0.0, 0.21, 0.37])))
+        ref = S.kde(x, S.kde_grid(-1.0, 1.0, ngrid), h)
+        assert ref.max() > 1e-300
+        np.testing.assert_allclose(_kde(x, sigma, ngrid), ref, rtol=RTOL, atol=1e-307)
