@@ -604,7 +604,8 @@ int kde_parts(int64_t n, int ncomp, int tiles) {
 //   ks_count, ks_sum   bucket counts, per block and summed
 //   ks_scan            ranks, bounds, candidates (one block a component)
 //   ks_collect         the candidates' values, each to its bucket's range
-//   ks_solve           ranks inside the candidates and the largest deviation
+//   ks_split           where values cluster: below
+//   ks_solve           ranks inside the candidates, the largest deviation, its p-value
 // Bound by launches and latency up to 2^20 values: 3 x 2^20 took 0.69 ms by
 // sorting (20 launches a component), 0.056 ms this way; samples of one block
 // take one launch (ks_one).
@@ -617,16 +618,32 @@ int kde_parts(int64_t n, int ncomp, int tiles) {
 constexpr int64_t kKsBucketMax = (int64_t)1 << 22;
 constexpr int kKsCount = 1024;           // threads of ks_count, ks_scan and ks_solve
 constexpr int kKsPerBlock = 16384;       // values counted by one block
-constexpr int kKsWave = 512;             // most values of a bucket that one wave ranks
+constexpr int kKsWave = 128;             // most values of a range that a wave ranks beside idle ones
+constexpr int kKsBlock = 512;            // most values that a wave or a block ranks
 constexpr int kKsBins = 1024;            // key bins of a refinement level
 constexpr int kKsLevels = 7;             // 10 bits a level of the 64-bit key
 constexpr unsigned kKsNone = 0xffffffffu;
+
+// Values that cluster (scalar products of aligned spins, samples of a few
+// values) put a large part of the sample into a few buckets, and a block that
+// refines such a bucket reads it alone: 2^22 equal values took 6.4 ms, a sort
+// 0.46.  Candidates with more than 1/16 of the sample (and 4096 values) are split
+// by all blocks instead, as the sample is, but by values drawn from them:
+// ks_scan sorts about 1000 of their values (splitters), ks_collect counts the
+// others at and between the splitters, ks_split takes the deviations at the
+// splitters, which are exact, and collects the values between two neighbours
+// only where their bound exceeds the largest of those.  Ties are then splitters,
+// and the rest is cut evenly however narrow the cluster: 0.12 ms.
+constexpr int kKsHuge = 15;              // most such buckets
+constexpr int kKsSplit = 1008;           // most splitters (with kKsHuge, a thread each)
+constexpr unsigned kKsHugeMark = 0xffffff00u;
+__host__ __device__ __forceinline__ int64_t ks_huge_min(int64_t n) { return n / 16 > 4096 ? n / 16 : 4096; }
 
 // Places of one component's workspace, in 4-byte words from its start
 // (256-byte aligned); buckets = 1024 .. 16384, about one for 16 values.
 struct KsPlan {
     int buckets, blocks;
-    int64_t count, slot, cand, part, list;              // word offsets
+    int64_t count, slot, cand, part, split, list;       // word offsets
     int64_t bytes;
 };
 
@@ -635,11 +652,12 @@ KsPlan ks_plan(int64_t n) {
     p.buckets = 1024;
     while (p.buckets < 16384 && (int64_t)p.buckets * 16 < n) p.buckets *= 2;
     p.blocks = (int)((n + kKsPerBlock - 1) / kKsPerBlock);
-    int64_t w = 64;                                      // header: D's bits, number of candidates
+    int64_t w = 64;                                      // header: KsView
     p.count = w; w += p.buckets + 64;                    // counts, then counts below (buckets + 1)
     p.slot = w; w += p.buckets;
     p.cand = w; w += p.buckets;
     p.part = w; w += (int64_t)p.buckets * p.blocks;
+    p.split = w; w += 5 * kKsSplit + 2 * kKsHuge + 2;    // KsView
     p.list = w; w += 2 * n;
     p.bytes = (w * 4 + 255) / 256 * 256;
     return p;
@@ -650,6 +668,20 @@ struct KsView {
     KsPlan p;
     __device__ unsigned long long* dmax() const { return (unsigned long long*)w; }
     __device__ unsigned* ncand() const { return w + 2; }
+    __device__ unsigned* nhuge() const { return w + 3; }
+    __device__ unsigned* nsub() const { return w + 4; }             // records at part(0)
+    __device__ unsigned* done() const { return w + 5; }             // blocks of ks_solve
+    // the huge buckets in order, the splitters below each (and all, at nhuge),
+    // the number of values in those before it
+    __device__ unsigned* huge_bucket() const { return w + 8; }
+    __device__ unsigned* huge_split() const { return w + 8 + kKsHuge; }
+    __device__ unsigned* huge_values() const { return w + 9 + 2 * kKsHuge; }
+    // the S splitters, and counts: at them, between them (of bucket h: from
+    // huge_split[h] + h), and the places of the latter already taken
+    __device__ double* splitter() const { return (double*)(w + p.split); }
+    __device__ unsigned* at_split() const { return w + p.split + 2 * kKsSplit; }
+    __device__ unsigned* between() const { return at_split() + kKsSplit; }
+    __device__ unsigned* taken() const { return between() + kKsSplit + kKsHuge; }
     __device__ unsigned* count() const { return w + p.count; }
     __device__ unsigned* slot() const { return w + p.slot; }
     __device__ unsigned* cand() const { return w + p.cand; }
@@ -682,13 +714,21 @@ __device__ __forceinline__ double ks_bucket_hi(int b, int buckets, double ib) {
     return b == buckets - 1 ? __builtin_inf() : ((double)(b + 1) * ib) * (1.0 + 0x1p-48);
 }
 
+// t[k] += 1 from each lane that calls; lanes that agree with the first add once
+__device__ __forceinline__ void lds_count(unsigned* t, int k) {
+    const int k0 = __builtin_amdgcn_readfirstlane(k);
+    const uint64_t same = __ballot(k == k0);
+    if (k != k0) atomicAdd(&t[k], 1u);
+    else if ((threadIdx.x & 63) == __ffsll((unsigned long long)same) - 1) atomicAdd(&t[k0], (unsigned)__popcll(same));
+}
+
 __global__ __launch_bounds__(kKsCount) void ks_count(int64_t n, int64_t ld, const double* __restrict__ x, double lo,
                                                      double scale, void* ws, KsPlan p) {
     extern __shared__ unsigned int sh[];
     const KsView v = ks_view(ws, p, blockIdx.y);
     const double* xc = x + (int64_t)blockIdx.y * ld;
     for (int b = threadIdx.x; b < p.buckets; b += kKsCount) sh[b] = 0u;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *v.dmax() = 0ull;
+    if (blockIdx.x == 0 && threadIdx.x == 0) { *v.dmax() = 0ull; *v.done() = 0u; }
     __syncthreads();
     const int64_t i0 = (int64_t)blockIdx.x * kKsPerBlock;
     const int64_t i1 = i0 + kKsPerBlock < n ? i0 + kKsPerBlock : n;
@@ -770,7 +810,7 @@ __device__ __forceinline__ void store_words(unsigned* __restrict__ to, const uns
 template <int PER>
 __device__ int ks_scan_block(int64_t n, unsigned* __restrict__ count, unsigned* __restrict__ slots,
                              unsigned* __restrict__ cursors, unsigned* __restrict__ cands, int buckets, unsigned* shu,
-                             double* shd) {
+                             double* shd, unsigned* nhuge = nullptr, unsigned* huge = nullptr) {
     const int b0 = threadIdx.x * PER;
     const double in = 1.0 / (double)n, ib = 1.0 / buckets;       // the latter exact: a power of two
     constexpr double kDown = 1.0 - 0x1p-50, kUp = 1.0 + 0x1p-50;
@@ -837,25 +877,123 @@ __device__ int ks_scan_block(int64_t n, unsigned* __restrict__ count, unsigned* 
             if (cursors) cursors[b0 + k] = slot;
             cands[at++] = b0 + k;
             slot += cnt[k];
+            if (nhuge && cnt[k] > ks_huge_min(n)) huge[atomicAdd(nhuge, 1u)] = b0 + k;
         }
     }
     store_words<PER>(slots + b0, word);
     return (int)total;
 }
 
-__global__ __launch_bounds__(kKsCount) void ks_scan(int64_t n, void* ws, KsPlan p) {
+// A place below n for each i, scattered so that it agrees with no period of the
+// sample (a grid of parameters): places at a fixed distance found no value of a
+// bucket that held all others.
+__device__ __forceinline__ int64_t ks_scatter(unsigned i, int64_t n) {
+    i = (i + 1u) * 0x9e3779b1u;
+    i = (i ^ (i >> 15)) * 0x85ebca77u;
+    i ^= i >> 13;
+    return (int64_t)(((uint64_t)i * (uint64_t)n) >> 32);      // n <= 2^22
+}
+
+// The huge buckets' splitters, sorted by the block (bitonic, a value a thread):
+// as many of their values as 16,384 places of the sample give, up to kKsSplit.
+__device__ void ks_splitters(const KsView& v, int64_t n, const double* __restrict__ x, double lo, double scale, int nh,
+                             const unsigned* huge, double* sh, unsigned* shn) {
+    const int t = threadIdx.x;
+    if (t == 0) *shn = 0u;
+    unsigned rank = 0, before = 0;
+    if (t < nh) {
+        for (int h = 0; h < nh; ++h)
+            if (huge[h] < huge[t]) {
+                ++rank;
+                before += v.count()[huge[h] + 1] - v.count()[huge[h]];
+            }
+        v.huge_bucket()[rank] = huge[t];
+        v.huge_values()[rank] = before;
+    }
+    for (int i = t; i < 3 * kKsSplit + 2 * kKsHuge; i += kKsCount) v.at_split()[i] = 0u;
+    __syncthreads();
+    constexpr int kAhead = 4;
+    for (int r = 0; r < 16; r += kAhead) {
+        double u[kAhead];
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) u[k] = x[ks_scatter((unsigned)((r + k) * kKsCount + t), n)];
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+            const unsigned b = ks_bucket(u[k], lo, scale, v.p.buckets);
+            bool in = false;
+            for (int h = 0; h < nh; ++h) in = in || huge[h] == b;
+            const uint64_t mask = __ballot(in);
+            unsigned at = 0;
+            if (in && (t & 63) == __ffsll((unsigned long long)mask) - 1) at = atomicAdd(shn, (unsigned)__popcll(mask));
+            if (mask != 0) at = __shfl(at, __ffsll((unsigned long long)mask) - 1) + __popcll(mask & ((1ull << (t & 63)) - 1));
+            if (in && at < kKsSplit) sh[at] = u[k];
+        }
+        __syncthreads();
+        const bool full = *shn >= kKsSplit;
+        __syncthreads();
+        if (full) break;
+    }
+    const int S = *shn < kKsSplit ? (int)*shn : kKsSplit;
+    double u = t < S ? sh[t] : __builtin_inf();
+    for (int k = 2; k <= kKsCount; k *= 2)
+        for (int j = k / 2; j > 0; j /= 2) {
+            double o;
+            if (j < 64) {
+                o = __shfl_xor(u, j);
+            } else {
+                __syncthreads();
+                sh[t] = u;
+                __syncthreads();
+                o = sh[t ^ j];
+            }
+            u = ((t & j) == 0) == ((t & k) == 0) ? __builtin_fmin(u, o) : __builtin_fmax(u, o);
+        }
+    if (t < S) v.splitter()[t] = u;
+    const unsigned b = ks_bucket(u, lo, scale, v.p.buckets);
+    for (int h = 0; h < nh; ++h) {
+        const int below = __syncthreads_count(t < S && b < v.huge_bucket()[h]);
+        if (t == 0) v.huge_split()[h] = below;
+    }
+    if (t == 0) v.huge_split()[nh] = S;
+}
+
+__global__ __launch_bounds__(kKsCount) void ks_scan(int64_t n, int64_t ld, const double* __restrict__ x, double lo,
+                                                    double scale, void* ws, KsPlan p) {
     __shared__ unsigned shu[kKsCount / 64];
     __shared__ double shd[kKsCount / 64];
+    __shared__ unsigned nhuge, huge[kKsHuge];
+    __shared__ double sample[kKsCount];
     const KsView v = ks_view(ws, p, blockIdx.x);
+    if (threadIdx.x == 0) nhuge = 0u;
+    __syncthreads();
     int total = 0;
+    unsigned *c = v.count(), *s = v.slot(), *k = v.cand();
     switch (p.buckets / kKsCount) {
-        case 1: total = ks_scan_block<1>(n, v.count(), v.slot(), nullptr, v.cand(), p.buckets, shu, shd); break;
-        case 2: total = ks_scan_block<2>(n, v.count(), v.slot(), nullptr, v.cand(), p.buckets, shu, shd); break;
-        case 4: total = ks_scan_block<4>(n, v.count(), v.slot(), nullptr, v.cand(), p.buckets, shu, shd); break;
-        case 8: total = ks_scan_block<8>(n, v.count(), v.slot(), nullptr, v.cand(), p.buckets, shu, shd); break;
-        default: total = ks_scan_block<16>(n, v.count(), v.slot(), nullptr, v.cand(), p.buckets, shu, shd); break;
+        case 1: total = ks_scan_block<1>(n, c, s, nullptr, k, p.buckets, shu, shd, &nhuge, huge); break;
+        case 2: total = ks_scan_block<2>(n, c, s, nullptr, k, p.buckets, shu, shd, &nhuge, huge); break;
+        case 4: total = ks_scan_block<4>(n, c, s, nullptr, k, p.buckets, shu, shd, &nhuge, huge); break;
+        case 8: total = ks_scan_block<8>(n, c, s, nullptr, k, p.buckets, shu, shd, &nhuge, huge); break;
+        default: total = ks_scan_block<16>(n, c, s, nullptr, k, p.buckets, shu, shd, &nhuge, huge); break;
     }
-    if (threadIdx.x == 0) *v.ncand() = (unsigned)total;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        *v.ncand() = (unsigned)total;
+        *v.nhuge() = nhuge;
+        *v.nsub() = 0u;
+    }
+    if (nhuge > 0) ks_splitters(v, n, x + (int64_t)blockIdx.x * ld, lo, scale, (int)nhuge, huge, sample, shu);
+}
+
+// The number of the splitters below v (1024 of them, padded with infinity), for
+// several values side by side.
+template <int K>
+__device__ __forceinline__ void ks_place(const double* spl, const double (&v)[K], int (&at)[K]) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) at[k] = 0;
+#pragma unroll
+    for (int step = 512; step > 0; step >>= 1)
+#pragma unroll
+        for (int k = 0; k < K; ++k) at[k] += spl[at[k] + step - 1] < v[k] ? step : 0;
 }
 
 // The candidates are a few per cent of the values: a word a bucket in LDS has
@@ -865,6 +1003,8 @@ __global__ __launch_bounds__(kKsCount) void ks_scan(int64_t n, void* ws, KsPlan 
 __global__ __launch_bounds__(kKsCount) void ks_collect(int64_t n, int64_t ld, const double* __restrict__ x, double lo,
                                                        double scale, void* ws, KsPlan p) {
     extern __shared__ unsigned int sh[];
+    __shared__ double spl[kKsCount];
+    __shared__ unsigned bins[2 * kKsSplit + kKsHuge];
     const KsView v = ks_view(ws, p, blockIdx.y);
     const double* xc = x + (int64_t)blockIdx.y * ld;
     double* list = v.list();
@@ -881,12 +1021,41 @@ __global__ __launch_bounds__(kKsCount) void ks_collect(int64_t n, int64_t ld, co
         const unsigned b = v.cand()[k];
         sh[b] = v.slot()[b] + before[b];
     }
+    const int nh = (int)*v.nhuge();
+    if (nh > 0) {
+        __syncthreads();
+        if ((int)threadIdx.x < nh) sh[v.huge_bucket()[threadIdx.x]] = kKsHugeMark + threadIdx.x;
+    }
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < kKeep; ++k) {
         const int b = ks_bucket(val[k], lo, scale, p.buckets);
-        if (i0 + k * kKsCount < n && sh[b] != kKsNone) list[atomicAdd(&sh[b], 1u)] = val[k];
+        if (i0 + k * kKsCount < n && sh[b] < kKsHugeMark) list[atomicAdd(&sh[b], 1u)] = val[k];
     }
+    if (nh == 0) return;
+    const int S = (int)v.huge_split()[nh];
+    spl[threadIdx.x] = (int)threadIdx.x < S ? v.splitter()[threadIdx.x] : __builtin_inf();
+    for (int i = threadIdx.x; i < 2 * kKsSplit + kKsHuge; i += kKsCount) bins[i] = 0u;
+    __syncthreads();
+    // (read again: kept, they would cost half the occupancy)
+    constexpr int kAhead = 2;
+#pragma unroll 1
+    for (int k0 = 0; k0 < kKeep; k0 += kAhead) {
+        double u[kAhead];
+        int at[kAhead];
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) u[k] = i0 + (k0 + k) * kKsCount < n ? xc[i0 + (k0 + k) * kKsCount] : 0.0;
+        ks_place(spl, u, at);
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+            const unsigned h = sh[ks_bucket(u[k], lo, scale, p.buckets)] - kKsHugeMark;
+            if (i0 + (k0 + k) * kKsCount < n && h < kKsHuge)
+                lds_count(bins, at[k] < S && spl[at[k]] == u[k] ? at[k] : kKsSplit + at[k] + (int)h);
+        }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < 2 * kKsSplit + kKsHuge; i += kKsCount)
+        if (bins[i]) atomicAdd(&v.at_split()[i], bins[i]);
 }
 
 // 64-bit keys that order as the values do
@@ -914,6 +1083,15 @@ __device__ __forceinline__ double ks_ranked(const double* l, int m, int64_t r0, 
     m = __builtin_amdgcn_readfirstlane(m);
     first = __builtin_amdgcn_readfirstlane(first);
     double d = 0.0;
+    if (m > 64) {                             // equal values: the first and the last rank
+        const double v0 = l[0];
+        int e = lane;
+        while (e - lane < m && __ballot(e < m && l[e] != v0) == 0) e += 64;
+        if (e - lane >= m) {
+            const double F = ks_F(v0, lo, w);
+            return __builtin_fmax(0.0, __builtin_fmax(ks_up(r0 + m - 1, dn, F), ks_down(r0, dn, F)));
+        }
+    }
     for (int e0 = first; e0 < m; e0 += stride) {
         const int e = e0 + lane;
         const double ve = e < m ? l[e] : 0.0;
@@ -944,7 +1122,7 @@ __device__ __forceinline__ double ks_ranked(const double* l, int m, int64_t r0, 
 // A bucket with more values than a wave ranks (values that cluster): the
 // whole block refines it by key bins, 1024 a level, the bin with the largest
 // upper bound first, until no bin's bound exceeds the deviation found; bins
-// of up to kKsWave values are ranked, bins of one repeated value have their
+// of up to kKsBlock values are ranked, bins of one repeated value have their
 // largest deviations at their first and last rank.
 struct KsRefine {
     unsigned below[kKsLevels][kKsBins + 1];
@@ -952,27 +1130,48 @@ struct KsRefine {
     uint64_t klo[kKsLevels], khi[kKsLevels];
     int64_t base[kKsLevels];
     int shift[kKsLevels];
-    double vals[kKsWave];
+    double vals[kKsBlock];
+    unsigned later[kKsCount], nmid, nbig;
     unsigned long long k0, k1, pick;
     unsigned nvals;
     unsigned scan[kKsCount / 64];
     double red[kKsCount / 64];
 };
 
+// f(value) for the m values, a block's threads in turn, eight loads in flight
+template <class F>
+__device__ __forceinline__ void ks_each(const double* l, int m, F&& f) {
+    constexpr int kAhead = 8;
+    for (int i0 = threadIdx.x; i0 < m; i0 += kAhead * kKsCount) {
+        double v[kAhead];
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) v[k] = i0 + k * kKsCount < m ? l[i0 + k * kKsCount] : 0.0;
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k)
+            if (i0 + k * kKsCount < m) f(v[k]);
+    }
+}
+
 // smallest and largest key of the values with keys in [a, b] (at least one)
-__device__ void ks_key_range(KsRefine& R, const double* l, int m, uint64_t a, uint64_t b) {
+__device__ __forceinline__ void ks_key_range(KsRefine& R, const double* l, int m, uint64_t a, uint64_t b) {
     __syncthreads();
     if (threadIdx.x == 0) { R.k0 = ~0ull; R.k1 = 0ull; }
     __syncthreads();
     unsigned long long k0 = ~0ull, k1 = 0ull;
-    for (int i = threadIdx.x; i < m; i += kKsCount) {
-        const uint64_t k = ks_key(l[i]);
+    ks_each(l, m, [&](double v) {
+        const uint64_t k = ks_key(v);
         if (k >= a && k <= b) {
             k0 = k < k0 ? k : k0;
             k1 = k > k1 ? k : k1;
         }
+    });
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+        const unsigned long long o0 = __shfl_xor(k0, d), o1 = __shfl_xor(k1, d);
+        k0 = o0 < k0 ? o0 : k0;
+        k1 = o1 > k1 ? o1 : k1;
     }
-    if (k0 <= k1) {
+    if ((threadIdx.x & 63) == 0 && k0 <= k1) {
         atomicMin(&R.k0, k0);
         atomicMax(&R.k1, k1);
     }
@@ -980,7 +1179,7 @@ __device__ void ks_key_range(KsRefine& R, const double* l, int m, uint64_t a, ui
 }
 
 // level lev: the values with keys in [R.k0, R.k1], the first of them of rank base
-__device__ void ks_build(KsRefine& R, int lev, const double* l, int m, int64_t base) {
+__device__ __forceinline__ void ks_build(KsRefine& R, int lev, const double* l, int m, int64_t base) {
     const uint64_t a = R.k0, b = R.k1;
     const int bits = 64 - __clzll((long long)(b - a));
     const int shift = bits > 10 ? bits - 10 : 0;
@@ -988,10 +1187,10 @@ __device__ void ks_build(KsRefine& R, int lev, const double* l, int m, int64_t b
     if (threadIdx.x < kKsBins / 32) R.done[lev][threadIdx.x] = 0u;
     if (threadIdx.x == 0) { R.klo[lev] = a; R.khi[lev] = b; R.shift[lev] = shift; R.base[lev] = base; }
     __syncthreads();
-    for (int i = threadIdx.x; i < m; i += kKsCount) {
-        const uint64_t k = ks_key(l[i]);
-        if (k >= a && k <= b) atomicAdd(&R.below[lev][(k - a) >> shift], 1u);
-    }
+    ks_each(l, m, [&](double v) {
+        const uint64_t k = ks_key(v);
+        if (k >= a && k <= b) lds_count(R.below[lev], (int)((k - a) >> shift));
+    });
     __syncthreads();
     unsigned total;
     const unsigned before = block_scan(R.below[lev][threadIdx.x], R.scan, total);      // kKsCount == kKsBins
@@ -1009,9 +1208,13 @@ __device__ __forceinline__ double block_max_all(KsRefine& R, double v) {
     return v;
 }
 
-__device__ double ks_refine(KsRefine& R, const double* l, int m, int64_t r0, double dn, double lo, double w) {
+__device__ __forceinline__ double ks_refine(KsRefine& R, const double* l, int m, int64_t r0, double dn, double lo, double w) {
     double best = 0.0;
     ks_key_range(R, l, m, 0ull, ~0ull);
+    if (R.k0 == R.k1) {                       // equal values
+        const double F = ks_F(ks_unkey(R.k0), lo, w);
+        return __builtin_fmax(0.0, __builtin_fmax(ks_up(r0 + m - 1, dn, F), ks_down(r0, dn, F)));
+    }
     int lev = 0;
     ks_build(R, 0, l, m, r0);
     while (lev >= 0) {
@@ -1045,12 +1248,11 @@ __device__ double ks_refine(KsRefine& R, const double* l, int m, int64_t r0, dou
         __syncthreads();
         if (threadIdx.x == 0) { R.done[lev][pb >> 5] |= 1u << (pb & 31); R.nvals = 0u; }
         __syncthreads();
-        if (cnt <= kKsWave) {
-            for (int i = threadIdx.x; i < m; i += kKsCount) {
-                const double v = l[i];
+        if (cnt <= kKsBlock) {
+            ks_each(l, m, [&](double v) {
                 const uint64_t k = ks_key(v);
                 if (k >= pa && k <= pe) R.vals[atomicAdd(&R.nvals, 1u)] = v;
-            }
+            });
             __syncthreads();
             best = __builtin_fmax(best, block_max_all(R, ks_ranked(R.vals, cnt, base, dn, lo, w, threadIdx.x & ~63, kKsCount)));
             continue;
@@ -1067,39 +1269,157 @@ __device__ double ks_refine(KsRefine& R, const double* l, int m, int64_t r0, dou
     return best;
 }
 
-// The largest deviation in the candidates of one component: a wave a
-// candidate, dealt to the blocks in turn (a block of 16 waves on 16 candidates
-// left half the CUs idle: 20 us against 12 for 3 x 2^20 values), and the block
-// its candidates that are too large for one; each wave's maximum, in every lane.
-__device__ __forceinline__ double ks_solve_block(KsRefine& R, const unsigned* cand, int ncand, const unsigned* count,
-                                                 const unsigned* slot, const double* list, double dn, double lo,
-                                                 double w, int block, int blocks) {
+// The deviations at the splitters of the huge buckets, and the values between
+// them where they may be exceeded, to the bucket's range of the list; each range
+// of these is a record (values, places below, place in the list) for ks_solve.
+// Every block forms the bounds for itself; a thread has the values between two
+// splitters and those at the upper one.
+__global__ __launch_bounds__(kKsCount) void ks_split(int64_t n, int64_t ld, const double* __restrict__ x, double lo,
+                                                     double w, double scale, int per, void* ws, KsPlan p) {
+    const KsView v = ks_view(ws, p, blockIdx.y);
+    const int nh = (int)*v.nhuge();
+    if (nh == 0) return;
+    __shared__ double spl[kKsCount];
+    __shared__ unsigned place[kKsSplit + kKsHuge], shu[kKsCount / 64], huge[kKsHuge];
+    __shared__ double shd[kKsCount / 64];
+    const double* xc = x + (int64_t)blockIdx.y * ld;
+    const double dn = (double)n, ib = 1.0 / p.buckets;
+    const int t = threadIdx.x, S = (int)v.huge_split()[nh];
+    spl[t] = t < S ? v.splitter()[t] : __builtin_inf();
+    if (t < nh) huge[t] = v.huge_bucket()[t];
+    __syncthreads();
+    const bool mine = t < S + nh;
+    int h = 0;
+    for (int k = 1; k < nh; ++k)
+        if (t >= (int)v.huge_split()[k] + k) h = k;
+    const int i = t - h, first = (int)v.huge_split()[h], end = (int)v.huge_split()[h + 1], b = (int)huge[h];
+    const unsigned open = mine ? v.between()[t] : 0u, at = mine && i < end ? v.at_split()[i] : 0u;
+    unsigned total;
+    const unsigned r0 = block_scan(open + at, shu, total) - v.huge_values()[h] + v.count()[b];
+    double d = 0.0;
+    if (at) {
+        const double F = ks_F(spl[i], lo, w);
+        d = __builtin_fmax(ks_up((int64_t)r0 + open + at - 1, dn, F), ks_down((int64_t)r0 + open, dn, F));
+    }
+    d = wave_max(__builtin_fmax(d, 0.0));
+    if ((t & 63) == 0) shd[t >> 6] = d;
+    __syncthreads();
+    double best = 0.0;
+    for (int k = 0; k < kKsCount / 64; ++k) best = __builtin_fmax(best, shd[k]);
+    // bounds of the values between, from the splitters' F and the bucket's edges
+    bool take = false;
+    if (open) {
+        const double fl = i > first ? ks_F(spl[i - 1], lo, w) : ks_bucket_lo(b, ib);
+        const double fh = i < end ? ks_F(spl[i], lo, w) : ks_bucket_hi(b, p.buckets, ib);
+        take = ks_up((int64_t)r0 + open - 1, dn, fl) > best || ks_down((int64_t)r0, dn, fh) > best;
+    }
+    // a bucket's range of the list has room for all of its values: they lie in it
+    // as those between the splitters do, r0 - count[b] from its start
+    unsigned recs;
+    const unsigned rec = block_scan(take ? 1u : 0u, shu, recs), to = v.slot()[b] + r0 - v.count()[b];
+    if (mine) place[t] = take ? to : kKsNone;
+    if (blockIdx.x == 0) {
+        if (take) {
+            unsigned* out = v.part(0) + 3 * rec;
+            out[0] = open;
+            out[1] = r0;
+            out[2] = to;
+        }
+        if (t == 0) {
+            *v.nsub() = recs;
+            if (best > 0.0) atomicMax(v.dmax(), (unsigned long long)__double_as_longlong(best));
+        }
+    }
+    if (recs == 0) return;
+    __syncthreads();
+    const int64_t i0 = (int64_t)blockIdx.x * per + t;
+    constexpr int kAhead = 4;
+    for (int k0 = 0; k0 < per / kKsCount; k0 += kAhead) {
+        double u[kAhead];
+        int pl[kAhead];
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) u[k] = i0 + (k0 + k) * kKsCount < n ? xc[i0 + (k0 + k) * kKsCount] : 0.0;
+        ks_place(spl, u, pl);
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+            const unsigned bu = ks_bucket(u[k], lo, scale, p.buckets);
+            int hu = -1;
+            for (int g = 0; g < nh; ++g) hu = huge[g] == bu ? g : hu;
+            if (i0 + (k0 + k) * kKsCount >= n || hu < 0 || (pl[k] < S && spl[pl[k]] == u[k])) continue;
+            const unsigned at0 = place[pl[k] + hu];
+            if (at0 != kKsNone) v.list()[at0 + atomicAdd(&v.taken()[pl[k] + hu], 1u)] = u[k];
+        }
+    }
+}
+
+// The largest deviation in the ranges of one component, range(k, m, r0) giving
+// the m values of the k-th and their first rank (m = 0: none to take): a wave a
+// range, dealt to the blocks in turn (a block of 16 waves on 16 candidates left
+// half the CUs idle: 20 us against 12 for 3 x 2^20 values), and the block its
+// ranges that are too large for one; each wave's maximum, in every lane.
+template <class Range>
+__device__ __forceinline__ double ks_solve_block(KsRefine& R, int count, Range&& range, double dn, double lo, double w,
+                                                 int block, int blocks) {
     constexpr int kWaves = kKsCount / 64;
     double d = 0.0;
-    bool large = false;
-    for (int k = (threadIdx.x >> 6) * blocks + block; k < ncand; k += blocks * kWaves) {
-        const int b = (int)cand[k];
-        const int64_t r0 = count[b];
-        const int m = (int)(count[b + 1] - count[b]);
-        if (m <= kKsWave) d = __builtin_fmax(d, ks_ranked(list + slot[b], m, r0, dn, lo, w, 0, 64));
-        else large = true;
-    }
-    if (__syncthreads_or(large)) {
-        for (int k = block; k < ncand; k += blocks) {
-            const int b = (int)cand[k];
-            const int64_t r0 = count[b];
-            const int m = (int)(count[b + 1] - count[b]);
-            if (m > kKsWave) d = __builtin_fmax(d, ks_refine(R, list + slot[b], m, r0, dn, lo, w));
+    const int wave = threadIdx.x >> 6;
+    // with a range for each wave none waits for one that takes long
+    const int own = count < blocks * kWaves ? kKsWave : kKsBlock;
+    if (threadIdx.x == 0) { R.nmid = 0u; R.nbig = 0u; }
+    __syncthreads();
+    for (int k = wave * blocks + block; k < count; k += blocks * kWaves) {
+        int m;
+        int64_t r0;
+        const double* l = range(k, m, r0);
+        if (m > own) {                            // at most 17,407 / 64 of a block, or 1024
+            if ((threadIdx.x & 63) == 0)
+                R.later[m > kKsBlock ? kKsCount - 1 - atomicAdd(&R.nbig, 1u) : atomicAdd(&R.nmid, 1u)] = k;
+        } else if (m > 0) {
+            d = __builtin_fmax(d, ks_ranked(l, m, r0, dn, lo, w, 0, 64));
         }
+    }
+    __syncthreads();
+    // a few of up to kKsBlock values: by all waves, one after the other (256 to 512
+    // values take a wave 4 to 8 times as long); more of them: a wave each
+    const int nmid = (int)R.nmid, nbig = (int)R.nbig;
+    const bool each = nmid > 4;
+    for (int k = each ? wave : 0; k < nmid; k += each ? kWaves : 1) {
+        int m;
+        int64_t r0;
+        const double* l = range(R.later[k], m, r0);
+        d = __builtin_fmax(d, ks_ranked(l, m, r0, dn, lo, w, each ? 0 : 64 * wave, each ? 64 : kKsCount));
+    }
+    for (int k = 0; k < nbig; ++k) {
+        int m;
+        int64_t r0;
+        const double* l = range(R.later[kKsCount - 1 - k], m, r0);
+        d = __builtin_fmax(d, ks_refine(R, l, m, r0, dn, lo, w));
     }
     return wave_max(d);
 }
 
-__global__ __launch_bounds__(kKsCount) void ks_solve(int64_t n, double lo, double w, void* ws, KsPlan p) {
+__device__ double kolmogorov_sf(double lam);
+
+__global__ __launch_bounds__(kKsCount) void ks_solve(int64_t n, double lo, double w, void* ws, KsPlan p,
+                                                     double* __restrict__ out) {
     __shared__ KsRefine R;
     const KsView v = ks_view(ws, p, blockIdx.y);
-    double d = ks_solve_block(R, v.cand(), (int)*v.ncand(), v.count(), v.slot(), v.list(), (double)n, lo, w,
-                                    blockIdx.x, gridDim.x);
+    const int ncand = (int)*v.ncand();
+    const int64_t most = ks_huge_min(n);
+    const auto range = [&](int k, int& m, int64_t& r0) -> const double* {
+        if (k < ncand) {
+            const unsigned b = v.cand()[k];
+            r0 = v.count()[b];
+            m = (int)(v.count()[b + 1] - v.count()[b]);
+            if (m > most) m = 0;                      // ks_split's
+            return v.list() + v.slot()[b];
+        }
+        const unsigned* r = v.part(0) + 3 * (k - ncand);
+        m = (int)r[0];
+        r0 = r[1];
+        return v.list() + r[2];
+    };
+    double d = ks_solve_block(R, ncand + (int)*v.nsub(), range, (double)n, lo, w, blockIdx.x, gridDim.x);
     // non-negative doubles order as their bits; one atomic a block (one a wave
     // made 1024 wait for one word)
     __syncthreads();
@@ -1108,9 +1428,14 @@ __global__ __launch_bounds__(kKsCount) void ks_solve(int64_t n, double lo, doubl
     if (threadIdx.x != 0) return;
     for (int k = 0; k < kKsCount / 64; ++k) d = __builtin_fmax(d, R.red[k]);
     if (d > 0.0) atomicMax(v.dmax(), (unsigned long long)__double_as_longlong(d));
+    // the last block has D
+    __threadfence();
+    if (atomicAdd(v.done(), 1u) != gridDim.x - 1) return;
+    __threadfence();
+    d = __longlong_as_double((long long)atomicMax(v.dmax(), 0ull));
+    out[2 * blockIdx.y] = d;
+    out[2 * blockIdx.y + 1] = kolmogorov_sf(sqrt((double)n) * d);
 }
-
-__device__ double kolmogorov_sf(double lam);
 
 // The whole test of a sample that one block counts (at most kKsPerBlock
 // values, 1024 buckets), in one launch: the tables in LDS, the candidates'
@@ -1146,7 +1471,13 @@ __global__ __launch_bounds__(kKsCount) void ks_one(int64_t n, int64_t ld, const 
             if (slot[b] != kKsNone) list[atomicAdd(&R.below[0][b], 1u)] = val[k];
         }
     __syncthreads();
-    double d = ks_solve_block(R, cand, ncand, count, slot, list, (double)n, lo, w, 0, 1);
+    const auto range = [&](int k, int& m, int64_t& r0) -> const double* {
+        const unsigned b = cand[k];
+        r0 = count[b];
+        m = (int)(count[b + 1] - count[b]);
+        return list + slot[b];
+    };
+    double d = ks_solve_block(R, ncand, range, (double)n, lo, w, 0, 1);
     if ((threadIdx.x & 63) == 0) shd[threadIdx.x >> 6] = d;
     __syncthreads();
     if (threadIdx.x != 0) return;
@@ -1195,16 +1526,15 @@ __device__ double kolmogorov_sf(double lam) {
     return p < 0.0 ? 0.0 : (p > 1.0 ? 1.0 : p);
 }
 
-// D and the p-value from `parts` partial maxima; component c's at part + c * stride
-__global__ __launch_bounds__(64) void ks_final_kernel(int64_t n, const double* __restrict__ part, int parts,
-                                                      int64_t stride, double* __restrict__ out) {
-    const double* pc = part + (int64_t)blockIdx.x * stride;
+// D and the p-value from the partial maxima
+__global__ __launch_bounds__(64) void ks_final_kernel(int64_t n, const double* __restrict__ part,
+                                                      double* __restrict__ out) {
     double d = 0.0;
-    for (int b = threadIdx.x; b < parts; b += 64) d = __builtin_fmax(d, pc[b]);
+    for (int b = threadIdx.x; b < kPart; b += 64) d = __builtin_fmax(d, part[b]);
     d = wave_max(d);
     if (threadIdx.x != 0) return;
-    out[2 * blockIdx.x] = d;
-    out[2 * blockIdx.x + 1] = kolmogorov_sf(sqrt((double)n) * d);
+    out[0] = d;
+    out[1] = kolmogorov_sf(sqrt((double)n) * d);
 }
 
 __global__ void fill_nan(double* p, int count) {
@@ -1380,12 +1710,13 @@ int pn_ks_uniform(int64_t n, int64_t ld, const double* x, int32_t ncomp, double 
                 hipLaunchKernelGGL(ks_count, dim3(p.blocks, g), dim3(kKsCount), p.buckets * sizeof(unsigned), s, n, ld,
                                    xc, lo, scale, workspace, p);
                 hipLaunchKernelGGL(ks_sum, dim3(p.buckets / kBlock, g), dim3(kBlock), 0, s, workspace, p);
-                hipLaunchKernelGGL(ks_scan, dim3(g), dim3(kKsCount), 0, s, n, workspace, p);
+                hipLaunchKernelGGL(ks_scan, dim3(g), dim3(kKsCount), 0, s, n, ld, xc, lo, scale, workspace, p);
                 hipLaunchKernelGGL(ks_collect, dim3(p.blocks, g), dim3(kKsCount), p.buckets * sizeof(unsigned), s, n,
                                    ld, xc, lo, scale, workspace, p);
-                hipLaunchKernelGGL(ks_solve, dim3(64, g), dim3(kKsCount), 0, s, n, lo, w, workspace, p);
-                hipLaunchKernelGGL(ks_final_kernel, dim3(g), dim3(64), 0, s, n, (const double*)workspace, 1,
-                                   p.bytes / 8, out + 2 * c);
+                const int per = n <= 262144 ? kKsPerBlock / 4 : kKsPerBlock;
+                hipLaunchKernelGGL(ks_split, dim3((unsigned)((n + per - 1) / per), g), dim3(kKsCount), 0, s, n, ld, xc, lo,
+                                   w, scale, per, workspace, p);
+                hipLaunchKernelGGL(ks_solve, dim3(64, g), dim3(kKsCount), 0, s, n, lo, w, workspace, p, out + 2 * c);
             }
             return launched();
         }
@@ -1401,7 +1732,7 @@ int pn_ks_uniform(int64_t n, int64_t ld, const double* x, int32_t ncomp, double 
         if (rocprim::radix_sort_keys(tmp, tmp_bytes, x + (int64_t)c * ld, sorted, (size_t)n, 0, 64, s) != hipSuccess)
             return PN_EHIP;
         hipLaunchKernelGGL(ks_kernel, dim3(kPart), dim3(kBlock), 0, s, n, sorted, lo, hi, part);
-        hipLaunchKernelGGL(ks_final_kernel, dim3(1), dim3(64), 0, s, n, part, kPart, (int64_t)0, out + 2 * c);
+        hipLaunchKernelGGL(ks_final_kernel, dim3(1), dim3(64), 0, s, n, part, out + 2 * c);
     }
     return launched();
 }
