@@ -67,16 +67,17 @@ __global__ void zero_i64(int64_t* p, int64_t count) {
         p[i] = 0;
 }
 
-// Blocks of 1024 threads count kHistPer values each (more for samples beyond
-// kHistBlocks blocks) in LDS and add their bins to the result with 64-bit
+// Blocks of 1024 threads count 4096 to 16,384 values each in LDS (more for
+// samples beyond kHistBlocks blocks) and add their bins to the result with 64-bit
 // global atomics.  Fewer values a block spread the counting over more of the
-// chip, but the atomics of all blocks meet in the same few words: 3 x 2^20
-// values take 21 / 12 / 13 us in 20 bins and 26 / 17 / 22 us in 79 x 79 with
-// 8192 / 16384 / 32768 values a block (1024 blocks of 1024 values, one copy
-// and every value corrected: 43 and 103 us).  A sample of one block is
-// stored without zeroing or atomics.
+// chip, but the atomics of all blocks meet in the same few words, so a sample
+// takes 64 blocks before they get more than 4096 values: 40,000 values in 79 x 79
+// bins take 8 / 13 us with 4096 / 16,384 values a block, 3 x 2^20 values 20 / 16
+// us, and 33 / 13 us in 20 bins (1024 blocks of 1024 values, one copy and every
+// value corrected: 43 and 103 us).  A sample of up to kHistOne values is stored
+// by one block without zeroing or atomics (5 us; a clearing launch is 3 us of 7).
 constexpr int kHistBlock = 1024;
-constexpr int kHistPer = 16384;
+constexpr int kHistOne = 8192;
 constexpr int kHistBlocks = 512;
 
 // LDS copies of a histogram, chosen so that they fit 4096 counters: lanes
@@ -89,8 +90,9 @@ int hist_copies(int nbins) {
 }
 
 unsigned hist_blocks(int64_t n) {
-    const int64_t b = (n + kHistPer - 1) / kHistPer;
-    return (unsigned)(b < 1 ? 1 : (b > kHistBlocks ? kHistBlocks : b));
+    if (n <= kHistOne) return 1;
+    const int64_t per = n / 64 < 4096 ? 4096 : (n / 64 > 16384 ? 16384 : n / 64), b = (n + per - 1) / per;
+    return (unsigned)(b > kHistBlocks ? kHistBlocks : b);
 }
 
 // The next kHistAhead values of each thread, loaded together so that their
