@@ -124,10 +124,10 @@ typedef struct pn_opts {
                               of a shape of their own, and block is not used: up to
                               16,384 inspirals in FP64, four lanes on each; above one
                               wave on each SIMD and up to 8,192 inspirals on each CU,
-                              without order or with packed, one block
-                              on each CU with a share of the inspirals, the longest of
-                              it (by the library's own estimate) first.  The results
-                              are the same bit for bit. */
+                              without order or with pn_cost_order's and packed, one
+                              block on each CU with a share of the inspirals, the longest
+                              of it (by an estimate of the library's own) first.  The
+                              results are the same bit for bit. */
     int32_t refill_min;    /* persistent: a wave refills once this many of its lanes
                               are idle (1..64) while inspirals are left, or all are;
                               0 -> 4 (each refill pass costs the whole wave, so
@@ -139,8 +139,9 @@ typedef struct pn_opts {
                               permutation of 0 .. n-1, e.g. from pn_cost_order).
                               Every output is written at the inspiral's own index,
                               so the results do not depend on the order, only the
-                              speed does.  Together with packed the order is refined
-                              (waves_per_simd above); by itself it is kept.
+                              speed does.  pn_cost_order's, together with packed, is
+                              refined (waves_per_simd above); any other is kept, and
+                              so is each without packed.
                               Entries outside [0, n) are skipped (that
                               slot integrates nothing); an index missing from the
                               array leaves its outputs unwritten.  Requires

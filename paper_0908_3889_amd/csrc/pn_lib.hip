@@ -1143,6 +1143,7 @@ __device__ __forceinline__ void list_loop(const Uni& u, unsigned long long* slot
         const LaunchDesc* d = reinterpret_cast<const LaunchDesc*>(slot + kDescOffset);
         const Io& io = d->io;
         const int64_t ld = d->u.ld, n = d->u.n;
+        if (*slot < (unsigned long long)n) return;       // the order is kept: prepare_launch
         const unsigned slots = 8 * (unsigned)((n + 8 * (int64_t)gridDim.x - 1) / (8 * (int64_t)gridDim.x));
         unsigned size = 8;
         while (size < slots) size *= 2;
@@ -1890,11 +1891,28 @@ __global__ __launch_bounds__(BLOCK) void replay_kernel(ReplayIo io, AdjUni u) {
     io.t[i] = t;
 }
 
-// Zeroes the work counter of a persistent launch and writes its launch
-// descriptor into the call's slot (one word per thread).
-__global__ void prepare_launch(unsigned long long* slot, LaunchDesc desc) {
+// Writes the launch descriptor of a call into its slot (one word per thread) and
+// sets the slot's work counter: to 0, or to n where the lists take the
+// inspirals, at which a persistent grid behind them finds none left.
+enum Lists { kNoLists, kLists, kListsIfCost };     // the last: if the order is pn_cost_order's
+__global__ void prepare_launch(unsigned long long* slot, LaunchDesc desc, Lists lists) {
     const unsigned t = threadIdx.x;
-    if (t == 0) slot[0] = 0ull;
+    unsigned long long start = lists != kNoLists ? (unsigned long long)desc.u.n : 0ull;
+    if (lists == kListsIfCost) {
+        // 64 places of the order, from the first to the last: each one's key at
+        // most the one before's (and the rounding of two compilations)
+        const int64_t n = desc.u.n, idx = desc.io.order[(n - 1) * (int64_t)t / 63];
+        const bool is = idx >= 0 && idx < n;
+        int key = 0;
+        if (is) {
+            double m1, m2, y[10];
+            fetch(desc.io, desc.u.ld, idx, y, m1, m2);
+            key = order_key(m1, m2, y, desc.u.omega_f);
+        }
+        const int before = __shfl_up(is ? key : INT32_MAX - 1, 1);
+        if (__ballot(t > 0 && is && key > before + 1) != 0) start = 0;
+    }
+    if (t == 0) slot[0] = start;
     const unsigned long long* src = reinterpret_cast<const unsigned long long*>(&desc);
     if (t < sizeof(LaunchDesc) / 8) slot[kDescOffset + t] = src[t];
 }
@@ -2065,20 +2083,13 @@ hipError_t launch_static(const Io& io, const Uni& u, int precision, hipStream_t 
     return hipGetLastError();
 }
 
-// The persistent launch on the call slot `counter`: prepare_launch zeroes the
-// slot's work counter and writes the descriptor, then the persistent grid.
+// The persistent grid on the call slot `counter`, which prepare_launch has set.
 template <int BLOCK>
 hipError_t launch_persistent(const Io& io, const Uni& u, int precision, int waves_per_simd, int cus,
                              unsigned long long* counter, hipStream_t s) {
     const bool f32 = precision == PN_PREC_FP32_SPLIT;
     const bool f32x = precision == PN_PREC_FP32_STATE;
     const bool ph = io.phase != nullptr;
-    LaunchDesc desc;
-    desc.io = io;
-    desc.u = u;
-    hipLaunchKernelGGL(prepare_launch, dim3(1), dim3(64), 0, s, counter, desc);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
     const int64_t waves_needed = (u.n + 63) / 64;
     int64_t waves = (int64_t)cus * 4 * waves_per_simd;
     if (waves > waves_needed) waves = waves_needed;
@@ -2113,12 +2124,6 @@ hipError_t launch_persistent(const Io& io, const Uni& u, int precision, int wave
 // The list launch: one block of waves_per_simd waves on each SIMD of a CU.
 hipError_t launch_list(const Io& io, const Uni& u, int precision, int cus, unsigned long long* counter,
                        hipStream_t s) {
-    LaunchDesc desc;
-    desc.io = io;
-    desc.u = u;
-    hipLaunchKernelGGL(prepare_launch, dim3(1), dim3(64), 0, s, counter, desc);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
     constexpr int B64 = 256 * kWpeF64, B32 = 256 * kWpeF32, B32S = 256 * kWpeF32S;
     const bool ph = io.phase != nullptr;
     const dim3 g((unsigned)cus);
@@ -2142,8 +2147,11 @@ hipError_t launch_list(const Io& io, const Uni& u, int precision, int cus, unsig
 // measured (1M workload's 17.5 -> 16.8 ms), at 4,194,304 no longer (34.7 -> 37.2
 // with lists of 16,384).  Their estimate ranks better than pn_cost_order's (1M workload with
 // that order: 9.0 ms from the global counter, 8.65 from the lists), whose order
-// comes with packed records; an order by itself is taken as it is (by the true
-// numbers of steps it is the better one: 8.1 ms).
+// comes with packed records: prepare_launch looks whether the order is that one
+// (64 of its places, sorted by that estimate), and any other is kept, as an order
+// without records is (by the true numbers of steps it is the better one: 8.0 ms
+// against 8.7, equal masses 4.9 against 6.1), by a persistent grid queued behind the
+// lists, which then leave at once (the grid without work costs 4 us).
 bool use_list(const Io& io, const Uni& u, int cus) {
     return !u.fixed && !u.tend && !u.tape && (!io.order || io.packed) && u.n > (int64_t)cus * 256 &&
            u.n <= (int64_t)cus * kListMax;
@@ -2284,12 +2292,18 @@ static int integrate_impl(int64_t n, int64_t ld, const double* m, const double* 
         return e == hipSuccess ? PN_OK : PN_EHIP;
     }
     const int cus = noalloc ? sd->cus : ctx->cus;
-    const bool list = !o.waves_per_simd && use_list(io, u, cus);
+    const Lists lists = o.waves_per_simd || !use_list(io, u, cus) ? kNoLists : (io.order ? kListsIfCost : kLists);
     auto launch = [&](unsigned long long* counter) {
-        hipError_t e;
-        if (list) {
+        LaunchDesc desc;
+        desc.io = io;
+        desc.u = u;
+        hipLaunchKernelGGL(prepare_launch, dim3(1), dim3(64), 0, s, counter, desc, lists);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return PN_EHIP;
+        if (lists != kNoLists) {
             e = launch_list(io, u, o.precision, cus, counter, s);
-            return e == hipSuccess ? PN_OK : PN_EHIP;
+            if (e != hipSuccess) return PN_EHIP;
+            if (lists == kLists) return PN_OK;
         }
         switch (block) {
             case 64: e = launch_persistent<64>(io, u, o.precision, wps, cus, counter, s); break;

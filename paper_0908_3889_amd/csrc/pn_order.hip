@@ -24,17 +24,11 @@
 #include <rocprim/device/device_radix_sort.hpp>
 
 #include "pn.h"
+#include "pn_cost.hpp"
 
 namespace pn_order {
 
 constexpr int kBlock = 256;
-
-// |v| sin(angle between v and the unit vector a)
-__device__ __forceinline__ double normal_part(double v0, double v1, double v2, double a0, double a1, double a2) {
-    const double vv = v0 * v0 + v1 * v1 + v2 * v2;
-    const double va = v0 * a0 + v1 * a1 + v2 * a2;
-    return __builtin_sqrt(__builtin_fmax(vv - va * va, 0.0));
-}
 
 __global__ void cost_key_kernel(int64_t n, int64_t ld, const double* __restrict__ m, const double* __restrict__ S,
                                 const double* __restrict__ L, const double* __restrict__ w0, double omega_f,
@@ -60,27 +54,8 @@ __global__ void cost_key_kernel(int64_t n, int64_t ld, const double* __restrict_
         r[6] = make_double2(0.0, 0.0);
         r[7] = make_double2(0.0, 0.0);
     }
-    double k = 0.0;       // inputs the integrator refuses, or that finish at once: last
-    if (m1 > 0.0 && m2 > 0.0 && w > 0.0 && (omega_f <= 0.0 || w < omega_f)) {
-        const double M = m1 + m2;
-        const double eta = m1 * m2 / (M * M);
-        const double lmag = eta * pow(M, 5.0 / 3.0) * pow(w, -1.0 / 3.0);
-        const double j0 = lmag * l0 + s10 + s20, j1 = lmag * l1 + s11 + s21, j2 = lmag * l2 + s12 + s22;
-        const double jn = __builtin_sqrt(j0 * j0 + j1 * j1 + j2 * j2);
-        const double span = (omega_f > 0.0 ? 1.0 / w - 1.0 / omega_f : 1.0 / w) / M;
-        if (jn > 0.0 && __builtin_isfinite(jn) && __builtin_isfinite(span)) {
-            const double a0 = j0 / jn, a1 = j1 / jn, a2 = j2 / jn;
-            const double k1 = (4.0 + 3.0 * m2 / m1) * pow(normal_part(s10, s11, s12, a0, a1, a2), 0.2);
-            const double k2 = (4.0 + 3.0 * m1 / m2) * pow(normal_part(s20, s21, s22, a0, a1, a2), 0.2);
-            const double kk = span * __builtin_fmax(k1, k2);
-            if (__builtin_isfinite(kk)) k = kk;
-        }
-    }
-    // positive floats order as their bit patterns do; the upper 16 bits
-    // (sign, exponent and 7 mantissa bits) rank the keys to within 1 %, far
-    // finer than the estimate itself, and halve the sort's passes
-    const float kf = (float)k;
-    key[i] = kf > 0.0f ? (uint16_t)(__float_as_uint(kf) >> 16) : (uint16_t)0;
+    const double y[10] = {w, s10, s11, s12, s20, s21, s22, l0, l1, l2};
+    key[i] = pn::order_key(m1, m2, y, omega_f);
 }
 
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
