@@ -127,7 +127,14 @@ typedef struct pn_opts {
                               without order or with pn_cost_order's and packed, one
                               block on each CU with a share of the inspirals, the longest
                               of it (by an estimate of the library's own) first.  The
-                              results are the same bit for bit. */
+                              results are the same bit for bit.  Those shapes, and
+                              the parts of pn_integrate_adjoint, take the chip for one
+                              call: four lanes issue 2.8 times the instructions of one.
+                              Programs that keep several small batches in flight on
+                              streams of their own set waves_per_simd (2 in FP64), and
+                              the batches share the SIMDs (16,384 inspirals on each of
+                              four streams: 0.21 ms a batch, at 0 0.39; one stream alone
+                              0.53 and 0.45). */
     int32_t refill_min;    /* persistent: a wave refills once this many of its lanes
                               are idle (1..64) while inspirals are left, or all are;
                               0 -> 4 (each refill pass costs the whole wave, so
@@ -420,7 +427,8 @@ int pn_integrate_record(int64_t n, int64_t ld,
  *   workspace: device buffer of pn_adjoint_workspace_bytes(n, K) bytes: the
  *     replayed states of one checkpoint segment per inspiral (11 n K doubles,
  *     which is also enough), and, for small n, of several parts of each
- *     inspiral that are then reversed side by side;
+ *     inspiral that are then reversed side by side (not with
+ *     opt->waves_per_simd set, nor in the smaller workspace);
  *   order: optional device permutation of [0, n) giving the order in which
  *     inspirals are assigned to lanes (e.g. sorted by step count, so that a
  *     wave's lanes run segments of equal length); NULL = identity.  Entries

@@ -2466,7 +2466,11 @@ int pn_integrate_adjoint(int64_t n, int64_t ld, const double* m, double omega_f,
     AdjIo io;
     io.m = m; io.status = status; io.gy = gy_final; io.gt = gt_final;
     io.g_m = g_m; io.g_S0 = g_S0; io.g_L0 = g_L0; io.g_w0 = g_omega0; io.order = order;
-    const int parts = adjoint_parts(n, ckpt_every, ws_bytes < kPartsBytes ? ws_bytes : kPartsBytes);
+    // (a caller who sets waves_per_simd shares the chip: the parts are 11 times
+    // the work, and four streams of 3,000 inspirals took 0.66 ms a batch, one lane
+    // an inspiral 0.41)
+    const int parts = opt && opt->waves_per_simd
+                          ? 1 : adjoint_parts(n, ckpt_every, ws_bytes < kPartsBytes ? ws_bytes : kPartsBytes);
     if (parts > 1) {
         AdjParts p;
         p.parts = parts;
