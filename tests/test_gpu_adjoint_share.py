@@ -1,6 +1,7 @@
 """Gradients of small batches in a launch that leaves SIMDs to other streams: with
 waves_per_simd set, one lane reverses each inspiral's whole run, as in a workspace
-of one segment per inspiral."""
+of one segment per inspiral; and the workspaces between that size and the full one,
+whose size is the number of parts."""
 import ctypes as C
 
 import numpy as np
@@ -10,6 +11,8 @@ from paper_0908_3889_amd import population as P
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
+
+RTOL = 1e-9      # of the largest component: test_gpu_adjoint_parts.py
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -57,3 +60,22 @@ def test_waves_per_simd_reverses_the_whole_run(n, K):
     b = _in(n * K * 11, m, omega_f, rec, gy)
     for k in a:
         assert torch.equal(a[k], b[k]), k
+
+
+# parts c take c segments of 11 n K doubles, and 24 n (1 + 11 (c - 1)) of what they
+# hand on: those sizes, and a double fewer
+@pytest.mark.parametrize("n,K", [(5, 3), (130, 16), (1000, 16)])
+def test_workspaces_of_two_parts_and_more(n, K):
+    from paper_0908_3889_amd import _lib
+    args = _record(n, K)
+    whole = _in(n * K * 11, *args)
+    full = int(_lib.load().pn_adjoint_workspace_bytes(n, K)) // 8
+    size = lambda c: c * n * K * 11 + 24 * n * (1 + 11 * (c - 1))
+    most = max(c for c in range(1, 17) if size(c) <= full)
+    assert most > 1 and size(most) == full
+    for c in range(2, most + 1):
+        for words in (size(c) - 1, size(c)):
+            got = _in(words, *args)
+            for k in got:
+                x, y = (v.cpu().numpy().reshape(-1, n) for v in (got[k], whole[k]))
+                assert (np.abs(x - y) <= RTOL * np.abs(y).max(0)).all(), (c, words, k)
