@@ -422,17 +422,19 @@ class PNIntegrate(torch.autograd.Function):
             if not bool((rec["status"] == _lib.PN_ST_TAPE_FULL).any()):
                 break
             cap *= 2
-        ctx.rec = rec
+        # not y and t: their graph node holds ctx, and the tape would stay until a
+        # pass of the cycle collector
+        ctx.save_for_backward(m, rec["tape"])
+        ctx.rec = {k: rec[k] for k in ("status", "steps", "cap_steps", "ckpt_every")}
         ctx.omega_f = float(omega_f)
-        ctx.save_for_backward(m)
         ctx.mark_non_differentiable(rec["status"], rec["steps"])
         return rec["y"], rec["t"], rec["status"], rec["steps"]
 
     @staticmethod
     def backward(ctx, gy, gt, _gs, _gst):
-        (m,) = ctx.saved_tensors
-        rec = ctx.rec
-        gy = torch.zeros_like(rec["y"]) if gy is None else gy.contiguous()
+        m, tape = ctx.saved_tensors
+        rec = {"tape": tape, **ctx.rec}
+        gy = m.new_zeros((10, m.shape[1])) if gy is None else gy.contiguous()
         gt = None if gt is None else gt.contiguous()
         order = torch.argsort(rec["steps"][0], descending=True).to(torch.int32)
         g = pn_integrate_adjoint(m, ctx.omega_f, rec, gy, gt, order=order)
