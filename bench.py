@@ -172,6 +172,20 @@ def measured_traffic(kernel: str, workload: str):
     return _profile_field(os.path.join(PROFILES, f"hbm_{kernel}_{workload}.txt"), "hbm_bytes_per_launch")
 
 
+def launched_kernel(n: int, cus: int, precision: str, schedule: str = "persistent", phase: bool = False,
+                    waves_per_simd: int = 0, block: int = 0, order: bool = False, packed: bool = False):
+    """The kernel that an adaptive integration to omega_f runs, and its threads a
+    block (the rule of pn_opts.waves_per_simd; `order` is pn_cost_order's)."""
+    kernel = f"integrate_{schedule}_{ {'fp64': 'f64', 'fp32split': 'f32s', 'fp32': 'f32x'}[precision] }"
+    block = block or 256
+    if schedule == "persistent" and not waves_per_simd:
+        if precision == "fp64" and n <= 16384:
+            kernel, block = "integrate_quad_f64", 256
+        elif 256 * cus < n <= 8192 * cus and (packed or not order):
+            kernel, block = kernel.replace("persistent", "list"), 512 if precision == "fp64" else 768
+    return kernel + ("_phase" if phase else ""), block
+
+
 def kernel_resources(kernel: str, block: int):
     """VGPRs, AGPRs, spills, scratch, LDS and occupancy of the timed kernel
     instantiation, from the compiler's resource report of the build."""
@@ -184,9 +198,11 @@ def kernel_resources(kernel: str, block: int):
             "integrate_static_f32x": f"integrate_static_f32xILi{block}E"}.get(kernel)
     if kernel.endswith("_phase"):
         want = f"{kernel}ILi{block}E"
+    base = kernel.removesuffix("_phase")
     if kernel.startswith("integrate_list_"):
-        base = kernel.removesuffix("_phase")
-        want = f"{base}ILi{512 if base.endswith('f64') else 768}ELb{int(base != kernel)}E"
+        want = f"{base}ILi{block}ELb{int(base != kernel)}E"
+    if kernel.startswith("integrate_quad_"):
+        want = f"{base}ILi{block}ELb0ELb{int(base != kernel)}E"
     for name, fields in build.resource_usage().items():
         if want and want in name:
             keep = ("VGPRs", "AGPRs", "ScratchSize [bytes/lane]", "Occupancy [waves/SIMD]", "VGPRs Spill",
@@ -706,17 +722,12 @@ def main() -> int:
     peak = FP64_VECTOR_PEAK_TFLOPS if precision == "fp64" else FP32_VECTOR_PEAK_TFLOPS
     n = pop["n"]
     value = n * args.steps / wall
-    kernel = (f"integrate_{args.schedule}_{ {'fp64': 'f64', 'fp32split': 'f32s', 'fp32': 'f32x'}[precision] }"
-              + ("_phase" if args.phase else ""))
-    # the sizes at which each CU takes a share of the inspirals, longest first
-    # (a share holds 8,192; up to one wave on each SIMD the lists are not used)
     cus = torch.cuda.get_device_properties(0).multi_processor_count
-    lists = (args.schedule == "persistent" and not opts.waves_per_simd and 256 * cus < n <= 8192 * cus)
-    if lists:
-        kernel = kernel.replace("persistent", "list")
+    kernel, block = launched_kernel(n, cus, precision, args.schedule, args.phase, opts.waves_per_simd, opts.block,
+                                    cost_order, cost_order)
     traffic = measured_traffic(kernel, w.name)
     counter_flop = measured_counter_flop(kernel, w.name)
-    resources = kernel_resources(kernel, opts.block or 256)
+    resources = kernel_resources(kernel, block)
     res = {
         "metric": METRIC,
         "value": value,
@@ -746,9 +757,12 @@ def main() -> int:
                      / (avg_ms * 1e-3) / 1e12 / peak,
                      "counter_achieved": (counter_flop / (avg_ms * 1e-3) / 1e12) if counter_flop else None,
                      "counter_frac": (counter_flop / (avg_ms * 1e-3) / 1e12 / peak) if counter_flop else None},
-        "kernel": kernel,
+        # the schedule's kernel; `launch` has the one that ran (small FP64 batches run
+        # four lanes on an inspiral)
+        "kernel": kernel.replace("_quad_", "_persistent_"),
         "kernel_resources": resources,
-        "launch": {"block": opts.block or 256, "refill_min": opts.refill_min or 4,
+        "launch": {"kernel": kernel, "block": block,
+                   "refill_min": None if "_quad_" in kernel else opts.refill_min or 4,
                    "waves_per_simd": opts.waves_per_simd or None, "autotuned": tuned},
         "kernel_ms": avg_ms,
         "step_ms_events": step_ms,
