@@ -17,6 +17,7 @@
 #include <hip/hip_runtime.h>
 
 #include <atomic>
+#include <cstddef>
 #include <cstring>
 #include <mutex>
 
@@ -1143,7 +1144,6 @@ __device__ __forceinline__ void list_loop(const Uni& u, unsigned long long* slot
         const LaunchDesc* d = reinterpret_cast<const LaunchDesc*>(slot + kDescOffset);
         const Io& io = d->io;
         const int64_t ld = d->u.ld, n = d->u.n;
-        if (*slot < (unsigned long long)n) return;       // the order is kept: prepare_launch
         const unsigned slots = 8 * (unsigned)((n + 8 * (int64_t)gridDim.x - 1) / (8 * (int64_t)gridDim.x));
         unsigned size = 8;
         while (size < slots) size *= 2;
@@ -1198,6 +1198,30 @@ template <int BLOCK, bool PHASE>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(kWpeF32S)))
 void integrate_list_f32x(Uni u, unsigned long long* slot) {
     list_loop<F32State<PHASE, false>, BLOCK>(u, slot);
+}
+
+// The global counter behind the lists, for an order that they do not take over;
+// where they do, prepare_launch has set the counter to n, and these leave on
+// reading it (3 us; 2,000 waves that each take their turn at it need 40).
+template <int BLOCK, bool PHASE>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(kWpeF64)))
+void integrate_kept_f64(Uni u, unsigned long long* slot) {
+    if (*slot >= (unsigned long long)u.n) return;
+    persistent_loop<F64<false, PHASE, false>>(u, slot, HandAll{slot});
+}
+
+template <int BLOCK, bool PHASE>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(kWpeF32)))
+void integrate_kept_f32s(Uni u, unsigned long long* slot) {
+    if (*slot >= (unsigned long long)u.n) return;
+    persistent_loop<F32Split<PHASE, false>>(u, slot, HandAll{slot});
+}
+
+template <int BLOCK, bool PHASE>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(kWpeF32S)))
+void integrate_kept_f32x(Uni u, unsigned long long* slot) {
+    if (*slot >= (unsigned long long)u.n) return;
+    persistent_loop<F32State<PHASE, false>>(u, slot, HandAll{slot});
 }
 
 template <int BLOCK, bool RECORD>
@@ -1673,7 +1697,7 @@ __global__ __launch_bounds__(BLOCK) void adjoint_kernel(AdjIo io, AdjUni u) {
 // gradient; adjoint_join then multiplies the parts' matrices onto it.  That is
 // 11 times the work on lanes that were idle: the time is the chain of steps of
 // one part instead of the whole run (1,000 inspirals, K = 16: one part 1.47
-// ms, five 0.46 ms).
+// ms, six 0.46 ms).
 // ---------------------------------------------------------------------------
 constexpr int kSeeds = 11;                 // lambda's 10 components and dL/dt
 constexpr int kSeedOut = 10 + NROW;        // lambda at the part's start, and the row adjoint
@@ -1893,7 +1917,10 @@ __global__ __launch_bounds__(BLOCK) void replay_kernel(ReplayIo io, AdjUni u) {
 
 // Writes the launch descriptor of a call into its slot (one word per thread) and
 // sets the slot's work counter: to 0, or to n where the lists take the
-// inspirals, at which a persistent grid behind them finds none left.
+// inspirals, at which a persistent grid behind them finds none left.  Where they
+// do not, the descriptor's n, which only they read, is 0, and their lists are
+// empty (a test of their own moved their steps to a slower place: FP32-split of
+// 2^20 inspirals 5.66 -> 5.75 ms).
 enum Lists { kNoLists, kLists, kListsIfCost };     // the last: if the order is pn_cost_order's
 __global__ void prepare_launch(unsigned long long* slot, LaunchDesc desc, Lists lists) {
     const unsigned t = threadIdx.x;
@@ -1914,7 +1941,8 @@ __global__ void prepare_launch(unsigned long long* slot, LaunchDesc desc, Lists 
     }
     if (t == 0) slot[0] = start;
     const unsigned long long* src = reinterpret_cast<const unsigned long long*>(&desc);
-    if (t < sizeof(LaunchDesc) / 8) slot[kDescOffset + t] = src[t];
+    const bool none = lists == kListsIfCost && start == 0 && t == (offsetof(LaunchDesc, u) + offsetof(Uni, n)) / 8;
+    if (t < sizeof(LaunchDesc) / 8) slot[kDescOffset + t] = none ? 0ull : src[t];
 }
 
 __global__ void rhs_kernel(int64_t n, int64_t ld, const double* __restrict__ m, const double* __restrict__ y,
@@ -2121,21 +2149,26 @@ hipError_t launch_persistent(const Io& io, const Uni& u, int precision, int wave
     return hipGetLastError();
 }
 
-// The list launch: one block of waves_per_simd waves on each SIMD of a CU.
-hipError_t launch_list(const Io& io, const Uni& u, int precision, int cus, unsigned long long* counter,
+// The list launch: one block of waves_per_simd waves on each SIMD of a CU; with
+// `kept`, behind it the persistent grid for an order that the lists leave.
+hipError_t launch_list(const Io& io, const Uni& u, int precision, bool kept, int cus, unsigned long long* counter,
                        hipStream_t s) {
     constexpr int B64 = 256 * kWpeF64, B32 = 256 * kWpeF32, B32S = 256 * kWpeF32S;
+    const dim3 g((unsigned)cus), b(256);
+    auto both = [&](auto list, unsigned block, auto behind, int waves) {
+        hipLaunchKernelGGL(list, g, dim3(block), 0, s, u, counter);
+        if (kept) hipLaunchKernelGGL(behind, dim3((unsigned)(cus * waves)), b, 0, s, u, counter);
+    };
     const bool ph = io.phase != nullptr;
-    const dim3 g((unsigned)cus);
     if (precision == PN_PREC_FP32_STATE) {
-        if (ph) hipLaunchKernelGGL((integrate_list_f32x<B32S, true>), g, dim3(B32S), 0, s, u, counter);
-        else hipLaunchKernelGGL((integrate_list_f32x<B32S, false>), g, dim3(B32S), 0, s, u, counter);
+        if (ph) both(integrate_list_f32x<B32S, true>, B32S, integrate_kept_f32x<256, true>, kWpeF32S);
+        else both(integrate_list_f32x<B32S, false>, B32S, integrate_kept_f32x<256, false>, kWpeF32S);
     } else if (precision == PN_PREC_FP32_SPLIT) {
-        if (ph) hipLaunchKernelGGL((integrate_list_f32s<B32, true>), g, dim3(B32), 0, s, u, counter);
-        else hipLaunchKernelGGL((integrate_list_f32s<B32, false>), g, dim3(B32), 0, s, u, counter);
+        if (ph) both(integrate_list_f32s<B32, true>, B32, integrate_kept_f32s<256, true>, kWpeF32);
+        else both(integrate_list_f32s<B32, false>, B32, integrate_kept_f32s<256, false>, kWpeF32);
     } else {
-        if (ph) hipLaunchKernelGGL((integrate_list_f64<B64, true>), g, dim3(B64), 0, s, u, counter);
-        else hipLaunchKernelGGL((integrate_list_f64<B64, false>), g, dim3(B64), 0, s, u, counter);
+        if (ph) both(integrate_list_f64<B64, true>, B64, integrate_kept_f64<256, true>, kWpeF64);
+        else both(integrate_list_f64<B64, false>, B64, integrate_kept_f64<256, false>, kWpeF64);
     }
     return hipGetLastError();
 }
@@ -2151,7 +2184,7 @@ hipError_t launch_list(const Io& io, const Uni& u, int precision, int cus, unsig
 // (64 of its places, sorted by that estimate), and any other is kept, as an order
 // without records is (by the true numbers of steps it is the better one: 8.0 ms
 // against 8.7, equal masses 4.9 against 6.1), by a persistent grid queued behind the
-// lists, which then leave at once (the grid without work costs 4 us).
+// lists, which are then empty.
 bool use_list(const Io& io, const Uni& u, int cus) {
     return !u.fixed && !u.tend && !u.tape && (!io.order || io.packed) && u.n > (int64_t)cus * 256 &&
            u.n <= (int64_t)cus * kListMax;
@@ -2301,9 +2334,8 @@ static int integrate_impl(int64_t n, int64_t ld, const double* m, const double* 
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return PN_EHIP;
         if (lists != kNoLists) {
-            e = launch_list(io, u, o.precision, cus, counter, s);
-            if (e != hipSuccess) return PN_EHIP;
-            if (lists == kLists) return PN_OK;
+            e = launch_list(io, u, o.precision, lists == kListsIfCost, cus, counter, s);
+            return e == hipSuccess ? PN_OK : PN_EHIP;
         }
         switch (block) {
             case 64: e = launch_persistent<64>(io, u, o.precision, wps, cus, counter, s); break;

@@ -22,7 +22,8 @@ def _resources(pattern):
     ("integrate_list_f64ILi512ELb0E", 2, 12), ("integrate_list_f64ILi512ELb1E", 2, 20),
     ("integrate_list_f32sILi768ELb0E", 3, 0), ("integrate_list_f32sILi768ELb1E", 3, 0),
     ("integrate_list_f32xILi768ELb0E", 3, 0), ("integrate_list_f32xILi768ELb1E", 3, 0),
-    ("integrate_quad_f64ILi256ELb0ELb0E", 1, 0), ("integrate_quad_f64ILi256ELb0ELb1E", 1, 0),
+    ("integrate_kept_f64ILi256ELb0E", 2, 12), ("integrate_kept_f32sILi256ELb0E", 3, 0),
+    ("integrate_kept_f32xILi256ELb0E", 3, 0), ("integrate_quad_f64ILi256ELb0ELb0E", 1, 0), ("integrate_quad_f64ILi256ELb0ELb1E", 1, 0),
     ("integrate_quad_f64ILi256ELb1ELb0E", 1, 0), ("adjoint_parts_kernel", 1, 0)])
 def test_integration_kernels_keep_their_budget(kernel, waves, scratch):
     for name, r in _resources(kernel):
