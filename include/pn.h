@@ -289,7 +289,7 @@ int pn_check_finish(pn_check* handle, const double* y_gpu, const int32_t* steps_
  * counter and launch descriptor), one copy per device, held until the
  * process ends; its size does not depend on n, so every n that pn_integrate
  * accepts (0 <= n <= ld <= PN_MAX_N) fits, and larger n is PN_EINVAL.  The
- * counter is cleared by a kernel on `stream` at the start of each call.
+ * counter is set by a kernel on `stream` at the start of each call.
  * Every pn_integrate_noalloc call on a device shares that array: calls on one
  * stream are ordered and safe, but calls that overlap on one device (several
  * streams or threads without ordering between them, or a captured graph
@@ -507,9 +507,9 @@ int pn_histogram2d(int64_t n, int64_t ld, const double* x, const double* y, int3
 /*
  * pn_pearson -- for each component pair (x[c], y[c]): out[c][0..4] = mean x,
  * mean y, standard deviation of x and of y (with 1/(n-1)), and the Pearson
- * product-moment coefficient r (Sec. V), from two passes (means, then
- * centred sums).  workspace: device buffer of pn_stats_workspace_bytes(n,
- * ncomp, 0) bytes.  n = 1 gives NaN deviations and r.
+ * product-moment coefficient r (Sec. V), from sums centred on the mean (of
+ * chunks, and combined, above 16,384 values).  workspace: device buffer of
+ * pn_stats_workspace_bytes(n, ncomp, 0) bytes.  n = 1 gives NaN deviations and r.
  */
 int pn_pearson(int64_t n, int64_t ld, const double* x, const double* y, int32_t ncomp, double* out,
                void* workspace, size_t ws_bytes, void* stream);
@@ -534,7 +534,8 @@ int pn_kde(int64_t n, int64_t ld, const double* x, int32_t ncomp, const double* 
  * distribution.  The values must not be NaN.  workspace:
  * pn_ks_workspace_bytes(n) bytes: the larger of a sorted copy with the sort's
  * scratch and, up to 2^22 values, three components' bucket counts and
- * candidates (less than that but enough for the sort is accepted, and sorts).
+ * candidates (less than that but enough for the sort is accepted: fewer
+ * components are then tested side by side, or sorted).
  */
 size_t pn_ks_workspace_bytes(int64_t n);
 int pn_ks_uniform(int64_t n, int64_t ld, const double* x, int32_t ncomp, double lo, double hi, double* out,

@@ -3,9 +3,11 @@
 // Gaussian kernel density estimator with Silverman's bandwidth, and the
 // Kolmogorov-Smirnov statistic against the uniform law.
 //
-// Every reduction runs over a fixed grid of kPart partial results combined
-// in a fixed order, so results do not depend on the device's size or on
-// scheduling.  Histogram counts use integer atomics (order-free).
+// The number of partial sums of a reduction follows from the sizes of the call
+// alone (at most kPart a component, of which the workspaces have room), and they
+// are combined in a fixed order, so results do not depend on the device's size or
+// on scheduling.  Histogram counts use integer atomics (order-free); the K-S
+// statistic is a maximum.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -22,7 +24,7 @@ int device_ready();   // pn_lib.hip: PN_OK when a gfx950 device is current
 namespace {
 
 constexpr int kBlock = 256;
-constexpr int kPart = 512;          // partial results per component
+constexpr int kPart = 512;          // most partial results per component
 constexpr int kMaxComp = 16;
 
 // ---------------------------------------------------------------------------
@@ -583,11 +585,12 @@ __global__ __launch_bounds__(kBlock) void kde_final_kernel(int64_t n, const doub
 }
 
 // Partial sums per component: enough blocks to fill the chip four deep (the
-// blocks of a CU that fit its LDS), no more than one chunk of 64 points a
-// wave needs; from the sizes alone, so that results do not depend on the device.
+// blocks of a CU that fit its LDS), no more than give each wave two chunks of
+// points; from the sizes alone, so that results do not depend on the device.
 int kde_parts(int64_t n, int ncomp, int tiles) {
     const int64_t fill = 1024 / ((int64_t)ncomp * tiles);
-    const int64_t need = ((n + 63) / 64 + kBlock / 64 - 1) / (kBlock / 64);
+    const int64_t two = (n + 2 * kKdePoints - 1) / (2 * kKdePoints);
+    const int64_t need = (two + kBlock / 64 - 1) / (kBlock / 64);
     int64_t p = need < fill ? need : fill;
     p = p < 16 ? (need < 16 ? need : 16) : p;
     return (int)(p > kPart ? kPart : p);
