@@ -9,7 +9,8 @@
 // permutations (DPP).  The stage sums, the error estimate and the norm's
 // scales are a third of the one-lane kernel's.  Every number is formed by the
 // same operations in the same order as there, so the results are the same
-// bit for bit.
+// bit for bit; a step whose fast path ends with a NaN norm is tried again with
+// what the fast path leaves out of that (rhs_quad).
 //
 // Included by pn_lib.hip after the FP64 lane.
 #pragma once
@@ -59,6 +60,10 @@ __device__ __forceinline__ void make_poly(PolyQ& p) {
     for (int i = 0; i < 7; ++i) { p.lg[i] = lg[i]; keep(p.lg[i]); }
 }
 
+// Growth of omega at the derivative of a step's start up to which the fast path
+// is tried (omega grows faster than linearly; the polynomials reach 1/16).
+constexpr double kQuadRange = 0.05;
+
 struct LaneQ {
     double v[3];       // own vector: S1, S2, L_hat, or (omega, 0, 0)
     double k1[3];      // its derivative along the step's variable
@@ -66,6 +71,7 @@ struct LaneQ {
     double kw;         // k1 of omega, on every lane
     double lnv, x, dt1, t, h;
     double phase;
+    double range;      // a step to more than (1 + range) omega takes the general path
     RowQ r;
     int64_t idx;
     int acc, rej, nt;
@@ -77,10 +83,16 @@ struct LaneQ {
 // used.  The operations are rhs_at's.  FAST: the polynomials of the cube root
 // and the log alone; `far` is set where the stage point is too far from the
 // step's base for them.  Otherwise such lanes take them in full.
-template <bool FAST>
+// Lanes 0 and 1 add 0 times lane 2's sum to their derivative and lane 2 a zero
+// Omega x L_hat to its own, which saves selects: nothing but a sign of zero for
+// finite numbers, a NaN where the other factor is infinite.  At a stage point
+// that is as good, the candidate is then not finite; a candidate far past
+// omega_f may be, and its infinite derivative means a rejected step.  EXACT:
+// the selects.
+template <bool FAST, bool EXACT = false>
 __device__ __forceinline__ double rhs_quad(const RowQ& r, const PolyQ& pc, const TermConsts& tc, const LogBase& lb,
                                            const double (&Y)[3], double (&d)[3], double& ws, double& kws, double& xo,
-                                           bool lane3, bool& far) {
+                                           int lane, bool& far) {
     const double w = quad_perm<kQ3>(Y[0]);
     const double u = (w - lb.w) * lb.iw;
     double q = pc.cb[0];
@@ -139,9 +151,10 @@ __device__ __forceinline__ double rhs_quad(const RowQ& r, const PolyQ& pc, const
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
         const double s = quad_perm<kQ0>(d[i]) + quad_perm<kQ1>(d[i]);
-        d[i] = __builtin_fma(qx, s, d[i]);
+        if (EXACT) d[i] = lane < 2 ? d[i] : qx * s;
+        else d[i] = __builtin_fma(qx, s, d[i]);
     }
-    d[0] = lane3 ? dw : d[0];
+    d[0] = lane == 3 ? dw : d[0];
     kws = quad_perm<kQ3>(dw);
     ws = w;
     xo = x;
@@ -205,6 +218,7 @@ struct QuadF64 {
         L.h = u.h0;
         L.dt1 = 1.0;
         L.phase = 0.0;
+        L.range = kQuadRange;
         L.r.M = row[R_M]; L.r.C2 = row[R_C2]; L.r.SO1 = row[R_SO1]; L.r.SO2 = row[R_SO2]; L.r.C4 = row[R_C4];
         L.r.SSD = row[R_SSD]; L.r.C5 = row[R_C5]; L.r.C6 = row[R_C6]; L.r.C7 = row[R_C7]; L.r.K = row[R_K];
         L.r.G = q == 0 ? row[R_G1] : (q == 1 ? row[R_G2] : 0.0);
@@ -305,14 +319,14 @@ struct QuadF64 {
             const double c1 = h * A21;
 #pragma unroll
             for (int i = 0; i < 3; ++i) Y[i] = __builtin_fma(c1, k1[i], y[i]);
-            rhs_quad<FAST>(L.r, pc, u.tc, lb, Y, k2, ws, kws, x7, lane3, far);
+            rhs_quad<FAST>(L.r, pc, u.tc, lb, Y, k2, ws, kws, x7, q, far);
             if (!FAST) to_omega_quad(k2, kws, dtj, om, lane3);
         }
         {
             const double c1 = h * A31, c2 = h * A32;
 #pragma unroll
             for (int i = 0; i < 3; ++i) Y[i] = __builtin_fma(c2, k2[i], __builtin_fma(c1, k1[i], y[i]));
-            rhs_quad<FAST>(L.r, pc, u.tc, lb, Y, k3, ws, kws, x7, lane3, far);
+            rhs_quad<FAST>(L.r, pc, u.tc, lb, Y, k3, ws, kws, x7, q, far);
             if (!FAST) { to_omega_quad(k3, kws, dtj, om, lane3); dts = __builtin_fma(B3, dtj, dts); }
             if (PHASE) ps = __builtin_fma(B3, ws * dtj, ps);
         }
@@ -321,7 +335,7 @@ struct QuadF64 {
 #pragma unroll
             for (int i = 0; i < 3; ++i)
                 Y[i] = __builtin_fma(c3, k3[i], __builtin_fma(c2, k2[i], __builtin_fma(c1, k1[i], y[i])));
-            rhs_quad<FAST>(L.r, pc, u.tc, lb, Y, k4, ws, kws, x7, lane3, far);
+            rhs_quad<FAST>(L.r, pc, u.tc, lb, Y, k4, ws, kws, x7, q, far);
             if (!FAST) { to_omega_quad(k4, kws, dtj, om, lane3); dts = __builtin_fma(B4, dtj, dts); }
             if (PHASE) ps = __builtin_fma(B4, ws * dtj, ps);
         }
@@ -331,7 +345,7 @@ struct QuadF64 {
             for (int i = 0; i < 3; ++i)
                 Y[i] = __builtin_fma(c4, k4[i], __builtin_fma(c3, k3[i],
                        __builtin_fma(c2, k2[i], __builtin_fma(c1, k1[i], y[i]))));
-            rhs_quad<FAST>(L.r, pc, u.tc, lb, Y, k5, ws, kws, x7, lane3, far);
+            rhs_quad<FAST>(L.r, pc, u.tc, lb, Y, k5, ws, kws, x7, q, far);
             if (!FAST) { to_omega_quad(k5, kws, dtj, om, lane3); dts = __builtin_fma(B5, dtj, dts); }
             if (PHASE) ps = __builtin_fma(B5, ws * dtj, ps);
         }
@@ -341,7 +355,7 @@ struct QuadF64 {
             for (int i = 0; i < 3; ++i)
                 Y[i] = __builtin_fma(c5, k5[i], __builtin_fma(c4, k4[i], __builtin_fma(c3, k3[i],
                        __builtin_fma(c2, k2[i], __builtin_fma(c1, k1[i], y[i])))));
-            rhs_quad<FAST>(L.r, pc, u.tc, lb, Y, k6, ws, kws, x7, lane3, far);
+            rhs_quad<FAST>(L.r, pc, u.tc, lb, Y, k6, ws, kws, x7, q, far);
             if (!FAST) { to_omega_quad(k6, kws, dtj, om, lane3); dts = __builtin_fma(B6, dtj, dts); }
             if (PHASE) ps = __builtin_fma(B6, ws * dtj, ps);
         }
@@ -356,7 +370,7 @@ struct QuadF64 {
                        __builtin_fma(E3, k3[i], E1 * k1[i]))));
             }
         }
-        T.lnv = rhs_quad<FAST>(L.r, pc, u.tc, lb, T.Y, T.k7, T.ws, T.kws, T.x, lane3, far);
+        T.lnv = rhs_quad<FAST, !FAST>(L.r, pc, u.tc, lb, T.Y, T.k7, T.ws, T.kws, T.x, q, far);
         T.dt7 = 1.0;
         if (!FAST) to_omega_quad(T.k7, T.kws, T.dt7, om, lane3);
 #pragma unroll
@@ -369,7 +383,10 @@ struct QuadF64 {
         T.far = far;
     }
 
-    // One attempted step; as F64::step.
+    // One attempted step; as F64::step.  A NaN norm on the fast path leaves
+    // the inspiral where it was and its next step to the general path, by a
+    // range below any step's (leaving the fast path for it within the step
+    // would make that branch wait for the norm).
     static __device__ __forceinline__ int step(const Uni& u, const PolyQ& pc, LaneQ& L, bool active, bool any_w, int q) {
         const bool lane3 = q == 3;
         int st = 0;
@@ -386,9 +403,8 @@ struct QuadF64 {
             h = last ? remain : L.h;
             h = active ? h : 0.0;
         }
-        // a step expected to leave the polynomials' range (omega grows faster
-        // than linearly: 0.05 at the derivative of its start) is not tried twice
-        bool slow = any_w || __ballot(h * L.kw > 0.05 * L.w) != 0;
+        // a step expected to leave the polynomials' range is not tried twice
+        bool slow = any_w || __ballot(h * L.kw > L.range * L.w) != 0;
         if (__builtin_expect(!slow, 1)) {
             attempt<true>(u, pc, L, h, q, T);
             slow = __ballot(T.far) != 0;
@@ -400,11 +416,12 @@ struct QuadF64 {
             f = quad_perm<kQ0>(f) & quad_perm<kQ1>(f) & quad_perm<kQ2>(f) & quad_perm<kQ3>(f);
             fin = f != 0;
         }
-        fin = fin && !__builtin_isnan(T.z);
         const double z = T.z, ws = T.ws;
+        fin = fin && !__builtin_isnan(z);
+        L.range = go && !fin ? -1.0 : kQuadRange;
 
         // as control()
-        if (go && !fin) st = PN_ST_NONFINITE;
+        if (go && !fin && slow) st = PN_ST_NONFINITE;
         const bool ok = go && fin;
         const bool acc = ok && z <= Z_ACCEPT;
         const bool to_w = acc && !L.omega_mode && ws > u.omega_f;
@@ -481,6 +498,7 @@ void integrate_quad_f64(Io io, Uni u) {
     const int q = threadIdx.x & 3;
     LaneQ L{};
     L.w = 1.0;                  // idle quads step on this state and discard the result
+    L.range = kQuadRange;
     L.v[0] = q == 3 ? 1.0 : 0.0;
     PolyQ pc;
     make_poly(pc);
