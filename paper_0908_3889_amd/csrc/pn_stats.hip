@@ -191,6 +191,9 @@ __device__ __forceinline__ void block_sum(double (&v)[K], double (*sh)[THREADS /
     }
 }
 
+__device__ __forceinline__ bool finite(double v) { return __builtin_isfinite(v); }
+__device__ __forceinline__ double finite_or_zero(double v) { return finite(v) ? v : 0.0; }
+
 __device__ __forceinline__ double block_max(double v, double* sh) {
     sh[threadIdx.x] = v;
     __syncthreads();
@@ -206,15 +209,22 @@ __device__ __forceinline__ double block_max(double v, double* sh) {
 // ---------------------------------------------------------------------------
 // Pearson: sums, then sums of the centred products.  Samples of one block
 // (kPearOne values) take one launch; of larger ones, up to kPearParts blocks
-// take chunks of kPearChunk values.  A chunk's values are kept in registers
-// between its sums and its centred sums, and the centred sums of two sets a, b
-// about their own means combine to those about the mean of both with
-// n_a n_b / (n_a + n_b) times the product of the differences of the means
-// (Chan, Golub & LeVeque 1983), which loses no more than a second pass over
-// memory would.  Workspace: part[c][kPearParts][5].  Bound by launches and
-// latency for small samples (3 x 4,099: four launches 12 us, one 6 us; 3 x
-// 16,384: 18 and 9 us), by reading them for large ones (3 x 2^20: two passes 24
-// us, one 16 us).
+// take chunks of kPearChunk values.  A wave keeps 64 x HOLD values in registers
+// between its sums and its centred sums; the waves of a block meet once, at the
+// end.  The centred sums of two sets a, b about their own means combine to those
+// about the mean of both with n_a n_b / (n_a + n_b) times the product of the
+// differences of the means (Chan, Golub & LeVeque 1983), which loses no more
+// than a second pass over memory would.  Values are centred about a pivot, their
+// mean as rounded; the sum of what is centred gives the distance from the pivot
+// to the mean, and the centred sums are corrected by n times its square (the
+// two-pass form with a correction of the same paper).  Means stay pairs of a
+// pivot and a distance where sets combine: means rounded at the size of a common
+// offset cost the deviations the offset's digits (offset 10^9, deviation 0.5:
+// 1e-9 of the deviations; with the pairs 1e-15).  Workspace:
+// part[c][kPearParts].  Bound by launches and latency for small samples (3 x
+// 4,099: four launches 12 us, one 6 us; 3 x 16,384: 18 and 9 us), by reading
+// them for large ones (3 x 2^20: two passes 24 us, one 17 us; with three blocks
+// on a CU, so that all 768 run at once: two blocks, at 106 registers, 2 us more).
 // ---------------------------------------------------------------------------
 
 constexpr int kPearBlock = 512;
@@ -225,7 +235,31 @@ constexpr int kPearOneBlock = 1024;
 constexpr int kPearKeep = 16;
 constexpr int64_t kPearOne = (int64_t)kPearOneBlock * kPearKeep;
 
-__device__ __forceinline__ void pearson_out(int64_t n, double mx, double my, const double (&v)[3],
+// a part: the mean of x and of y as a double and what that rounds off as a
+// fraction of it (|fraction| <= 2^-53), the centred sums
+struct PearPart {
+    double mean[2];
+    float rest[2];
+    double cen[3];
+};
+static_assert(kPearParts * sizeof(PearPart) <= kPart * 3 * sizeof(double), "the parts fit the workspace");
+
+// a set of n values: pivots, the means' distances from them, the centred sums
+struct PearSet {
+    double n, piv[2], d[2], cen[3];
+};
+
+// sums over LANES lanes side by side, in each of them
+template <int LANES, int K>
+__device__ __forceinline__ void lane_sum(double (&v)[K]) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+#pragma unroll
+        for (int d = LANES / 2; d > 0; d >>= 1) v[k] += __shfl_xor(v[k], d);
+    }
+}
+
+__device__ __forceinline__ void pearson_out(int64_t n, double mx, double my, const double* v,
                                             double* __restrict__ out) {
     const double nm1 = (double)(n - 1);
     out[0] = mx;
@@ -235,40 +269,118 @@ __device__ __forceinline__ void pearson_out(int64_t n, double mx, double my, con
     out[4] = v[2] / sqrt(v[0] * v[1]);
 }
 
-__global__ __launch_bounds__(kPearOneBlock) void pearson_one_kernel(int64_t n, int64_t ld, const double* __restrict__ x,
-                                                                    const double* __restrict__ y,
-                                                                    double* __restrict__ out) {
-    __shared__ double sh[3][kPearOneBlock / 64];
-    const int c = blockIdx.x;
-    const double* xc = x + (int64_t)c * ld;
-    const double* yc = y + (int64_t)c * ld;
-    double xv[kPearKeep], yv[kPearKeep];
+// the set of a wave's cnt > 0 values (0 in the places past them).  Distances are
+// 0 where a value or the pivot is infinite, and the sums not finite anyway; a
+// correction that overflows belongs to sums that do.
+template <int HOLD>
+__device__ __forceinline__ void pearson_wave(int cnt, const double (&xv)[HOLD], const double (&yv)[HOLD], PearSet& o) {
+    const int lane = threadIdx.x & 63;
+    double m[2] = {0.0, 0.0}, v[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int k = 0; k < kPearKeep; ++k) {
-        const int i = k * kPearOneBlock + threadIdx.x;
-        xv[k] = i < n ? xc[i] : 0.0;
-        yv[k] = i < n ? yc[i] : 0.0;
-    }
-    double m[2] = {0.0, 0.0};
-#pragma unroll
-    for (int k = 0; k < kPearKeep; ++k) {
+    for (int k = 0; k < HOLD; ++k) {
         m[0] += xv[k];
         m[1] += yv[k];
     }
-    block_sum<2, kPearOneBlock>(m, sh);
-    const double mx = m[0] / (double)n, my = m[1] / (double)n;
-    double v[3] = {0.0, 0.0, 0.0};
+    lane_sum<64>(m);
+    o.n = (double)cnt;
+    const double in = 1.0 / o.n;
+    {
+#pragma clang fp contract(off)
+        o.piv[0] = m[0] * in;    // rounded: the same pivot for what is centred and for the set
+        o.piv[1] = m[1] * in;
+    }
 #pragma unroll
-    for (int k = 0; k < kPearKeep; ++k) {
-        if (k * kPearOneBlock + (int)threadIdx.x < n) {
-            const double dx = xv[k] - mx, dy = yv[k] - my;
+    for (int k = 0; k < HOLD; ++k) {
+        if (k * 64 + lane < cnt) {
+            const double dx = xv[k] - o.piv[0], dy = yv[k] - o.piv[1];
             v[0] += dx * dx;
             v[1] += dy * dy;
             v[2] += dx * dy;
+            v[3] += dx;
+            v[4] += dy;
         }
     }
-    block_sum<3, kPearOneBlock>(v, sh);
-    if (threadIdx.x == 0) pearson_out(n, mx, my, v, out + c * 5);
+    lane_sum<64>(v);
+    o.d[0] = finite_or_zero(v[3] * in);
+    o.d[1] = finite_or_zero(v[4] * in);
+    o.cen[0] = v[0] - finite_or_zero(v[3] * o.d[0]);
+    o.cen[1] = v[1] - finite_or_zero(v[4] * o.d[1]);
+    o.cen[2] = v[2] - finite_or_zero(v[3] * o.d[1]);
+}
+
+// a = a and b
+__device__ __forceinline__ void pearson_join(PearSet& a, const PearSet& b) {
+    // (from an infinite pivot on, distances from 0: infinities keep their sign)
+    const double dx = (finite(a.piv[0]) ? b.piv[0] - a.piv[0] : b.piv[0]) + b.d[0] - a.d[0];
+    const double dy = (finite(a.piv[1]) ? b.piv[1] - a.piv[1] : b.piv[1]) + b.d[1] - a.d[1];
+    const double w = b.n / (a.n + b.n), f = a.n * w;
+    a.cen[0] += b.cen[0] + f * dx * dx;
+    a.cen[1] += b.cen[1] + f * dy * dy;
+    a.cen[2] += b.cen[2] + f * dx * dy;
+    a.d[0] += w * dx;
+    a.d[1] += w * dy;
+    a.n += b.n;
+}
+
+// the sets of WAVES waves, one a lane (n = 0: none), as one about the first
+// one's pivot; plain: the means as sums of n times mean, for those that are not
+// finite.  In each of WAVES lanes side by side.
+template <int WAVES>
+__device__ __forceinline__ void pearson_meet(const PearSet& p, const double (&base)[2], double (&d)[2],
+                                             double (&plain)[2], double (&cen)[3]) {
+    const bool any = p.n > 0.0;
+    const double dx = any ? (p.piv[0] - base[0]) + p.d[0] : 0.0, dy = any ? (p.piv[1] - base[1]) + p.d[1] : 0.0;
+    double m[5] = {p.n * dx, p.n * dy, any ? p.n * (p.piv[0] + p.d[0]) : 0.0, any ? p.n * (p.piv[1] + p.d[1]) : 0.0,
+                   p.n};
+    lane_sum<WAVES>(m);
+    const double in = 1.0 / m[4];
+    d[0] = m[0] * in; d[1] = m[1] * in;
+    plain[0] = m[2] * in; plain[1] = m[3] * in;
+    const double ex = any ? dx - d[0] : 0.0, ey = any ? dy - d[1] : 0.0;
+    cen[0] = p.cen[0] + p.n * ex * ex;
+    cen[1] = p.cen[1] + p.n * ey * ey;
+    cen[2] = p.cen[2] + p.n * ex * ey;
+    lane_sum<WAVES>(cen);
+}
+
+// the waves' sets to the lanes of the first wave; false in the other waves
+template <int WAVES>
+__device__ __forceinline__ bool pearson_gather(PearSet& p, PearSet* sh, double (&base)[2]) {
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = p;
+    __syncthreads();
+    if (threadIdx.x >= WAVES) return false;
+    p = sh[threadIdx.x];
+    base[0] = sh[0].piv[0];
+    base[1] = sh[0].piv[1];
+    return true;
+}
+
+__global__ __launch_bounds__(kPearOneBlock) void pearson_one_kernel(int64_t n, int64_t ld, const double* __restrict__ x,
+                                                                    const double* __restrict__ y,
+                                                                    double* __restrict__ out) {
+    constexpr int kWaves = kPearOneBlock / 64;
+    __shared__ PearSet sh[kWaves];
+    const int c = blockIdx.x;
+    const double* xc = x + (int64_t)c * ld;
+    const double* yc = y + (int64_t)c * ld;
+    // a row of 64 values a wave, then the next rows: small samples spread over the waves
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    double xv[kPearKeep], yv[kPearKeep];
+    int cnt = 0;
+#pragma unroll
+    for (int k = 0; k < kPearKeep; ++k) {
+        const int r = (k * kWaves + wave) * 64, i = r + lane;
+        xv[k] = i < n ? xc[i] : 0.0;
+        yv[k] = i < n ? yc[i] : 0.0;
+        cnt += n - r < 64 ? (n > r ? (int)(n - r) : 0) : 64;
+    }
+    PearSet p = {};
+    if (cnt > 0) pearson_wave(cnt, xv, yv, p);
+    double base[2], d[2], plain[2], cen[3];
+    if (!pearson_gather<kWaves>(p, sh, base)) return;
+    pearson_meet<kWaves>(p, base, d, plain, cen);
+    const double mx = base[0] + d[0], my = base[1] + d[1];
+    if (threadIdx.x == 0) pearson_out(n, finite(mx) ? mx : plain[0], finite(my) ? my : plain[1], cen, out + c * 5);
 }
 
 // the number of values in the chunks k, k + parts, .. of a block
@@ -278,80 +390,81 @@ __device__ __forceinline__ double pearson_count(int64_t n, int k, int parts) {
     return (double)(mine * kPearChunk - ((chunks - 1) % parts == k ? chunks * kPearChunk - n : 0));
 }
 
-__global__ __launch_bounds__(kPearBlock) void pearson_part_kernel(int64_t n, int64_t ld, const double* __restrict__ x,
-                                                                  const double* __restrict__ y,
-                                                                  double* __restrict__ part) {
-    __shared__ double sh[3][kPearBlock / 64];
+__global__ __launch_bounds__(kPearBlock, 6) void pearson_part_kernel(int64_t n, int64_t ld, const double* __restrict__ x,
+                                                                     const double* __restrict__ y,
+                                                                     PearPart* __restrict__ part) {
+    constexpr int kWaves = kPearBlock / 64, kRow = 64 * kPearHold;
+    __shared__ PearSet sh[kWaves];
     const int c = blockIdx.y;
     const double* xc = x + (int64_t)c * ld;
     const double* yc = y + (int64_t)c * ld;
-    double sum[2] = {0.0, 0.0}, cen[3] = {0.0, 0.0, 0.0}, na = 0.0;
-    for (int64_t i0 = blockIdx.x * kPearChunk; i0 < n; i0 += gridDim.x * kPearChunk) {
-        const int cnt = n - i0 < kPearChunk ? (int)(n - i0) : (int)kPearChunk;
-        double xv[kPearHold], yv[kPearHold], m[2] = {0.0, 0.0}, v[3] = {0.0, 0.0, 0.0};
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    PearSet p = {};
+    for (int64_t i0 = blockIdx.x * kPearChunk + wave * kRow; i0 < n; i0 += gridDim.x * kPearChunk) {
+        const int cnt = n - i0 < kRow ? (int)(n - i0) : kRow;
+        double xv[kPearHold], yv[kPearHold];
 #pragma unroll
         for (int k = 0; k < kPearHold; ++k) {
-            const int i = k * kPearBlock + threadIdx.x;
+            const int i = k * 64 + lane;
             xv[k] = i < cnt ? xc[i0 + i] : 0.0;
             yv[k] = i < cnt ? yc[i0 + i] : 0.0;
         }
-#pragma unroll
-        for (int k = 0; k < kPearHold; ++k) {
-            m[0] += xv[k];
-            m[1] += yv[k];
-        }
-        block_sum<2, kPearBlock>(m, sh);
-        const double nb = (double)cnt, mx = m[0] / nb, my = m[1] / nb;
-#pragma unroll
-        for (int k = 0; k < kPearHold; ++k) {
-            if (k * kPearBlock + (int)threadIdx.x < cnt) {
-                const double dx = xv[k] - mx, dy = yv[k] - my;
-                v[0] += dx * dx;
-                v[1] += dy * dy;
-                v[2] += dx * dy;
-            }
-        }
-        block_sum<3, kPearBlock>(v, sh);
-        if (na > 0.0) {
-            const double dx = mx - sum[0] / na, dy = my - sum[1] / na, f = na * nb / (na + nb);
-            v[0] += f * dx * dx;
-            v[1] += f * dy * dy;
-            v[2] += f * dx * dy;
-        }
-        na += nb;
-        sum[0] += m[0];
-        sum[1] += m[1];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) cen[k] += v[k];
+        PearSet q;
+        pearson_wave(cnt, xv, yv, q);
+        if (p.n > 0.0) pearson_join(p, q);
+        else p = q;
     }
+    double base[2], d[2], plain[2], cen[3];
+    if (!pearson_gather<kWaves>(p, sh, base)) return;
+    pearson_meet<kWaves>(p, base, d, plain, cen);
     if (threadIdx.x == 0) {
-        double* o = part + ((int64_t)c * kPearParts + blockIdx.x) * 5;
-        o[0] = sum[0]; o[1] = sum[1]; o[2] = cen[0]; o[3] = cen[1]; o[4] = cen[2];
+        PearPart& o = part[(int64_t)c * kPearParts + blockIdx.x];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            // the pivot and the distance as their sum and what it rounds off
+            const double mean = base[k] + d[k], t = mean - base[k];
+            const double rest = (base[k] - (mean - t)) + (d[k] - t);
+            o.mean[k] = finite(mean) ? mean : plain[k];
+            o.rest[k] = (float)finite_or_zero(rest / mean);
+        }
+        o.cen[0] = cen[0]; o.cen[1] = cen[1]; o.cen[2] = cen[2];
     }
 }
 
-__global__ __launch_bounds__(kPearParts) void pearson_final_kernel(int64_t n, int parts, const double* __restrict__ part,
+__global__ __launch_bounds__(kPearParts) void pearson_final_kernel(int64_t n, int parts,
+                                                                   const PearPart* __restrict__ part,
                                                                    double* __restrict__ out) {
-    __shared__ double sh[3][kPearParts / 64];
+    __shared__ double sh[4][kPearParts / 64];
     const int c = blockIdx.x;
     const bool mine = (int)threadIdx.x < parts;
-    double m[2] = {0.0, 0.0}, v[3] = {0.0, 0.0, 0.0};
+    // the means' distances from the first part's, summed for the centred sums;
+    // the plain sums for the mean itself (the first part's may be far from it)
+    double d[2] = {0.0, 0.0}, m[4] = {0.0, 0.0, 0.0, 0.0}, v[3] = {0.0, 0.0, 0.0}, base[2], nb = 0.0;
+    const PearPart& first = part[(int64_t)c * kPearParts];
+    base[0] = first.mean[0];
+    base[1] = first.mean[1];
     if (mine) {
-        const double* o = part + ((int64_t)c * kPearParts + threadIdx.x) * 5;
-        m[0] = o[0]; m[1] = o[1];
-        v[0] = o[2]; v[1] = o[3]; v[2] = o[4];
+        const PearPart& o = part[(int64_t)c * kPearParts + threadIdx.x];
+        nb = pearson_count(n, threadIdx.x, parts);
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            d[k] = (o.mean[k] - base[k]) + o.mean[k] * (double)o.rest[k];
+            m[k] = nb * d[k];
+            m[2 + k] = nb * o.mean[k];
+        }
+        v[0] = o.cen[0]; v[1] = o.cen[1]; v[2] = o.cen[2];
     }
-    const double sx = m[0], sy = m[1];
-    block_sum<2, kPearParts>(m, sh);
-    const double mx = m[0] / (double)n, my = m[1] / (double)n;
+    block_sum<4, kPearParts>(m, sh);
+    m[0] /= (double)n;
+    m[1] /= (double)n;
     if (mine) {
-        const double nb = pearson_count(n, threadIdx.x, parts), dx = sx / nb - mx, dy = sy / nb - my;
+        const double dx = d[0] - m[0], dy = d[1] - m[1];
         v[0] += nb * dx * dx;
         v[1] += nb * dy * dy;
         v[2] += nb * dx * dy;
     }
     block_sum<3, kPearParts>(v, sh);
-    if (threadIdx.x == 0) pearson_out(n, mx, my, v, out + c * 5);
+    if (threadIdx.x == 0) pearson_out(n, m[2] / (double)n, m[3] / (double)n, v, out + c * 5);
 }
 
 // ---------------------------------------------------------------------------
@@ -1631,10 +1744,9 @@ int pn_pearson(int64_t n, int64_t ld, const double* x, const double* y, int32_t 
         hipLaunchKernelGGL(pearson_one_kernel, dim3(ncomp), dim3(kPearOneBlock), 0, s, n, ld, x, y, out);
         return launched();
     }
-    static_assert(kPearParts * 5 <= kPart * 3, "the partial sums fit the workspace");
     const int64_t chunks = (n + kPearChunk - 1) / kPearChunk;
     const int parts = chunks < kPearParts ? (int)chunks : kPearParts;
-    double* part = (double*)workspace;
+    PearPart* part = (PearPart*)workspace;
     hipLaunchKernelGGL(pearson_part_kernel, dim3(parts, ncomp), dim3(kPearBlock), 0, s, n, ld, x, y, part);
     hipLaunchKernelGGL(pearson_final_kernel, dim3(ncomp), dim3(kPearParts), 0, s, n, parts, part, out);
     return launched();

@@ -1,0 +1,78 @@
+"""Pearson sums of values with a large common offset or one far value: about a
+pivot near the mean the centred values are exact or rounded to eps of
+themselves, so that the deviations and r keep all their digits."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_0908_3889_amd import _lib
+    _lib.load()
+    yield
+
+
+def _cuda(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).cuda()
+
+
+def _moments(x, y):
+    x, y = x.astype(np.longdouble), y.astype(np.longdouble)
+    mx, my = x.mean(), y.mean()
+    sx, sy = ((x - mx) ** 2).sum(), ((y - my) ** 2).sum()
+    return mx, my, np.sqrt(sx / (x.size - 1)), np.sqrt(sy / (x.size - 1)), ((x - mx) * (y - my)).sum() / np.sqrt(sx * sy)
+
+
+# Sums of n terms in trees of depth about log2 n + 16: 64 eps of the sum of
+# magnitudes (which for xy is at most the root of the product of the others).
+# The sizes: one block, its largest, the first in chunks, some chunks, more
+# chunks than blocks.
+@pytest.mark.parametrize("kind", ["offset", "far first", "far last", "drift"])
+@pytest.mark.parametrize("n", [1000, 16384, 16385, 70001, 300000, 1200007])
+def test_offset_costs_no_digits(n, kind):
+    rng = np.random.default_rng(n)
+    x = rng.normal(0.0, 0.5, (2, n))
+    y = 0.5 * x + rng.normal(0.0, 0.4, (2, n))
+    if kind == "offset":
+        x += np.array([[1e9], [-3e11]])
+        y += np.array([[7e9], [1e8]])
+    elif kind == "drift":
+        x += 1e9 + np.linspace(0.0, 5.0, n)
+        y -= 1e9 + np.linspace(0.0, 3.0, n)
+    else:
+        i = 0 if kind == "far first" else n - 1
+        x[:, i], y[:, i] = 1e9, -4e8
+    got = _api().pn_pearson(_cuda(x), _cuda(y)).cpu().numpy()
+    eps = 2.0 ** -52
+    for c in range(2):
+        ref = _moments(x[c], y[c])
+        for k in (0, 1):
+            assert abs(got[c, k] - ref[k]) <= 64 * eps * np.abs((x, y)[k][c]).mean()
+        for k in (2, 3):
+            assert abs(got[c, k] / ref[k] - 1) <= 64 * eps
+        assert abs(got[c, 4] - ref[4]) <= 64 * eps
+
+
+# a value that is not finite: the mean is what the plain sum gives, the rest NaN
+@pytest.mark.parametrize("n", [1000, 70001, 1200007])
+@pytest.mark.parametrize("values,mean", [((np.inf,), np.inf), ((-np.inf,), -np.inf), ((np.inf, np.inf), np.inf),
+                                         ((np.inf, -np.inf), np.nan), ((np.nan,), np.nan)])
+@pytest.mark.parametrize("first", [0, 700])
+def test_infinite_values(n, values, mean, first):
+    rng = np.random.default_rng(2)
+    x, y = rng.normal(size=(1, n)), rng.normal(size=(1, n))
+    for k, v in enumerate(values):
+        x[0, first if k == 0 else n - 1 - first] = v
+    got = _api().pn_pearson(_cuda(x), _cuda(y)).cpu().numpy()[0]
+    np.testing.assert_equal(got[0], mean)
+    assert np.isnan(got[2]) and np.isnan(got[4]) and np.isfinite(got[1]) and np.isfinite(got[3])
+
+
+def _api():
+    from paper_0908_3889_amd import api
+    return api
