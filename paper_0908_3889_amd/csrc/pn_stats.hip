@@ -330,8 +330,8 @@ __device__ __forceinline__ void pearson_meet(const PearSet& p, const double (&ba
                                              double (&plain)[2], double (&cen)[3]) {
     const bool any = p.n > 0.0;
     const double dx = any ? (p.piv[0] - base[0]) + p.d[0] : 0.0, dy = any ? (p.piv[1] - base[1]) + p.d[1] : 0.0;
-    double m[5] = {p.n * dx, p.n * dy, any ? p.n * (p.piv[0] + p.d[0]) : 0.0, any ? p.n * (p.piv[1] + p.d[1]) : 0.0,
-                   p.n};
+    const double w = p.n * 0x1p-14;    // n times a mean may overflow where the mean of all does not
+    double m[5] = {w * dx, w * dy, any ? w * (p.piv[0] + p.d[0]) : 0.0, any ? w * (p.piv[1] + p.d[1]) : 0.0, w};
     lane_sum<WAVES>(m);
     const double in = 1.0 / m[4];
     d[0] = m[0] * in; d[1] = m[1] * in;
@@ -446,17 +446,16 @@ __global__ __launch_bounds__(kPearParts) void pearson_final_kernel(int64_t n, in
     if (mine) {
         const PearPart& o = part[(int64_t)c * kPearParts + threadIdx.x];
         nb = pearson_count(n, threadIdx.x, parts);
+        const double w = nb / (double)n;
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             d[k] = (o.mean[k] - base[k]) + o.mean[k] * (double)o.rest[k];
-            m[k] = nb * d[k];
-            m[2 + k] = nb * o.mean[k];
+            m[k] = w * d[k];
+            m[2 + k] = w * o.mean[k];
         }
         v[0] = o.cen[0]; v[1] = o.cen[1]; v[2] = o.cen[2];
     }
     block_sum<4, kPearParts>(m, sh);
-    m[0] /= (double)n;
-    m[1] /= (double)n;
     if (mine) {
         const double dx = d[0] - m[0], dy = d[1] - m[1];
         v[0] += nb * dx * dx;
@@ -464,7 +463,7 @@ __global__ __launch_bounds__(kPearParts) void pearson_final_kernel(int64_t n, in
         v[2] += nb * dx * dy;
     }
     block_sum<3, kPearParts>(v, sh);
-    if (threadIdx.x == 0) pearson_out(n, m[2] / (double)n, m[3] / (double)n, v, out + c * 5);
+    if (threadIdx.x == 0) pearson_out(n, m[2], m[3], v, out + c * 5);
 }
 
 // ---------------------------------------------------------------------------

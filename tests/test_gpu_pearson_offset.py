@@ -73,6 +73,18 @@ def test_infinite_values(n, values, mean, first):
     assert np.isnan(got[2]) and np.isnan(got[4]) and np.isfinite(got[1]) and np.isfinite(got[3])
 
 
+# values whose partial sums and mean are doubles, means of waves times their
+# counts not: rows of 64 (one block) and of 512 values (chunks) of either sign
+@pytest.mark.parametrize("n,row,size", [(16384, 64, 1.2e305), (16385, 512, 3e305), (70001, 512, 3e305),
+                                        (1200007, 512, 3e305)])
+def test_mean_of_large_values(n, row, size):
+    x = size * (1 - 2 * (np.arange(n) // row % 2))[None] * np.random.default_rng(7).uniform(0.9, 1.0, n)
+    got = _api().pn_pearson(_cuda(x), _cuda(-x)).cpu().numpy()[0]
+    mean = x[0].astype(np.longdouble).mean()
+    assert abs(got[0] - mean) <= 64 * 2.0 ** -52 * size
+    assert abs(got[1] + mean) <= 64 * 2.0 ** -52 * size
+
+
 def _api():
     from paper_0908_3889_amd import api
     return api
