@@ -169,15 +169,37 @@ __global__ __launch_bounds__(kHistBlock) void hist2d_kernel(int64_t n, int64_t l
 // fixed-order block reductions
 // ---------------------------------------------------------------------------
 
-// the sums over a block of THREADS, in every thread
-template <int K, int THREADS>
-__device__ __forceinline__ void block_sum(double (&v)[K], double (*sh)[THREADS / 64]) {
+// v of another lane by a data-parallel move (0 in the rows that ROWS leaves out):
+// a shuffle goes through the LDS, whose pipe the waves of a CU share (Pearson of
+// 3 x 4,099 values 9.6 us with shuffles, 6.5 so; of 3 x 2^20 17.4 and 16 us)
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ double dpp(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+
+// sums over LANES (8, 16 or 64) lanes side by side, in each of them
+template <int LANES, int K>
+__device__ __forceinline__ void lane_sum(double (&v)[K]) {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-#pragma unroll
-        for (int d = 32; d > 0; d >>= 1) v[k] += __shfl_xor(v[k], d);
+        v[k] += dpp<0xB1>(v[k]);                          // lanes 1, 0, 3, 2 of a quad
+        v[k] += dpp<0x4E>(v[k]);                          // 2, 3, 0, 1
+        v[k] += dpp<0x141>(v[k]);                         // 7 .. 0 of eight
+        if (LANES > 8) v[k] += dpp<0x140>(v[k]);          // 15 .. 0 of a row
+        if (LANES > 16) {
+            v[k] += dpp<0x142, 0xa>(v[k]);                // lane 15 to the row after, for rows 1 and 3
+            v[k] += dpp<0x143, 0xc>(v[k]);                // lane 31 to rows 2 and 3
+            v[k] = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v[k]), 63),
+                                    __builtin_amdgcn_readlane(__double2loint(v[k]), 63));
+        }
     }
-    __syncthreads();
+}
+
+// the sums of the waves of THREADS, in every thread, from each wave's in its lanes
+template <int K, int THREADS>
+__device__ __forceinline__ void block_add(double (&v)[K], double (*sh)[THREADS / 64]) {
     if ((threadIdx.x & 63) == 0) {
 #pragma unroll
         for (int k = 0; k < K; ++k) sh[k][threadIdx.x >> 6] = v[k];
@@ -189,6 +211,14 @@ __device__ __forceinline__ void block_sum(double (&v)[K], double (*sh)[THREADS /
 #pragma unroll
         for (int w = 0; w < THREADS / 64; ++w) v[k] += sh[k][w];
     }
+}
+
+// the sums over a block of THREADS, in every thread
+template <int K, int THREADS>
+__device__ __forceinline__ void block_sum(double (&v)[K], double (*sh)[THREADS / 64]) {
+    lane_sum<64>(v);
+    __syncthreads();
+    block_add<K, THREADS>(v, sh);
 }
 
 __device__ __forceinline__ bool finite(double v) { return __builtin_isfinite(v); }
@@ -210,8 +240,8 @@ __device__ __forceinline__ double block_max(double v, double* sh) {
 // Pearson: sums, then sums of the centred products.  Samples of one block
 // (kPearOne values) take one launch; of larger ones, up to kPearParts blocks
 // take chunks of kPearChunk values.  A wave keeps 64 x HOLD values in registers
-// between its sums and its centred sums; the waves of a block meet once, at the
-// end.  The centred sums of two sets a, b about their own means combine to those
+// between its sums and its centred sums; the waves of a chunked block meet once,
+// at its end.  The centred sums of two sets a, b about their own means combine to those
 // about the mean of both with n_a n_b / (n_a + n_b) times the product of the
 // differences of the means (Chan, Golub & LeVeque 1983), which loses no more
 // than a second pass over memory would.  Values are centred about a pivot, their
@@ -223,8 +253,8 @@ __device__ __forceinline__ double block_max(double v, double* sh) {
 // 1e-9 of the deviations; with the pairs 1e-15).  Workspace:
 // part[c][kPearParts].  Bound by launches and latency for small samples (3 x
 // 4,099: four launches 12 us, one 6 us; 3 x 16,384: 18 and 9 us), by reading
-// them for large ones (3 x 2^20: two passes 24 us, one 17 us; with three blocks
-// on a CU, so that all 768 run at once: two blocks, at 106 registers, 2 us more).
+// them for large ones (3 x 2^20: two passes 24 us, one 16 us; with three blocks
+// on a CU, so that all 768 run at once).
 // ---------------------------------------------------------------------------
 
 constexpr int kPearBlock = 512;
@@ -249,16 +279,6 @@ struct PearSet {
     double n, piv[2], d[2], cen[3];
 };
 
-// sums over LANES lanes side by side, in each of them
-template <int LANES, int K>
-__device__ __forceinline__ void lane_sum(double (&v)[K]) {
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-#pragma unroll
-        for (int d = LANES / 2; d > 0; d >>= 1) v[k] += __shfl_xor(v[k], d);
-    }
-}
-
 __device__ __forceinline__ void pearson_out(int64_t n, double mx, double my, const double* v,
                                             double* __restrict__ out) {
     const double nm1 = (double)(n - 1);
@@ -269,30 +289,37 @@ __device__ __forceinline__ void pearson_out(int64_t n, double mx, double my, con
     out[4] = v[2] / sqrt(v[0] * v[1]);
 }
 
-// the set of a wave's cnt > 0 values (0 in the places past them).  Distances are
-// 0 where a value or the pivot is infinite, and the sums not finite anyway; a
-// correction that overflows belongs to sums that do.
+// a wave's sums of its HOLD x 64 places
 template <int HOLD>
-__device__ __forceinline__ void pearson_wave(int cnt, const double (&xv)[HOLD], const double (&yv)[HOLD], PearSet& o) {
-    const int lane = threadIdx.x & 63;
-    double m[2] = {0.0, 0.0}, v[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+__device__ __forceinline__ void pearson_sums(const double (&xv)[HOLD], const double (&yv)[HOLD], double (&m)[2]) {
+    m[0] = m[1] = 0.0;
 #pragma unroll
     for (int k = 0; k < HOLD; ++k) {
         m[0] += xv[k];
         m[1] += yv[k];
     }
     lane_sum<64>(m);
-    o.n = (double)cnt;
-    const double in = 1.0 / o.n;
-    {
+}
+
+// the pivot from the sums, in = 1/n: rounded, the same for what is centred and
+// for the set (no contraction with the subtraction)
+__device__ __forceinline__ void pearson_pivot(const double (&m)[2], double in, PearSet& o) {
 #pragma clang fp contract(off)
-        o.piv[0] = m[0] * in;    // rounded: the same pivot for what is centred and for the set
-        o.piv[1] = m[1] * in;
-    }
+    o.piv[0] = m[0] * in;
+    o.piv[1] = m[1] * in;
+}
+
+// a wave's centred sums xx, yy, xy, x and y of its cnt values
+template <int HOLD>
+__device__ __forceinline__ void pearson_centre(int cnt, const double (&xv)[HOLD], const double (&yv)[HOLD],
+                                               const PearSet& p, double (&v)[5]) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int k = 0; k < 5; ++k) v[k] = 0.0;
 #pragma unroll
     for (int k = 0; k < HOLD; ++k) {
         if (k * 64 + lane < cnt) {
-            const double dx = xv[k] - o.piv[0], dy = yv[k] - o.piv[1];
+            const double dx = xv[k] - p.piv[0], dy = yv[k] - p.piv[1];
             v[0] += dx * dx;
             v[1] += dy * dy;
             v[2] += dx * dy;
@@ -301,6 +328,12 @@ __device__ __forceinline__ void pearson_wave(int cnt, const double (&xv)[HOLD], 
         }
     }
     lane_sum<64>(v);
+}
+
+// the rest of the set from them.  Distances are 0 where a value or the pivot is
+// infinite, and the sums not finite anyway; a correction that overflows belongs
+// to sums that do.
+__device__ __forceinline__ void pearson_settle(const double (&v)[5], double in, PearSet& o) {
     o.d[0] = finite_or_zero(v[3] * in);
     o.d[1] = finite_or_zero(v[4] * in);
     o.cen[0] = v[0] - finite_or_zero(v[3] * o.d[0]);
@@ -343,6 +376,52 @@ __device__ __forceinline__ void pearson_meet(const PearSet& p, const double (&ba
     lane_sum<WAVES>(cen);
 }
 
+__global__ __launch_bounds__(kPearOneBlock) void pearson_one_kernel(int64_t n, int64_t ld, const double* __restrict__ x,
+                                                                    const double* __restrict__ y,
+                                                                    double* __restrict__ out) {
+    constexpr int kWaves = kPearOneBlock / 64;
+    __shared__ double sh[2][kWaves], sv[kWaves][5];
+    const int c = blockIdx.x;
+    const double* xc = x + (int64_t)c * ld;
+    const double* yc = y + (int64_t)c * ld;
+    // a row of 64 values a wave, then the next rows: small samples spread over the waves
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const double in = 1.0 / (double)n;
+    double xv[kPearKeep], yv[kPearKeep], m[2], v[5];
+    int cnt = 0;
+#pragma unroll
+    for (int k = 0; k < kPearKeep; ++k) {
+        const int r = (k * kWaves + wave) * 64, i = r + lane;
+        xv[k] = i < n ? xc[i] : 0.0;
+        yv[k] = i < n ? yc[i] : 0.0;
+        cnt += n - r < 64 ? (n > r ? (int)(n - r) : 0) : 64;
+    }
+    // one pivot for the block: its waves have their sums of a few values at once
+    pearson_sums(xv, yv, m);
+    block_add<2, kPearOneBlock>(m, sh);
+    PearSet p;
+    pearson_pivot(m, in, p);
+    pearson_centre(cnt, xv, yv, p, v);
+    if (lane == 0) {
+#pragma unroll
+        for (int k = 0; k < 5; ++k) sv[wave][k] = v[k];
+    }
+    __syncthreads();
+    if (threadIdx.x >= kWaves) return;
+#pragma unroll
+    for (int k = 0; k < 5; ++k) v[k] = sv[threadIdx.x][k];
+    lane_sum<kWaves>(v);
+    pearson_settle(v, in, p);
+    if (threadIdx.x == 0) pearson_out(n, p.piv[0] + p.d[0], p.piv[1] + p.d[1], p.cen, out + c * 5);
+}
+
+// the number of values in the chunks k, k + parts, .. of a block
+__device__ __forceinline__ double pearson_count(int64_t n, int k, int parts) {
+    const int64_t chunks = (n + kPearChunk - 1) / kPearChunk;
+    const int64_t mine = (chunks - k + parts - 1) / parts;
+    return (double)(mine * kPearChunk - ((chunks - 1) % parts == k ? chunks * kPearChunk - n : 0));
+}
+
 // the waves' sets to the lanes of the first wave; false in the other waves
 template <int WAVES>
 __device__ __forceinline__ bool pearson_gather(PearSet& p, PearSet* sh, double (&base)[2]) {
@@ -353,41 +432,6 @@ __device__ __forceinline__ bool pearson_gather(PearSet& p, PearSet* sh, double (
     base[0] = sh[0].piv[0];
     base[1] = sh[0].piv[1];
     return true;
-}
-
-__global__ __launch_bounds__(kPearOneBlock) void pearson_one_kernel(int64_t n, int64_t ld, const double* __restrict__ x,
-                                                                    const double* __restrict__ y,
-                                                                    double* __restrict__ out) {
-    constexpr int kWaves = kPearOneBlock / 64;
-    __shared__ PearSet sh[kWaves];
-    const int c = blockIdx.x;
-    const double* xc = x + (int64_t)c * ld;
-    const double* yc = y + (int64_t)c * ld;
-    // a row of 64 values a wave, then the next rows: small samples spread over the waves
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    double xv[kPearKeep], yv[kPearKeep];
-    int cnt = 0;
-#pragma unroll
-    for (int k = 0; k < kPearKeep; ++k) {
-        const int r = (k * kWaves + wave) * 64, i = r + lane;
-        xv[k] = i < n ? xc[i] : 0.0;
-        yv[k] = i < n ? yc[i] : 0.0;
-        cnt += n - r < 64 ? (n > r ? (int)(n - r) : 0) : 64;
-    }
-    PearSet p = {};
-    if (cnt > 0) pearson_wave(cnt, xv, yv, p);
-    double base[2], d[2], plain[2], cen[3];
-    if (!pearson_gather<kWaves>(p, sh, base)) return;
-    pearson_meet<kWaves>(p, base, d, plain, cen);
-    const double mx = base[0] + d[0], my = base[1] + d[1];
-    if (threadIdx.x == 0) pearson_out(n, finite(mx) ? mx : plain[0], finite(my) ? my : plain[1], cen, out + c * 5);
-}
-
-// the number of values in the chunks k, k + parts, .. of a block
-__device__ __forceinline__ double pearson_count(int64_t n, int k, int parts) {
-    const int64_t chunks = (n + kPearChunk - 1) / kPearChunk;
-    const int64_t mine = (chunks - k + parts - 1) / parts;
-    return (double)(mine * kPearChunk - ((chunks - 1) % parts == k ? chunks * kPearChunk - n : 0));
 }
 
 __global__ __launch_bounds__(kPearBlock, 6) void pearson_part_kernel(int64_t n, int64_t ld, const double* __restrict__ x,
@@ -410,7 +454,13 @@ __global__ __launch_bounds__(kPearBlock, 6) void pearson_part_kernel(int64_t n, 
             yv[k] = i < cnt ? yc[i0 + i] : 0.0;
         }
         PearSet q;
-        pearson_wave(cnt, xv, yv, q);
+        double m[2], v[5];
+        q.n = (double)cnt;
+        const double in = 1.0 / q.n;
+        pearson_sums(xv, yv, m);
+        pearson_pivot(m, in, q);
+        pearson_centre(cnt, xv, yv, q, v);
+        pearson_settle(v, in, q);
         if (p.n > 0.0) pearson_join(p, q);
         else p = q;
     }
