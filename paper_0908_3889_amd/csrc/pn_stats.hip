@@ -241,10 +241,10 @@ __device__ __forceinline__ double block_max(double v, double* sh) {
 // (kPearOne values) take one launch; of larger ones, up to kPearParts blocks
 // take chunks of kPearChunk values.  A wave keeps 64 x HOLD values in registers
 // between its sums and its centred sums; the waves of a chunked block meet once,
-// at its end.  The centred sums of two sets a, b about their own means combine to those
-// about the mean of both with n_a n_b / (n_a + n_b) times the product of the
-// differences of the means (Chan, Golub & LeVeque 1983), which loses no more
-// than a second pass over memory would.  Values are centred about a pivot, their
+// at its end.  The centred sums of two sets a, b about their own means combine
+// to those about the mean of both with n_a n_b / (n_a + n_b) times the product
+// of the differences of the means (Chan, Golub & LeVeque 1983), which loses no
+// more than a second pass over memory would.  Values are centred about a pivot, their
 // mean as rounded; the sum of what is centred gives the distance from the pivot
 // to the mean, and the centred sums are corrected by n times its square (the
 // two-pass form with a correction of the same paper).  Means stay pairs of a
@@ -341,7 +341,7 @@ __device__ __forceinline__ void pearson_settle(const double (&v)[5], double in, 
     o.cen[2] = v[2] - finite_or_zero(v[3] * o.d[1]);
 }
 
-// a = a and b
+// a: a and b
 __device__ __forceinline__ void pearson_join(PearSet& a, const PearSet& b) {
     // (from an infinite pivot on, distances from 0: infinities keep their sign)
     const double dx = (finite(a.piv[0]) ? b.piv[0] - a.piv[0] : b.piv[0]) + b.d[0] - a.d[0];
@@ -422,18 +422,6 @@ __device__ __forceinline__ double pearson_count(int64_t n, int k, int parts) {
     return (double)(mine * kPearChunk - ((chunks - 1) % parts == k ? chunks * kPearChunk - n : 0));
 }
 
-// the waves' sets to the lanes of the first wave; false in the other waves
-template <int WAVES>
-__device__ __forceinline__ bool pearson_gather(PearSet& p, PearSet* sh, double (&base)[2]) {
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = p;
-    __syncthreads();
-    if (threadIdx.x >= WAVES) return false;
-    p = sh[threadIdx.x];
-    base[0] = sh[0].piv[0];
-    base[1] = sh[0].piv[1];
-    return true;
-}
-
 __global__ __launch_bounds__(kPearBlock, 6) void pearson_part_kernel(int64_t n, int64_t ld, const double* __restrict__ x,
                                                                      const double* __restrict__ y,
                                                                      PearPart* __restrict__ part) {
@@ -443,7 +431,7 @@ __global__ __launch_bounds__(kPearBlock, 6) void pearson_part_kernel(int64_t n, 
     const double* xc = x + (int64_t)c * ld;
     const double* yc = y + (int64_t)c * ld;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    PearSet p = {};
+    if (lane == 0) sh[wave] = PearSet{};
     for (int64_t i0 = blockIdx.x * kPearChunk + wave * kRow; i0 < n; i0 += gridDim.x * kPearChunk) {
         const int cnt = n - i0 < kRow ? (int)(n - i0) : kRow;
         double xv[kPearHold], yv[kPearHold];
@@ -461,11 +449,22 @@ __global__ __launch_bounds__(kPearBlock, 6) void pearson_part_kernel(int64_t n, 
         pearson_pivot(m, in, q);
         pearson_centre(cnt, xv, yv, q, v);
         pearson_settle(v, in, q);
-        if (p.n > 0.0) pearson_join(p, q);
-        else p = q;
+        if (lane == 0) {
+            // (the set so far is not kept in registers, which 24 waves a CU leave no more of)
+            if (i0 >= kPearChunk * gridDim.x) {
+                PearSet p = sh[wave];
+                pearson_join(p, q);
+                sh[wave] = p;
+            } else {
+                sh[wave] = q;
+            }
+        }
     }
-    double base[2], d[2], plain[2], cen[3];
-    if (!pearson_gather<kWaves>(p, sh, base)) return;
+    __syncthreads();
+    if (threadIdx.x >= kWaves) return;
+    const PearSet p = sh[threadIdx.x];
+    const double base[2] = {sh[0].piv[0], sh[0].piv[1]};
+    double d[2], plain[2], cen[3];
     pearson_meet<kWaves>(p, base, d, plain, cen);
     if (threadIdx.x == 0) {
         PearPart& o = part[(int64_t)c * kPearParts + blockIdx.x];
